@@ -221,6 +221,15 @@ sv_status sv_check_pass_layouts(int d, int gateset, int zchain, int xpair, int* 
  * summed amplitude by amplitude); SV_EINVAL names the first failing unit. */
 sv_status sv_check_spec_layouts(int d, int gateset, int zchain, int* n_units);
 
+/* Host-side self-check of the basis-change passes sv_run_rounds (d = 5) and
+ * sv_run_batch (d = 4) use for (d, gateset) when the data ZZ layer is off: the
+ * chains take every check once and in order with its qubits in its basis, the
+ * round ends where it began, both layouts of every pass cover its tile, the
+ * regroup brings every amplitude to its place, and the flipped qubits are the
+ * planned ones.  No device work.  *n_passes receives the passes per round, 0
+ * below 12 qubits (no such passes); SV_EINVAL names the first failure. */
+sv_status sv_check_flip_layouts(int d, int gateset, int* n_passes);
+
 typedef struct sv_job {
   int d;               /* code distance, 2..5 */
   int gateset;         /* sv_gateset */
@@ -267,14 +276,17 @@ typedef struct sv_result {
  * are enumerated in circuit order: per round, per stabilizer, one per noise
  * location and then one for the measurement; after the last round one per
  * final data measurement.  Synchronous.  Records are the raw ancilla bits.
- * With zeta = 0 and d >= 4 (outcomes then mostly repeat from round to round)
- * the register passes are speculative: a pair of X checks or a chain of Z
- * checks is summed and applied in one pass with predicted outcomes (the
- * trivial ones in the first round, the previous round's after that) and the
- * pass runs again when a drawn outcome differs; records, p1 and states are
- * those of the plain passes.  The environment variable QECSV_SPEC = 0 / 1
- * turns this off / on whatever zeta is (not with the dense crosstalk, which
- * always uses the plain passes). */
+ * With zeta = 0 and d = 5 the register passes change the basis of up to 12
+ * qubits each, so that chains of up to six checks of either type are summed
+ * and applied at once (five passes a round; sv_tuning's zchain, xpair and
+ * pass_wgs_per_cu do not apply).  With zeta = 0 and d = 4 (outcomes then
+ * mostly repeat from round to round) they are speculative: a pair of X checks
+ * or a chain of Z checks is summed and applied in one pass with predicted
+ * outcomes (the trivial ones in the first round, the previous round's after
+ * that) and the pass runs again when a drawn outcome differs.  Records, p1 and
+ * states are those of the plain passes.  The environment variable QECSV_SPEC =
+ * 0 / 1 asks for the plain / the speculative passes whatever zeta is (not with
+ * the dense crosstalk, which always uses the plain passes). */
 sv_status sv_run_rounds(const sv_job* job, sv_result* res);
 
 /* The same run enqueued without waiting, so that jobs on several streams
@@ -369,8 +381,9 @@ sv_status sv_tuning_load(const char* path);
  * per SIMD; the environment variable QECSV_BATCH_SPLIT = 1, 2 or 4 forces the
  * count); d = 4 keeps the registers in HBM and runs the trajectories in
  * lockstep through the register passes, the trajectory being a grid
- * dimension; with zeta = 0 those passes are speculative as in sv_run_rounds
- * (each slot then holds two registers; QECSV_SPEC = 0 / 1 forces the mode).
+ * dimension; with zeta = 0 those passes change basis as sv_run_rounds' do at
+ * d = 5 (three a round; QECSV_SPEC = 0 / 1 asks for the plain / the
+ * speculative passes, the latter with two registers a slot).
  * Synchronous. */
 typedef struct sv_batch_job {
   int d;                    /* 2..4 */

@@ -121,6 +121,7 @@ _SIGS = {
                                              ctypes.POINTER(ctypes.c_int)]),
     "sv_check_spec_layouts": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_int,
                                              ctypes.POINTER(ctypes.c_int)]),
+    "sv_check_flip_layouts": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]),
     "sv_template_info": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int),
                                         ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "sv_run_rounds": (ctypes.c_int, [ctypes.POINTER(Job), ctypes.POINTER(Result)]),
@@ -224,6 +225,14 @@ def check_spec_layouts(d, gateset, zchain=4):
     passes' layouts; returns the units per round (0: the plain passes run)."""
     n = ctypes.c_int()
     _check(lib().sv_check_spec_layouts(d, _GATESETS[gateset], int(zchain), ctypes.byref(n)))
+    return n.value
+
+
+def check_flip_layouts(d, gateset):
+    """sv_check_flip_layouts: host-side consistency of the basis-change
+    passes; returns the passes per round (0: none for this distance)."""
+    n = ctypes.c_int()
+    _check(lib().sv_check_flip_layouts(d, _GATESETS[gateset], ctypes.byref(n)))
     return n.value
 
 

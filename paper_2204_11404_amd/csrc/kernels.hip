@@ -13,6 +13,8 @@
 //                  register (highest label first) from a two-level sum tree.
 //   k_commit       staged results of a replayed (graph) trajectory.
 // General register ops are in kernels_ops.hip.
+#pragma once
+
 #include "qec_common.h"
 
 namespace qec {
@@ -61,7 +63,12 @@ struct RegBuf {
       const unsigned long long x = __double_as_longlong(a.re), y = __double_as_longlong(a.im);
       __attribute__((ext_vector_type(4))) unsigned v = {(unsigned)x, (unsigned)(x >> 32), (unsigned)y,
                                                         (unsigned)(y >> 32)};
-      __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, soff, 0);
+      // the offsets added up, not as a scalar one: a store of more than eight
+      // bytes reads its data late, and the compiler keeps its registers from
+      // being written right behind it only in the form without a scalar
+      // offset (with one, a loaded chip stored amplitudes whose low words had
+      // already been overwritten: errors of 1e-7 at random places)
+      __builtin_amdgcn_raw_buffer_store_b128(v, r, voff + soff, 0, 0);
     } else {
       __attribute__((ext_vector_type(2))) unsigned v = {__float_as_uint(a.re), __float_as_uint(a.im)};
       __builtin_amdgcn_raw_buffer_store_b64(v, r, voff, soff, 0);
@@ -206,7 +213,7 @@ __device__ __forceinline__ double clamp_p1(double p1) {
 // Draws and Kraus pairs of every block instance of n_traj trajectories
 // (draw streams traj0 + i, or *stream for a single trajectory when given);
 // twirl_thr: per-site sin^2 eps of the Pauli-twirled model, or null.
-__global__ void k_prepare(const TBlock* __restrict__ blocks, int n_stab, int rounds,
+static __global__ void k_prepare(const TBlock* __restrict__ blocks, int n_stab, int rounds,
                           int draws_per_round, uint64_t seed, uint64_t traj0, int n_traj,
                           double p, const double* __restrict__ eps_site,
                           BlockRT* __restrict__ out, int* __restrict__ err,
@@ -242,7 +249,7 @@ __global__ void k_prepare(const TBlock* __restrict__ blocks, int n_stab, int rou
 // thread per (trajectory, block instance, input label x) runs the circuit on
 // |anc 0, data x> with the instance's drawn Paulis and writes column x of K_0
 // and K_1 (the same draws as k_prepare).
-__global__ __launch_bounds__(128) void k_prepare_dense(
+static __global__ __launch_bounds__(128) void k_prepare_dense(
     const TBlock* __restrict__ blocks, int n_stab, int rounds, int draws_per_round, uint64_t seed,
     uint64_t traj0, int n_traj, double p, const double* __restrict__ eps_site,
     BlockDense* __restrict__ out, int* __restrict__ err, const uint64_t* __restrict__ stream,
@@ -280,7 +287,7 @@ __global__ __launch_bounds__(128) void k_prepare_dense(
 
 // cos / sin of every gate site's angle for each trajectory slot (one thread
 // per slot and op of the round template).
-__global__ void k_site_cs(const TBlock* __restrict__ blocks, int n_stab,
+static __global__ void k_site_cs(const TBlock* __restrict__ blocks, int n_stab,
                           const double* __restrict__ eps, int eps_stride, int n_sites, int slots,
                           double* __restrict__ cs) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -299,7 +306,7 @@ __global__ void k_site_cs(const TBlock* __restrict__ blocks, int n_stab,
 // Kraus pairs of round r for `slots` trajectories with their own seed, draw
 // stream and p: 16 lanes per block instance, lane x evaluates draw x (shared
 // with the group by shuffles) and then the circuit's column x.
-__global__ __launch_bounds__(256) void k_prepare_round(
+static __global__ __launch_bounds__(256) void k_prepare_round(
     const TBlock* __restrict__ blocks, int n_stab, int r, int draws_round,
     const uint64_t* __restrict__ seeds, const uint64_t* __restrict__ streams,
     const double* __restrict__ pvec, const double* __restrict__ cs, int n_sites, int slots,
@@ -1768,7 +1775,7 @@ __device__ __forceinline__ void chain_tree_lds(int lb, V v, double* full) {
 // workgroup of a slot to finish (ticket counter, reset for the next use)
 // decides.  split = 0, grid (slots): one workgroup per slot, thread a sums
 // sum a serially (few partials: many small registers side by side).
-__global__ __launch_bounds__(256) void k_udecide(const double* __restrict__ partials, int n,
+static __global__ __launch_bounds__(256) void k_udecide(const double* __restrict__ partials, int n,
                                                  int lb, const BlockRT* __restrict__ rtb,
                                                  Decision* __restrict__ dec_b,
                                                  uint8_t* __restrict__ rec_b,
@@ -1843,7 +1850,7 @@ __global__ __launch_bounds__(256) void k_udecide(const double* __restrict__ part
 // per slot (lockstep launches: thousands of slots, each with few partials,
 // and no fence per workgroup).  A slot's tables, records, control record,
 // partials and ticket are found with the lockstep strides.
-__global__ __launch_bounds__(256) void k_sdecide(const double* __restrict__ partials, int n, int len, int tree,
+static __global__ __launch_bounds__(256) void k_sdecide(const double* __restrict__ partials, int n, int len, int tree,
                                                  const BlockRT* __restrict__ rtb, const Decision* __restrict__ dec_a,
                                                  Decision* __restrict__ dec_b, uint8_t* __restrict__ rec_b,
                                                  double* __restrict__ p1_b, SpecCtl* __restrict__ ctl,
@@ -1957,7 +1964,7 @@ __global__ __launch_bounds__(256) void k_sdecide(const double* __restrict__ part
 
 // Decision records of n trajectory slots (stride apart) for a register that
 // logical |0> is written into: norm 1, frame 0.
-__global__ void k_dec_init(Decision* __restrict__ d, int n, size_t stride) {
+static __global__ void k_dec_init(Decision* __restrict__ d, int n, size_t stride) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) d[(size_t)i * stride] = Decision{1.0, 0, 0u};
 }
@@ -2013,10 +2020,12 @@ __global__ __launch_bounds__(1024) void k_final_measure(const T* __restrict__ st
                                                          const int* __restrict__ rounds,
                                                          uint64_t draws_round,
                                                          const Decision* __restrict__ dfin,
-                                                         size_t dfin_stride) {
+                                                         size_t dfin_stride, int xframe) {
   const int slot = blockIdx.x;
-  // Pauli-X frame of the register: logical bit q = physical bit q ^ phi_q
-  const uint32_t phi = dfin ? dfin[(size_t)slot * dfin_stride].phi : 0u;
+  // Pauli frame of the register: logical bit q = physical bit q ^ phi_q (the
+  // X-type frame, or after a transform of every qubit the Z-type one)
+  const Decision* const fd = dfin ? dfin + (size_t)slot * dfin_stride : nullptr;
+  const uint32_t phi = fd ? (xframe ? fd->phix : fd->phi) : 0u;
   st += (size_t)slot * st_stride;
   sums += (size_t)slot << (n - cb);
   bits += (size_t)slot * n;
@@ -2070,7 +2079,7 @@ __global__ __launch_bounds__(1024) void k_final_measure(const T* __restrict__ st
 
 // Replayed trajectories: copy the staged records, p1 trace and final bits of
 // trajectory *cur to their slots, then advance *cur and its draw stream.
-__global__ void k_commit(const uint8_t* __restrict__ rec_s, const double* __restrict__ p1_s,
+static __global__ void k_commit(const uint8_t* __restrict__ rec_s, const double* __restrict__ p1_s,
                          const uint8_t* __restrict__ bits_s, uint8_t* __restrict__ rec,
                          double* __restrict__ p1, uint8_t* __restrict__ bits, int per_traj, int n,
                          uint64_t* __restrict__ cur, uint64_t* __restrict__ stream, uint64_t traj0) {

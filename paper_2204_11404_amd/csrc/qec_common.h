@@ -557,6 +557,8 @@ struct Decision {
   double Sm;
   int m;
   uint32_t phi;
+  uint32_t phix;  // passes with a basis change: the Z-type frame and the sign (see FlipPass)
+  int neg;
 };
 
 // ------------------------------------------------------------ pass units --
@@ -655,6 +657,82 @@ struct UnitPass {
   int aw[kChainMax], bw[kChainMax];
   uint32_t a_j_loc[kChainMax][16];  // member-i local index carried by slot j's bits (layout 1)
   uint32_t b_j_loc[kChainMax][16];
+};
+
+// A pass with a basis change (k_flip): apply chain A, transform the flipped
+// qubits, sum chain B.  Chains run over consecutive checks of either type,
+// each member diagonal in the basis its qubits are in at that point.  A tile
+// has 2^12 amplitudes: the three lowest bits (on lane bits 0..2 throughout),
+// four slot bits s0 of layout 1 (load), four slot bits s2 of layout 2 (store)
+// and one more, e.  Thread-index bits: layout 1 {0, 1, 2, s2[0], s2[1], e,
+// s2[2], s2[3]}, layout 2 {0, 1, 2, s0[0..3], e}; without a regroup (two = 0)
+// layout 1 serves for the store too.  Local indices of a chain's members are
+// packed four bits each into one word, XOR-linear in the global index.
+//
+// Slot bits 0, 1 of the layout of the store carry qubits of B's member mp
+// alone (or none), slot bits 2, 3 of member mq alone; ord lists B's members
+// with mp and mq last.
+struct FlipPass {
+  int n_outer;
+  int la, lb;
+  int ax, bx;          // bit i: member i is an X check
+  int touch;           // bit k: member 2 k or 2 k + 1 of A has a qubit on layout 1's slots
+  int m0, m2;          // flipped slot bits of layout 1 / layout 2
+  int lane5, low;      // e is flipped; flipped bits among the three lowest
+  int two;
+  int plain;           // the store writes amplitude g at place g (the last pass of a trajectory)
+  int n_brel;          // leading outer bits that carry qubits of B
+  double norm;         // 2^(-flips / 2); the initial state's pass: its amplitude
+  uint32_t outer_bit[20];
+  uint32_t s0[4], s2[4], e;
+  uint32_t a_tid[8], a_slot[4], a_outer[20];  // packed local indices of A (layout 1)
+  uint32_t b_tid[8], b_slot[4], b_outer[20];  // of B, in the layout of the store
+  uint32_t aq[kChainMax][4], bq[kChainMax][4];
+  int aw[kChainMax], bw[kChainMax];
+  int ord[kChainMax];
+  // the initial state's pass: code words with a pivot among the
+  // untransformed bits (zmask), and parity conditions on the transformed ones
+  int n_piv, n_par;
+  uint32_t zmask;
+  uint32_t piv_bit[16], piv_vec[16], par_vec[16];
+  int par_pos[16];
+};
+
+// Where amplitude g of a register in the mixed basis is kept: some low bits
+// XOR the high ones, so that the pieces of a tile that spans high bits do not
+// all sit a power of two apart (the same memory channels).  d = 5, tiles on
+// bits 12..20: complex128 279 -> 199 us a pass, complex64 141 -> 105 us; the
+// folds are the best of several measured for each precision.  The three
+// lowest bits stay (runs of eight amplitudes).
+template <typename T>
+QEC_HD uint32_t flip_place(uint32_t g) {
+  if constexpr (sizeof(T) == 8) return g ^ ((((g >> 12) ^ (g >> 21)) & 0x1FFu) << 3);
+  else return g ^ ((((g >> 12) ^ (g >> 18)) & 0x3Fu) << 5);
+}
+
+// Regroup of a tile through LDS between the two layouts.  An amplitude's
+// place is a sum of strides, one per tile bit: a thread's part plus a constant
+// per slot, which the LDS instructions carry as their offset.  The strides of
+// thread bits 3 and 4 are 8 and 16 modulo the 32 eight-byte banks in both
+// layouts, so 32 lanes reach 32 banks.  complex64 moves whole amplitudes (two
+// barriers a tile); complex128 real parts, then imaginary parts, through a
+// buffer of the same size (four barriers, but three workgroups per CU).
+struct FlipLds {
+  // strides of s0[0..3], s2[0..3], e (bits 0..2: 1, 2, 4); each exceeds the
+  // sum of the smaller ones, so no two places coincide
+  static constexpr int s0[4] = {40, 80, 304, 608};
+  static constexpr int s2[4] = {8, 16, 1216, 2432};
+  static constexpr int e = 152;
+  static constexpr int kSize = 4864;
+  // offset of slot j in layout 1 as written (l5: e and s0[3] have changed
+  // places) and in layout 2 as read
+  template <bool L5>
+  __host__ __device__ static constexpr int w(int j) {
+    return (j & 1 ? s0[0] : 0) + (j & 2 ? s0[1] : 0) + (j & 4 ? s0[2] : 0) + (j & 8 ? (L5 ? e : s0[3]) : 0);
+  }
+  __host__ __device__ static constexpr int r(int j) {
+    return (j & 1 ? s2[0] : 0) + (j & 2 ? s2[1] : 0) + (j & 4 ? s2[2] : 0) + (j & 8 ? s2[3] : 0);
+  }
 };
 
 }  // namespace qec

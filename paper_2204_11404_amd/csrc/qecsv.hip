@@ -28,6 +28,7 @@
 #include "qecsv.h"
 #include "qec_common.h"
 #include "kernels.hip"
+#include "passes.h"
 #include "kernels_ops.hip"
 #include "kernels_batch.hip"
 
@@ -813,104 +814,14 @@ void launch_wht_all(hipStream_t s, T* st, int n) {
   }
 }
 
-// One pass kernel launch; the instantiation with the dense Kraus code exists
-// only for unit pairs with an X check, the one summing a Z chain amplitude by
-// amplitude (bmode 0) only for a Z chain B.
-template <typename T, int AK, int AP, int BK, int BP>
-void launch_pass(bool dense, bool bm0, dim3 g, dim3 b, hipStream_t s, T* st, const UnitPass* pd,
-                 const JobConst* jc, const BlockRT* rta, const BlockRT* rtb, const Decision* da, Decision* db,
-                 double* part, int rev, SlotStrides ss, const BlockDense* dna, const BlockDense* dnb) {
-#define QEC_K(DNV, BMV)                                                                                  \
-  hipLaunchKernelGGL((k_upass<T, AK, AP, BK, BP, DNV, BMV, 0>), g, b, 0, s, st, pd, jc, rta, rtb, da, db, part, \
-                     rev, ss, dna, dnb, SpecArgs{})
-  if constexpr (BK == U_Z) {
-    if (bm0) {
-      if constexpr (AK == U_X) {
-        if (dense) {
-          QEC_K(true, true);
-          return;
-        }
-      }
-      QEC_K(false, true);
-      return;
-    }
-  }
-  if constexpr ((AK == U_X || BK == U_X) && AK != U_XP && BK != U_XP) {  // pairs are never dense
-    if (dense) {
-      QEC_K(true, false);
-      return;
-    }
-  }
-  QEC_K(false, false);
-#undef QEC_K
+// Pass launches (compiled apart from this file, see passes.inc): a status of
+// the launch tables as an sv_status.
+sv_status pass_status(int r) {
+  if (r == kLaunchNoTable) return fail(SV_EINVAL, "dense unit without its Kraus table");
+  if (r == kLaunchNoFit) return fail(SV_EINVAL, "pass layout does not fit a tile");
+  if (r != 0) return fail(SV_EINVAL, "no pass kernel for these units");
+  return SV_OK;
 }
-
-// Launches the pass kernel instantiated for the descriptor's unit kinds.
-template <typename T>
-sv_status launch_upass(const UnitPass& h, dim3 g, dim3 b, hipStream_t s, T* st, const UnitPass* pd,
-                       const JobConst* jc, const BlockRT* rta, const BlockRT* rtb,
-                       const Decision* da, Decision* db, double* part, int rev,
-                       SlotStrides ss = SlotStrides{0, 0, 0}, const BlockDense* dna = nullptr,
-                       const BlockDense* dnb = nullptr) {
-#define QEC_UP(AK, AP, BK, BP)                                                                      \
-  if (h.akind == AK && ap == AP && h.bkind == BK && bp == BP) {                                     \
-    launch_pass<T, AK, AP, BK, BP>(h.adense || h.bdense, h.bkind == U_Z && h.bmode == 0, g, b, s, st, pd, jc, \
-                                   rta, rtb, da, db, part, \
-                                   rev, ss, dna, dnb);                                              \
-    return SV_OK;                                                                                   \
-  }
-#define QEC_UP_B(AK, AP) \
-  QEC_UP(AK, AP, U_X, 2) QEC_UP(AK, AP, U_X, 4) QEC_UP(AK, AP, U_Z, 1) QEC_UP(AK, AP, U_Z, 2) \
-  QEC_UP(AK, AP, U_Z, 3) QEC_UP(AK, AP, U_Z, 4) QEC_UP(AK, AP, U_Z, 5) QEC_UP(AK, AP, U_Z, 6)
-  if ((h.adense && !dna) || (h.bdense && !dnb)) return fail(SV_EINVAL, "dense unit without its Kraus table");
-  if (h.tb <= 0) return fail(SV_EINVAL, "pass layout does not fit a tile");
-  const int ap = h.akind == U_X ? h.wa : (h.akind == U_Z ? h.la : 0);
-  const int bp = h.bkind == U_X ? h.wb : (h.bkind == U_Z ? h.lb : 0);
-  QEC_UP_B(U_INIT, 0)
-  QEC_UP_B(U_X, 2) QEC_UP_B(U_X, 4) QEC_UP(U_X, 2, U_NONE, 0) QEC_UP(U_X, 4, U_NONE, 0)
-  QEC_UP_B(U_Z, 1) QEC_UP_B(U_Z, 2) QEC_UP_B(U_Z, 3) QEC_UP_B(U_Z, 4) QEC_UP_B(U_Z, 5) QEC_UP_B(U_Z, 6)
-  QEC_UP(U_Z, 1, U_NONE, 0) QEC_UP(U_Z, 2, U_NONE, 0) QEC_UP(U_Z, 3, U_NONE, 0) QEC_UP(U_Z, 4, U_NONE, 0)
-  QEC_UP(U_Z, 5, U_NONE, 0) QEC_UP(U_Z, 6, U_NONE, 0)
-  // X pairs (weights handled at run time)
-  QEC_UP(U_INIT, 0, U_XP, 0) QEC_UP(U_X, 2, U_XP, 0) QEC_UP(U_X, 4, U_XP, 0)
-  QEC_UP(U_Z, 1, U_XP, 0) QEC_UP(U_Z, 2, U_XP, 0) QEC_UP(U_Z, 3, U_XP, 0) QEC_UP(U_Z, 4, U_XP, 0)
-  QEC_UP(U_Z, 5, U_XP, 0) QEC_UP(U_Z, 6, U_XP, 0)
-  QEC_UP_B(U_XP, 0) QEC_UP(U_XP, 0, U_XP, 0) QEC_UP(U_XP, 0, U_NONE, 0)
-  QEC_UP(U_INIT, 0, U_NONE, 0)  // logical |0> alone (speculative runs)
-#undef QEC_UP_B
-#undef QEC_UP
-  return fail(SV_EINVAL, "no pass kernel for units (%d,%d)->(%d,%d)", h.akind, h.wa, h.bkind, h.wb);
-}
-
-// A speculative unit's prediction pass (redo = false) or redo: reads st,
-// writes sa.out; the unit is A (an X check or pair, B none) or B (a Z chain,
-// A the pending renormalisation).
-template <typename T>
-sv_status launch_spass(const UnitPass& h, bool redo, dim3 g, dim3 b, hipStream_t s, T* st, const UnitPass* pd,
-                       const JobConst* jc, const BlockRT* rta, const BlockRT* rtb, const Decision* da,
-                       Decision* db, double* part, int rev, SpecArgs sa, SlotStrides ss) {
-#define QEC_SP(AK, AP, BK, BP)                                                                              \
-  if (h.akind == AK && ap == AP && h.bkind == BK && bp == BP) {                                             \
-    if (redo)                                                                                               \
-      hipLaunchKernelGGL((k_uredo<T, AK, AP, BK, BP>), g, b, 0, s, st, pd, jc, rta, rtb, da, db, part, rev, \
-                         ss, nullptr, nullptr, sa);                                                         \
-    else                                                                                                    \
-      hipLaunchKernelGGL((k_upass<T, AK, AP, BK, BP, false, false, 1>), g, b, 0, s, st, pd, jc, rta, rtb,   \
-                         da, db, part, rev, ss, nullptr, nullptr, sa);                                      \
-    return SV_OK;                                                                                           \
-  }
-  if (h.tb <= 0) return fail(SV_EINVAL, "pass layout does not fit a tile");
-  if (h.adense || h.bdense || (h.bkind == U_Z && h.bmode == 0))
-    return fail(SV_EINVAL, "no speculative pass for this unit");
-  const int ap = h.akind == U_X ? h.wa : 0;
-  const int bp = h.bkind == U_Z ? h.lb : 0;
-  QEC_SP(U_X, 2, U_NONE, 0) QEC_SP(U_X, 4, U_NONE, 0) QEC_SP(U_XP, 0, U_NONE, 0)
-  QEC_SP(U_SC, 0, U_Z, 1) QEC_SP(U_SC, 0, U_Z, 2) QEC_SP(U_SC, 0, U_Z, 3) QEC_SP(U_SC, 0, U_Z, 4)
-  QEC_SP(U_SC, 0, U_Z, 5) QEC_SP(U_SC, 0, U_Z, 6)
-#undef QEC_SP
-  return fail(SV_EINVAL, "no speculative pass for units (%d,%d)->(%d,%d)", h.akind, h.wa, h.bkind, h.lb);
-}
-
 
 // Units of one round with X pairs (pairs on): each run of consecutive X
 // checks is cut into single checks and pairs of consecutive checks, the
@@ -1039,6 +950,318 @@ std::vector<UnitPass> make_spec_passes(int n, int tb, const Template& tp, const 
   return pds;
 }
 
+// ------------------------------------------- passes with a basis change --
+// Plan of one round without the data ZZ layer (see k_flip): consecutive
+// checks in chains of at most kChainMax members, each chain preceded by the
+// flips that bring its qubits into their bases, at most nine beside the three
+// lowest bits (a tile holds no more); room that a chain leaves is filled with
+// the flips needed soonest.  Every round starts and ends with all qubits in
+// the computational basis.  Empty if some check needs more flips than fit.
+struct FlipPlan {
+  std::vector<Unit> units;
+  std::vector<uint32_t> flips;     // before the sums of unit u
+  std::vector<FlipPass> passes;    // [0] initial state, [1 + u] apply u, [nu + 1] apply the last one alone
+};
+constexpr int kFlipLow = 3;        // lowest bits, always in the tile and on the lanes
+constexpr int kFlipHigh = kTileMax - kFlipLow;
+
+uint32_t check_mask(const TBlock& b) {
+  uint32_t m = 0;
+  for (int l = 0; l < b.w; ++l) m |= 1u << b.qubit[l];
+  return m;
+}
+
+bool plan_flips(int n, const Template& tp, FlipPlan& P) {
+  const uint32_t low = (1u << kFlipLow) - 1;
+  const int ns = (int)tp.blocks.size();
+  uint32_t xb = 0;  // qubits in the Hadamard basis
+  for (int c = 0; c < ns;) {
+    uint32_t F = 0, locked = 0;
+    int len = 0;
+    for (; len < kChainMax && c + len < ns; ++len) {
+      const TBlock& b = tp.blocks[c + len];
+      const uint32_t q = check_mask(b);
+      const uint32_t need = q & (b.type == 0 ? ~(xb ^ F) : (xb ^ F));
+      if ((need & locked) || __builtin_popcount((F | need) & ~low) > kFlipHigh) break;
+      F |= need;
+      locked |= q;
+    }
+    if (len == 0) return false;
+    for (int k = c + len; k < ns; ++k) {
+      const TBlock& b = tp.blocks[k];
+      for (int l = 0; l < b.w; ++l) {
+        const uint32_t bit = 1u << b.qubit[l];
+        if (locked & bit) continue;
+        locked |= bit;
+        const bool in_x = (xb & bit) != 0;
+        if (in_x == (b.type == 0)) continue;
+        if (__builtin_popcount((F | bit) & ~low) <= kFlipHigh) F |= bit;
+      }
+    }
+    xb ^= F;
+    P.units.push_back({U_NONE, c, len});
+    P.flips.push_back(F);
+    c += len;
+  }
+  (void)n;
+  return xb == 0;
+}
+
+// Pass descriptor: apply A (null: write the initial state), flip F, sum B
+// (null: none).
+FlipPass make_flip_pass(int n, const Template& tp, const Unit* A, const Unit* B, uint32_t F) {
+  FlipPass pd{};
+  auto members = [&](const Unit* U, uint32_t (*q)[4], int* w, int& xm) {
+    uint32_t m = 0;
+    if (!U) return m;
+    for (int i = 0; i < U->len; ++i) {
+      const TBlock& b = tp.blocks[U->first + i];
+      w[i] = b.w;
+      if (b.type == 0) xm |= 1 << i;
+      for (int l = 0; l < b.w; ++l) q[i][l] = 1u << b.qubit[l];
+      m |= check_mask(b);
+    }
+    return m;
+  };
+  pd.la = A ? A->len : 0;
+  pd.lb = B ? B->len : 0;
+  members(A, pd.aq, pd.aw, pd.ax);
+  const uint32_t UB = members(B, pd.bq, pd.bw, pd.bx);
+  pd.norm = std::pow(2.0, -0.5 * __builtin_popcount(F));
+  const uint32_t low = (1u << kFlipLow) - 1;
+  pd.low = (int)(F & low);
+  // the tile: the flips, then B's qubits (so that a workgroup's tiles can
+  // differ outside them), then the lowest
+  uint32_t tile = low | F;
+  auto take = [&](uint32_t from, int most) {
+    for (int q = 0; q < n && __builtin_popcount(tile) < most; ++q)
+      if ((from >> q) & 1) tile |= 1u << q;
+  };
+  // (the last pass of a trajectory: the lowest ones, its tiles are stored in
+  // plain order)
+  if (B) take(UB, kTileMax);
+  take(~0u, kTileMax);
+  std::vector<int> nine;
+  for (int q = kFlipLow; q < n; ++q)
+    if ((tile >> q) & 1) nine.push_back(q);
+  // four slot bits of layout 1, four of layout 2, and the one left over (on
+  // lane bit 5 of layout 1): as few members of A as possible on layout 1's
+  // slots, the one left over not flipped if that is possible, and the slots
+  // of the layout of the store in two pairs, each carrying qubits of at most
+  // one member of B that has it to itself
+  const int two = (F & ~low) || !B ? 1 : 0;
+  pd.plain = !B;
+  auto touches = [&](uint32_t S) {
+    int t = 0;
+    for (int i = 0; i < pd.la; ++i)
+      for (int l = 0; l < pd.aw[i]; ++l)
+        if (pd.aq[i][l] & S) t |= 1 << (i / 2);
+    return t;
+  };
+  // the member of B that has qubit q to itself: -1 none has it, -2 several do
+  auto owner = [&](int q) {
+    int o = -1;
+    for (int i = 0; i < pd.lb; ++i)
+      for (int l = 0; l < pd.bw[i]; ++l)
+        if (pd.bq[i][l] == (1u << q)) o = o == -1 ? i : -2;
+    return o;
+  };
+  // four store slots ordered as two pairs, and the pairs' members
+  auto pair_up = [&](std::vector<int>& J, int& mp, int& mq) {
+    static const int split[3][4] = {{0, 1, 2, 3}, {0, 2, 1, 3}, {0, 3, 1, 2}};
+    for (const int* t : split) {
+      const int o[4] = {owner(J[t[0]]), owner(J[t[1]]), owner(J[t[2]]), owner(J[t[3]])};
+      auto one = [](int x, int y, int& m) {
+        m = std::max(x, y);
+        return x != -2 && y != -2 && (x == y || x == -1 || y == -1);
+      };
+      int p, q;
+      if (!one(o[0], o[1], p) || !one(o[2], o[3], q) || (p >= 0 && p == q)) continue;
+      if (pd.lb == 1 && q >= 0) continue;  // a single check is the first pair's
+      for (int m = 0; p < 0 && m < pd.lb; ++m)
+        if (m != q) p = m;
+      for (int m = 0; q < 0 && m < pd.lb && pd.lb > 1; ++m)
+        if (m != p) q = m;
+      J = {J[t[0]], J[t[1]], J[t[2]], J[t[3]]};
+      mp = p;
+      mq = q;
+      return true;
+    }
+    return false;
+  };
+  int best = 1 << 30, mp = 0, mq = 0;
+  std::vector<int> J1, J2;
+  int E = 0;
+  for (int S = 0; S < (1 << kFlipHigh); ++S) {
+    if (__builtin_popcount((unsigned)S) != 4) continue;
+    for (int e = 0; e < kFlipHigh; ++e) {
+      if ((S >> e) & 1) continue;
+      std::vector<int> a, b;
+      uint32_t s0 = 0;
+      for (int i = 0; i < kFlipHigh; ++i) {
+        if ((S >> i) & 1) {
+          a.push_back(nine[i]);
+          s0 |= 1u << nine[i];
+        } else if (i != e) {
+          b.push_back(nine[i]);
+        }
+      }
+      const int cost = 4 * __builtin_popcount((unsigned)touches(s0)) + (((F >> nine[e]) & 1) ? 8 : 0);
+      // among equals the highest bits on layout 1's slots: its lanes keep the
+      // low ones
+      if (cost > best) continue;
+      int p = 0, q = 0;
+      if (B && !pair_up(two ? b : a, p, q)) continue;
+      best = cost;
+      J1 = a;
+      J2 = b;
+      E = nine[e];
+      mp = p;
+      mq = q;
+    }
+  }
+  if (best == 1 << 30) {
+    pd.lb = -1;  // no such slots: never launched
+    return pd;
+  }
+  const uint32_t bestS = (1u << J1[0]) | (1u << J1[1]) | (1u << J1[2]) | (1u << J1[3]);
+  const int bestE = E;
+  {
+    int k = 0;
+    for (int m = 0; m < pd.lb; ++m)
+      if (m != mp && (pd.lb == 1 || m != mq)) pd.ord[k++] = m;
+    if (pd.lb > 1) pd.ord[k++] = mp;
+    if (pd.lb > 0) pd.ord[k] = pd.lb > 1 ? mq : mp;
+  }
+  pd.touch = touches(bestS);
+  pd.two = two;
+  for (int b = 0; b < 4; ++b) {
+    pd.s0[b] = 1u << J1[b];
+    pd.s2[b] = 1u << J2[b];
+    if ((F >> J1[b]) & 1) pd.m0 |= 1 << b;
+    if ((F >> J2[b]) & 1) pd.m2 |= 1 << b;
+  }
+  pd.e = 1u << bestE;
+  pd.lane5 = (F >> bestE) & 1;
+  // outer bits: B's qubits first, then ascending, so that the highest bits
+  // change last
+  for (int pass = 0; pass < 2; ++pass)
+    for (int q = 0; q < n; ++q)
+      if (!((tile >> q) & 1) && (((UB >> q) & 1) != 0) == (pass == 0)) pd.outer_bit[pd.n_outer++] = 1u << q;
+  pd.n_brel = __builtin_popcount(UB & ~tile);
+  auto packed = [](uint32_t bit, int len, const uint32_t (*q)[4], const int* w) {
+    uint32_t x = 0;
+    for (int i = 0; i < len; ++i)
+      for (int l = 0; l < w[i]; ++l)
+        if (q[i][l] == bit) x |= 1u << (4 * i + l);
+    return x;
+  };
+  auto pa = [&](uint32_t bit) { return packed(bit, pd.la, pd.aq, pd.aw); };
+  auto pb = [&](uint32_t bit) { return packed(bit, pd.lb, pd.bq, pd.bw); };
+  const uint32_t t1[8] = {1u, 2u, 4u, pd.s2[0], pd.s2[1], pd.e, pd.s2[2], pd.s2[3]};
+  const uint32_t t2[8] = {1u, 2u, 4u, pd.s0[0], pd.s0[1], pd.s0[2], pd.s0[3], pd.e};
+  for (int i = 0; i < 8; ++i) {
+    pd.a_tid[i] = pa(t1[i]);
+    pd.b_tid[i] = pb(two ? t2[i] : t1[i]);
+  }
+  for (int b = 0; b < 4; ++b) {
+    pd.a_slot[b] = pa(pd.s0[b]);
+    pd.b_slot[b] = pb(two ? pd.s2[b] : pd.s0[b]);
+  }
+  for (int i = 0; i < pd.n_outer; ++i) {
+    pd.a_outer[i] = pa(pd.outer_bit[i]);
+    pd.b_outer[i] = pb(pd.outer_bit[i]);
+  }
+  return pd;
+}
+
+// The initial code state in the basis where the qubits T are transformed:
+// the code words are the span of the X checks (logical |0>), with X_L on the
+// first column too for logical |+>.
+void flip_init_state(const Template& tp, int d, bool plus, uint32_t T, FlipPass& pd) {
+  const int n = d * d;
+  std::vector<uint32_t> gens;
+  for (const TBlock& b : tp.blocks)
+    if (b.type == 0) gens.push_back(check_mask(b));
+  if (plus) {
+    uint32_t xl = 0;
+    for (int r = 0; r < d; ++r) xl |= 1u << (r * d);
+    gens.push_back(xl);
+  }
+  const uint32_t all = n == 32 ? ~0u : (1u << n) - 1;
+  pd.zmask = all & ~T;
+  // reduce over the untransformed bits first: the rows left without one span
+  // the code words within T
+  auto reduce = [](std::vector<uint32_t>& rows, uint32_t within, std::vector<uint32_t>& vec,
+                   std::vector<uint32_t>& piv) {
+    std::vector<uint32_t> rest;
+    for (uint32_t v : rows) {
+      for (size_t i = 0; i < vec.size(); ++i)
+        if (v & piv[i]) v ^= vec[i];
+      if (!(v & within)) {
+        if (v) rest.push_back(v);
+        continue;
+      }
+      const uint32_t p = (v & within) & (0u - (v & within));
+      for (uint32_t& o : vec)
+        if (o & p) o ^= v;
+      vec.push_back(v);
+      piv.push_back(p);
+    }
+    // rows set aside early may hold pivots found later
+    for (uint32_t& v : rest)
+      for (size_t i = 0; i < vec.size(); ++i)
+        if (v & piv[i]) v ^= vec[i];
+    rows = rest;
+  };
+  std::vector<uint32_t> zv, zp, tv, tpv;
+  reduce(gens, pd.zmask, zv, zp);
+  reduce(gens, T, tv, tpv);
+  pd.n_piv = (int)zv.size();
+  pd.n_par = (int)tv.size();
+  for (int i = 0; i < pd.n_piv; ++i) {
+    pd.piv_vec[i] = zv[i];
+    pd.piv_bit[i] = zp[i];
+  }
+  for (int i = 0; i < pd.n_par; ++i) {
+    pd.par_vec[i] = tv[i];
+    pd.par_pos[i] = __builtin_ctz(tpv[i]);
+  }
+  pd.norm = std::pow(2.0, pd.n_par - 0.5 * (pd.n_piv + pd.n_par) - 0.5 * __builtin_popcount(T));
+}
+
+FlipPlan make_flip_plan(int d, const Template& tp, bool plus) {
+  FlipPlan P;
+  const int n = d * d;
+  if (n < kTileMax || !plan_flips(n, tp, P)) return FlipPlan{};
+  const int nu = (int)P.units.size();
+  P.passes.resize(nu + 2);
+  P.passes[0] = make_flip_pass(n, tp, nullptr, &P.units[0], 0u);
+  flip_init_state(tp, d, plus, P.flips[0], P.passes[0]);
+  for (int u = 0; u < nu; ++u) {
+    const int v = (u + 1) % nu;
+    P.passes[1 + u] = make_flip_pass(n, tp, &P.units[u], &P.units[v], P.flips[v]);
+  }
+  P.passes[nu + 1] = make_flip_pass(n, tp, &P.units[nu - 1], nullptr, 0u);
+  for (const FlipPass& h : P.passes)
+    if (h.lb < 0) return FlipPlan{};
+  return P;
+}
+
+// Workgroups of a pass over one register, about `want`: n_cls_wg groups share
+// out the patterns of the outer bits that carry qubits of B, the workgroups
+// of a group the tiles of each pattern.
+struct FlipGrid {
+  unsigned wgs, n_cls_wg;
+};
+FlipGrid flip_grid(const FlipPass& h, unsigned want) {
+  const unsigned classes = 1u << h.n_brel, tiles = 1u << h.n_outer;
+  unsigned g = 1;
+  while (2 * g <= std::min(classes, want)) g *= 2;
+  const unsigned per = std::min(tiles / classes, std::max(1u, want / g));
+  return {g * per, g};
+}
+
 }  // namespace
 
 namespace {
@@ -1053,6 +1276,7 @@ struct RunStage {
   std::vector<double> eps, thr;
   std::vector<UnitPass> spds;   // speculative passes
   std::vector<uint8_t> pred0;   // first-round predictions
+  std::vector<FlipPass> fpds;   // passes with a basis change
 };
 
 // Every block of the template builds a monomial Kraus pair with no Pauli
@@ -1070,18 +1294,28 @@ bool template_is_monomial(const Template& tp, const std::vector<double>& eps) {
 
 int env_int(const char* name, int dflt);
 
+// Which passes run.  Without the data ZZ layer (zeta = 0) a d = 5 register
+// takes the passes with a basis change (k_flip): five a round, none redone,
+// one register (complex64, p = 2e-3: 0.63 ms a round against 1.55 with the
+// speculative units, complex128 1.2 against 2.4).  d = 4 keeps the
+// speculative units here, whose count callers read in passes_per_round;
+// batches of d = 4 trajectories take the basis change (run_batch_lockstep).
+// With the layer the plain passes run: it is diagonal in the computational
+// basis only, and the X checks cannot be summed together across it.
+// QECSV_SPEC = 0 / 1 asks for the plain / speculative passes whatever zeta is.
+//
 // done == nullptr: synchronous.  Otherwise every step is enqueued on the
 // job's stream, `done` is recorded after the results' copies to the host and
 // the call returns without waiting (no graph replay, no final states).
 // Speculative units (stream launches, asynchronous runs and graph replay of
 // a register of at least 2^12 amplitudes whose blocks are all monomial): each
 // unit is summed and applied in one pass with predicted outcomes, then
-// confirmed or redone (see k_sdecide); two register buffers.  They pay when
-// outcomes repeat from round to round, i.e. without the data ZZ layer: at
-// d = 5, p = 1e-3 a round takes 2.1 ms instead of 2.9 (complex128); with
-// zeta = 0.01 the layer turns 15 % of the X checks' outcomes from one round to
-// the next and the redos make them slower (3.1 against 3.0 ms).  So they run
-// when zeta = 0; QECSV_SPEC = 0 / 1 turns them off / on whatever zeta is.
+// confirmed or redone (see k_sdecide); two register buffers.  They pay against
+// the plain passes when outcomes repeat from round to round: at d = 5, p =
+// 1e-3 without the data ZZ layer a round takes 2.1 ms instead of 2.9
+// (complex128); with zeta = 0.01 the layer turns 15 % of the X checks'
+// outcomes from one round to the next and the redos make them slower (3.1
+// against 3.0 ms).
 template <typename T>
 sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                        const std::atomic<int>* cancel = nullptr, hipEvent_t done = nullptr) {
@@ -1090,11 +1324,15 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   const int tb = std::min(kTileMax, n);
   const int per_traj = R * ns;  // block instances (records) per trajectory
   const sv_tuning tune = tuning_for(d, job->dtype);
-  const std::vector<Unit> units = make_units_paired(tp, tune.zchain, n, tune.xpair);
+  const int spec_env = env_int("QECSV_SPEC", -1);
+  const bool xbasis = (job->flags & SV_RUN_XBASIS) != 0;
+  FlipPlan fplan;
+  if (spec_env < 0 && job->zeta == 0.0 && n > 16 && !tp.any_dense) fplan = make_flip_plan(d, tp, xbasis);
+  const bool flip = !fplan.units.empty();
+  const std::vector<Unit> units = flip ? fplan.units : make_units_paired(tp, tune.zchain, n, tune.xpair);
   const int nu = (int)units.size();
   const int per_units = R * nu;  // passes per trajectory after the first
-  const int spec_env = env_int("QECSV_SPEC", -1);
-  bool spec = (spec_env < 0 ? job->zeta == 0.0 : spec_env != 0) && n >= kTileMax && !tp.any_dense;
+  bool spec = !flip && (spec_env < 0 ? job->zeta == 0.0 : spec_env != 0) && n >= kTileMax && !tp.any_dense;
   std::vector<Unit> sunits;
   std::vector<UnitPass> spds;
   if (spec) {
@@ -1156,8 +1394,9 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   BlockDense* ddn = nullptr;  // dense Kraus pairs (blocks with crosstalk inside)
   if (tp.any_dense) HIP_OK(M.alloc(&ddn, dn_per_traj * chunk));
 
-  const std::vector<UnitPass> pds = make_unit_passes(n, tb, tp, units);
-  const bool xbasis = (job->flags & SV_RUN_XBASIS) != 0;
+  const std::vector<UnitPass> pds = flip ? std::vector<UnitPass>(nu + 2) : make_unit_passes(n, tb, tp, units);
+  FlipPass* dfpass = nullptr;
+  if (flip) HIP_OK(M.alloc(&dfpass, sizeof(FlipPass) * (nu + 2)));
   // speculative runs: the second register, pass descriptors, control records,
   // first-round predictions (the trivial outcome of every check), redo count
   T* st2 = nullptr;
@@ -1197,7 +1436,8 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   {
     // set-up copies from a staging block that a host function on the stream
     // deletes once the stream has passed them (the call may return first)
-    RunStage* stage = new RunStage{tp.blocks, pds, make_job_const(d, job->zeta, xbasis), eps, thr, spds, pred0};
+    RunStage* stage = new RunStage{tp.blocks, pds, make_job_const(d, job->zeta, xbasis), eps, thr, spds, pred0,
+                                   fplan.passes};
     const hipError_t e = [&]() -> hipError_t {
       hipError_t r;
       if ((r = hipMemcpyAsync(dblocks, stage->blocks.data(), sizeof(TBlock) * ns, hipMemcpyHostToDevice, s)))
@@ -1210,6 +1450,9 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                               hipMemcpyHostToDevice, s)))
         return r;
       if (dthr && (r = hipMemcpyAsync(dthr, stage->thr.data(), sizeof(double) * stage->thr.size(),
+                                      hipMemcpyHostToDevice, s)))
+        return r;
+      if (flip && (r = hipMemcpyAsync(dfpass, stage->fpds.data(), sizeof(FlipPass) * stage->fpds.size(),
                                       hipMemcpyHostToDevice, s)))
         return r;
       if (spec && (r = hipMemcpyAsync(dspass, stage->spds.data(), sizeof(UnitPass) * stage->spds.size(),
@@ -1252,6 +1495,9 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                               ? n_tiles
                               : std::min<size_t>(n_tiles, (size_t)device_cu_count() * tune.pass_wgs_per_cu);
   const dim3 grid((unsigned)pass_wgs), block((unsigned)std::max(64, 1 << (tb - 4)));
+  // passes with a basis change: as many workgroups as run at once (two per CU
+  // in complex128, three in complex64; see FlipShape)
+  const unsigned flip_wgs = (unsigned)device_cu_count() * (sizeof(T) == 8 ? 2u : 3u);
   const SlotStrides ss0{0, 0, 0};
   const int draws_round = tp.n_draws;
   const int last_t = job->n_traj - 1;
@@ -1261,28 +1507,42 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   auto traj_passes = [&](hipStream_t q, const BlockRT* rt, const BlockDense* dn, uint8_t* rec, double* p1,
                          bool timed) -> sv_status {
     auto dense = [&](int ui) { return dn ? dn + inst(ui) : (const BlockDense*)nullptr; };
-    auto decide = [&](int ui) {
+    // pass pidx: unit instance ui applied (-1: the initial state), the next
+    // one summed unless `last`; returns the workgroups that left partial sums
+    auto pass = [&](int pidx, int ui, bool last, int rev, unsigned* parts) -> sv_status {
+      const BlockRT* ra = ui < 0 ? nullptr : rt + inst(ui);
+      const BlockRT* rb = last ? nullptr : rt + inst(ui + 1);
+      const Decision* da = ui < 0 ? nullptr : &ddec[ui];
+      if (flip) {
+        const FlipPass& h = fplan.passes[pidx];
+        const FlipGrid fg = flip_grid(h, flip_wgs);
+        *parts = fg.wgs;
+        return pass_status(launch_flip<T>(h, ui < 0, dim3(fg.wgs), q, st, &dfpass[pidx], ra, rb, da, &ddec[ui + 1],
+                                          partials, rev, (int)fg.n_cls_wg, last && !xbasis ? dsums : nullptr, ss0));
+      }
+      *parts = grid.x;
+      return pass_status(launch_upass<T>(pds[pidx], grid, block, q, st, &dpass[pidx], djc, ra, rb, da, &ddec[ui + 1], partials,
+                             rev, ss0, ui < 0 ? nullptr : dense(ui), last ? nullptr : dense(ui + 1)));
+    };
+    auto decide = [&](int ui, unsigned parts) {
       const int bi = inst(ui);
       const int lb = units[ui % nu].len;
       // one partial per pass workgroup
-      hipLaunchKernelGGL(k_udecide, dim3(unit_sums(lb)), dim3(256), 0, q, partials, (int)grid.x, lb,
+      hipLaunchKernelGGL(k_udecide, dim3(unit_sums(lb)), dim3(256), 0, q, partials, (int)parts, lb,
                          rt + bi, &ddec[ui], rec + bi, p1 ? p1 + bi : nullptr, ss0, (size_t)0, dacc,
                          dticket, 1);
     };
-    SV_OK_OR_RETURN(launch_upass<T>(pds[0], grid, block, q, st, &dpass[0], djc, nullptr, rt + inst(0),
-                                    nullptr, &ddec[0], partials, 0, ss0, nullptr, dense(0)));
-    decide(0);
+    unsigned parts = 0;
+    SV_OK_OR_RETURN(pass(0, -1, false, 0, &parts));
+    decide(0, parts);
     for (int ui = 0; ui < per_units; ++ui) {
       const int u = ui % nu;
       const bool last = (ui == per_units - 1);
       const int pidx = last ? nu + 1 : 1 + u;
       if (timed) HIP_OK(hipEventRecord(evs[2 * ui], q));
-      SV_OK_OR_RETURN(launch_upass<T>(pds[pidx], grid, block, q, st, &dpass[pidx], djc, rt + inst(ui),
-                                      last ? nullptr : rt + inst(ui + 1), &ddec[ui], &ddec[ui + 1],
-                                      partials, snake ? ((ui + 1) & 1) : 0, ss0, dense(ui),
-                                      last ? nullptr : dense(ui + 1)));
+      SV_OK_OR_RETURN(pass(pidx, ui, last, snake ? ((ui + 1) & 1) : 0, &parts));
       if (timed) HIP_OK(hipEventRecord(evs[2 * ui + 1], q));
-      if (!last) decide(ui + 1);
+      if (!last) decide(ui + 1, parts);
     }
     HIP_OK(hipGetLastError());
     return SV_OK;
@@ -1295,8 +1555,8 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                        T** out) -> sv_status {
     T* cur = st;
     T* oth = st2;
-    SV_OK_OR_RETURN(launch_upass<T>(spds[0], grid, block, q, cur, &dspass[0], djc, nullptr, nullptr, nullptr,
-                                    &ddec[0], partials, 0, ss0));
+    SV_OK_OR_RETURN(pass_status(launch_upass<T>(spds[0], grid, block, q, cur, &dspass[0], djc, nullptr, nullptr, nullptr,
+                                    &ddec[0], partials, 0, ss0)));
     for (int ui = 0; ui < per_units_s; ++ui) {
       const int u = ui % nus, r = ui / nus;
       const Unit& U = sunits[u];
@@ -1308,8 +1568,8 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
       const BlockRT* rtb = zb ? rt + bi : nullptr;
       const int rev = snake ? (ui & 1) : 0;
       auto pass = [&](bool redo) {
-        return launch_spass<T>(spds[1 + u], redo, grid, block, q, cur, &dspass[1 + u], djc, rta, rtb, &ddec[ui],
-                               &ddec[ui + 1], partials, rev, sa, ss0);
+        return pass_status(launch_spass<T>(spds[1 + u], redo, grid, block, q, cur, &dspass[1 + u], djc, rta, rtb, &ddec[ui],
+                               &ddec[ui + 1], partials, rev, sa, ss0));
       };
       auto decide = [&]() {
         hipLaunchKernelGGL(k_sdecide, dim3(zb ? unit_sums(U.len) : 2 * U.len), dim3(256), 0, q, partials,
@@ -1337,16 +1597,17 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   // outcome probabilities are ratios: a pending renormalisation is harmless)
   auto traj_final = [&](hipStream_t q, T* buf, uint8_t* bits, uint64_t t, const uint64_t* tptr) {
     if (xbasis) launch_wht_all<T>(q, buf, n);
-    hipLaunchKernelGGL(k_final_sums<T>, dim3(1u << (n - cb)), dim3(256), 0, q, buf, cb, dsums,
-                       (size_t)0);
+    // (the last pass with a basis change has left the sums)
+    if (!flip || xbasis)
+      hipLaunchKernelGGL(k_final_sums<T>, dim3(1u << (n - cb)), dim3(256), 0, q, buf, cb, dsums, (size_t)0);
     hipLaunchKernelGGL(k_final_measure<T>, dim3(1), dim3(1024), 0, q, buf, n, cb, dsums, job->seed, t,
                        (uint64_t)R * (uint64_t)draws_round, bits, (size_t)0, (const uint64_t*)nullptr,
                        tptr, (const int*)nullptr, (uint64_t)0,
-                       xbasis ? (const Decision*)nullptr : (const Decision*)&ddec[fin],
-                       (size_t)0);
+                       xbasis && !flip ? (const Decision*)nullptr : (const Decision*)&ddec[fin],
+                       (size_t)0, xbasis ? 1 : 0);
   };
   double pass_ms_graph = -1.0;
-  std::vector<uint32_t> phi_host(res->final_states ? job->n_traj : 0);
+  std::vector<Decision> fin_host(res->final_states ? job->n_traj : 0);
   if (job->flags & SV_RUN_GRAPH) {
     // one trajectory's sequence, staged through fixed buffers and a device
     // trajectory counter, captured once and replayed n_traj times
@@ -1451,10 +1712,8 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                                buf, na, (const Decision*)&ddec[fin]);
           HIP_OK(hipMemcpyAsync((char*)res->final_states + (size_t)tg * sizeof(T) * 2 * na, buf,
                                 sizeof(T) * 2 * na, hipMemcpyDeviceToHost, s));
-          Decision fd{};
-          HIP_OK(hipMemcpyAsync(&fd, &ddec[fin], sizeof fd, hipMemcpyDeviceToHost, s));
+          HIP_OK(hipMemcpyAsync(&fin_host[tg], &ddec[fin], sizeof(Decision), hipMemcpyDeviceToHost, s));
           HIP_OK(hipStreamSynchronize(s));
-          phi_host[tg] = fd.phi;
         }
         traj_final(s, buf, dbits + (size_t)tg * n, job->traj0 + (uint64_t)tg, nullptr);
         HIP_OK(hipGetLastError());
@@ -1485,12 +1744,16 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   if (res->p1_trace)
     HIP_OK(hipMemcpyAsync(res->p1_trace, dp1, sizeof(double) * nrec, hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
-  // registers handed back in the logical frame: amplitude x sits at x ^ phi
+  // registers handed back in the logical frame: amplitude x sits at x ^ phi,
+  // after a basis-change pass with the sign of neg and of phix & (x ^ phi)
   if (res->final_states)
     for (int t = 0; t < job->n_traj; ++t) {
-      const uint32_t phi = phi_host[t];
-      if (!phi) continue;
+      const uint32_t phi = fin_host[t].phi, phix = fin_host[t].phix;
       C2<T>* a = reinterpret_cast<C2<T>*>((char*)res->final_states + (size_t)t * sizeof(T) * 2 * na);
+      if (phix || fin_host[t].neg)
+        for (uint64_t x = 0; x < na; ++x)
+          if ((__builtin_popcount((uint32_t)x & phix) ^ fin_host[t].neg) & 1) a[x] = C2<T>{-a[x].re, -a[x].im};
+      if (!phi) continue;
       for (uint64_t x = 0; x < na; ++x) {
         const uint64_t y = x ^ phi;
         if (x < y) std::swap(a[x], a[y]);
@@ -1812,12 +2075,15 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
   const sv_tuning tune = tuning_for(d, sizeof(T) == 8 ? SV_C128 : SV_C64);
   const size_t cap = (size_t)tune.lockstep_mib << 20;
   const int per_traj = in.max_rounds * ns;
-  const std::vector<Unit> units = make_units_paired(tp, tune.zchain, n, tune.xpair);
-  const int nu = (int)units.size();
-  // speculative units (as for one register: on when zeta = 0 unless
-  // QECSV_SPEC says otherwise); each slot then holds two registers
   const int spec_env = env_int("QECSV_SPEC", -1);
-  bool spec = (spec_env < 0 ? in.zeta == 0.0 : spec_env != 0) && !tp.any_dense;
+  FlipPlan fplan;
+  if (spec_env < 0 && in.zeta == 0.0 && !tp.any_dense) fplan = make_flip_plan(d, tp, false);
+  const bool flip = !fplan.units.empty();
+  const std::vector<Unit> units = flip ? fplan.units : make_units_paired(tp, tune.zchain, n, tune.xpair);
+  const int nu = (int)units.size();
+  // speculative units (when QECSV_SPEC asks for them); each slot then holds
+  // two registers
+  bool spec = !flip && (spec_env < 0 ? in.zeta == 0.0 : spec_env != 0) && !tp.any_dense;
   std::vector<Unit> sunits;
   std::vector<UnitPass> spds;
   if (spec) {
@@ -1887,7 +2153,12 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
     HIP_OK(hipMemsetAsync(dredos, 0, sizeof(int), s));
   }
 
-  const std::vector<UnitPass> pds = make_unit_passes(n, tb, tp, units);
+  const std::vector<UnitPass> pds = flip ? std::vector<UnitPass>(nu + 2) : make_unit_passes(n, tb, tp, units);
+  FlipPass* dfpass = nullptr;
+  if (flip) {
+    HIP_OK(M.alloc(&dfpass, sizeof(FlipPass) * (nu + 2)));
+    HIP_OK(hipMemcpyAsync(dfpass, fplan.passes.data(), sizeof(FlipPass) * (nu + 2), hipMemcpyHostToDevice, s));
+  }
   const JobConst jc = make_job_const(d, in.zeta);
   HIP_OK(hipMemcpyAsync(dblocks, tp.blocks.data(), sizeof(TBlock) * ns, hipMemcpyHostToDevice, s));
   HIP_OK(hipMemcpyAsync(dpass, pds.data(), sizeof(UnitPass) * (nu + 2), hipMemcpyHostToDevice, s));
@@ -1918,6 +2189,11 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
   HIP_OK(hipStreamCreateWithFlags(&ev.s2, hipStreamNonBlocking));
   const dim3 block((unsigned)std::max(64, 1 << (tb - 4)));
   const SlotStrides ss{reg, (size_t)ns, dec_stride};
+  // passes with a basis change: at least four workgroups per slot of four
+  // tiles each, more when few slots would leave compute units idle (2048
+  // complex64 trajectories: 10.0 / 9.4 / 9.3 / 10.4 / 13.1 ms with 1 / 2 / 4 /
+  // 8 / 16; 300: 2.45 / 2.44 / 2.30 / 2.44 / 2.75)
+  const unsigned flip_wgs = (unsigned)device_cu_count() * (sizeof(T) == 8 ? 2u : 3u);
   // pass workgroups per slot, each taking tiles grid-stride: four tiles each
   // for passes that sum a Z chain or write logical |0> (their tables - up to
   // four chain members' weights, a phase table per layer count - are loaded
@@ -1980,11 +2256,13 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
     // final Z measurement of the slots [from, from + cnt) on register buffer
     // buf, their frames in the decision records at dfin
     auto measure = [&](const T* buf, int from, int cnt, const Decision* dfin) {
-      hipLaunchKernelGGL(k_final_sums<T>, dim3(1u << (n - cb), cnt), dim3(256), 0, s, buf + (size_t)from * reg, cb,
-                         dsums, reg);
+      // (the last pass with a basis change has left the sums)
+      if (!flip)
+        hipLaunchKernelGGL(k_final_sums<T>, dim3(1u << (n - cb), cnt), dim3(256), 0, s, buf + (size_t)from * reg, cb,
+                           dsums, reg);
       hipLaunchKernelGGL(k_final_measure<T>, dim3(cnt), dim3(1024), 0, s, buf + (size_t)from * reg, n, cb, dsums,
                          (uint64_t)0, (uint64_t)0, (uint64_t)0, dbits + (size_t)from * n, reg, dseed + from,
-                         dstream + from, drounds + from, (uint64_t)tp.n_draws, dfin, dec_stride);
+                         dstream + from, drounds + from, (uint64_t)tp.n_draws, dfin, dec_stride, 0);
     };
     if (spec) {
       // speculative units: logical |0> into st, then per unit of every round
@@ -1993,8 +2271,8 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
       T* cur = st;
       T* oth = st2;
       hipLaunchKernelGGL(k_dec_init, dim3((unsigned)((gn + 255) / 256)), dim3(256), 0, s, ddec, gn, dec_stride);
-      SV_OK_OR_RETURN(launch_upass<T>(spds[0], dim3(gx_of(spds[0]), gn), block, s, cur, &dspass[0], djc, nullptr,
-                                      nullptr, nullptr, ddec, partials, 0, ss));
+      SV_OK_OR_RETURN(pass_status(launch_upass<T>(spds[0], dim3(gx_of(spds[0]), gn), block, s, cur, &dspass[0], djc, nullptr,
+                                      nullptr, nullptr, ddec, partials, 0, ss)));
       int ui = 0;
       for (int r = 0; r < R0; ++r) {
         const int Ar = active(r), An = active(r + 1);
@@ -2023,9 +2301,9 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
           // 40.7 with two and 44.9 with one workgroup per slot)
           const unsigned gr = std::max(1u, gx / 4);
           auto pass = [&](bool redo) {
-            return launch_spass<T>(h, redo, dim3(redo ? gr : gx, Ar), block, s, cur, &dspass[1 + u], djc,
+            return pass_status(launch_spass<T>(h, redo, dim3(redo ? gr : gx, Ar), block, s, cur, &dspass[1 + u], djc,
                                    zb ? nullptr : rtu, zb ? rtu : nullptr, ddec + ui, ddec + ui + 1, partials, rev,
-                                   sa, ss);
+                                   sa, ss));
           };
           auto sdecide = [&](unsigned parts) {
             hipLaunchKernelGGL(k_sdecide, dim3(Ar), dim3(64), 0, s, partials, (int)parts, U.len, zb ? 1 : 0, rtu,
@@ -2046,9 +2324,24 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
         HIP_OK(hipGetLastError());
       }
     } else {
-    SV_OK_OR_RETURN(launch_upass<T>(pds[0], dim3(gx_of(pds[0]), gn), block, s, st, &dpass[0], djc,
-                                    nullptr, rtA + units[0].first, nullptr, ddec, partials, 0, ss));
-    decide(gn, rtA, 0, 0, gx_of(pds[0]));
+    // pass pidx over cnt slots from `from` on (register, tables and decisions
+    // of the first of them given); workgroups per slot in *gx
+    auto pass = [&](int pidx, int cnt, T* reg0, const BlockRT* ra, const BlockRT* rb, const Decision* da, Decision* db,
+                    int rev, unsigned* gx) -> sv_status {
+      if (flip) {
+        const FlipPass& h = fplan.passes[pidx];
+        const FlipGrid fg = flip_grid(h, std::max(4u, flip_wgs / (unsigned)cnt));
+        *gx = fg.wgs;
+        return pass_status(launch_flip<T>(h, pidx == 0, dim3(fg.wgs, cnt), s, reg0, &dfpass[pidx], ra, rb, da, db,
+                                          partials, rev, (int)fg.n_cls_wg, rb ? nullptr : dsums, ss));
+      }
+      *gx = gx_of(pds[pidx]);
+      return pass_status(launch_upass<T>(pds[pidx], dim3(*gx, cnt), block, s, reg0, &dpass[pidx], djc, ra, rb, da, db, partials,
+                             rev, ss));
+    };
+    unsigned gx = 0;
+    SV_OK_OR_RETURN(pass(0, gn, st, nullptr, rtA + units[0].first, nullptr, ddec, 0, &gx));
+    decide(gn, rtA, 0, 0, gx);
     for (int r = 0; r < R0; ++r) {
       const int Ar = active(r), An = active(r + 1);
       BlockRT* rt_cur = (r & 1) ? rtB : rtA;
@@ -2067,25 +2360,19 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
         const int rev = (++pass_no) & 1;
         const BlockRT* rta = rt_cur + units[u].first;
         if (u < nu - 1) {
-          SV_OK_OR_RETURN(launch_upass<T>(pds[1 + u], dim3(gx_of(pds[1 + u]), Ar), block, s, st,
-                                          &dpass[1 + u], djc, rta, rt_cur + units[u + 1].first,
-                                          ddec + ui, ddec + ui + 1, partials, rev, ss));
-          decide(Ar, rt_cur, r, u + 1, gx_of(pds[1 + u]));
+          SV_OK_OR_RETURN(pass(1 + u, Ar, st, rta, rt_cur + units[u + 1].first, ddec + ui, ddec + ui + 1, rev, &gx));
+          decide(Ar, rt_cur, r, u + 1, gx);
           continue;
         }
         if (An > 0) {
-          SV_OK_OR_RETURN(launch_upass<T>(pds[1 + u], dim3(gx_of(pds[1 + u]), An), block, s, st,
-                                          &dpass[1 + u], djc, rta, rt_nxt + units[0].first,
-                                          ddec + ui, ddec + ui + 1, partials, rev, ss));
-          decide(An, rt_nxt, r + 1, 0, gx_of(pds[1 + u]));
+          SV_OK_OR_RETURN(pass(1 + u, An, st, rta, rt_nxt + units[0].first, ddec + ui, ddec + ui + 1, rev, &gx));
+          decide(An, rt_nxt, r + 1, 0, gx);
         }
         if (Ar > An) {  // trajectories ending with this round
           const int cnt = Ar - An;
           Decision* dfin = ddec + (size_t)An * dec_stride + ui + 1;
-          SV_OK_OR_RETURN(launch_upass<T>(pds[nu + 1], dim3(gx_of(pds[nu + 1]), cnt), block, s,
-                                          st + (size_t)An * reg, &dpass[nu + 1], djc,
-                                          rta + (size_t)An * ns, nullptr,
-                                          ddec + (size_t)An * dec_stride + ui, dfin, partials, rev, ss));
+          SV_OK_OR_RETURN(pass(nu + 1, cnt, st + (size_t)An * reg, rta + (size_t)An * ns, nullptr,
+                               ddec + (size_t)An * dec_stride + ui, dfin, rev, &gx));
           measure(st, An, cnt, dfin);
         }
       }
@@ -2606,6 +2893,117 @@ sv_status sv_check_spec_layouts(int d, int gateset, int zchain, int* n_units) {
       return fail(SV_EINVAL, "speculative unit %zu: stored from a layout without the lowest bits on its lanes", u);
   }
   *n_units = (int)units.size();
+  return SV_OK;
+}
+
+sv_status sv_check_flip_layouts(int d, int gateset, int* n_passes) {
+  if (d < 2 || d > 5) return fail(SV_EINVAL, "d=%d out of 2..5", d);
+  if (gateset != SV_GATESET_CR && gateset != SV_GATESET_TEXTBOOK) return fail(SV_EINVAL, "bad gate set %d", gateset);
+  const Template tp = build_template(d, gateset);
+  const int n = d * d, ns = (int)tp.blocks.size();
+  const FlipPlan P = make_flip_plan(d, tp, false);
+  const int nu = (int)P.units.size();
+  if (n_passes) *n_passes = nu;
+  if (nu == 0) return SV_OK;
+  // chains: every check once, in order, all its qubits in its basis
+  uint32_t xb = 0;
+  int c = 0;
+  for (int u = 0; u < nu; ++u) {
+    xb ^= P.flips[u];
+    if (P.units[u].first != c || P.units[u].len < 1 || P.units[u].len > kChainMax)
+      return fail(SV_EINVAL, "chain %d: not the next checks", u);
+    for (int i = 0; i < P.units[u].len; ++i, ++c) {
+      const uint32_t q = check_mask(tp.blocks[c]);
+      if ((tp.blocks[c].type == 0 ? q & ~xb : q & xb) != 0) return fail(SV_EINVAL, "check %d: wrong basis", c);
+    }
+  }
+  if (c != ns || xb != 0) return fail(SV_EINVAL, "the round does not end in the computational basis");
+  for (int p = 0; p < nu + 2; ++p) {
+    const FlipPass& h = P.passes[p];
+    const uint32_t F = p == 0 || p == nu + 1 ? 0u : P.flips[p % nu];
+    uint32_t outer = 0;
+    for (int i = 0; i < h.n_outer; ++i) outer |= h.outer_bit[i];
+    const uint32_t tile = ((1u << n) - 1) & ~outer;
+    if (__builtin_popcount(tile) != kTileMax || __builtin_popcount(outer) != h.n_outer)
+      return fail(SV_EINVAL, "pass %d: tile of %d bits", p, __builtin_popcount(tile));
+    // both layouts reach every amplitude of the tile and no two places of the
+    // buffer coincide; the regroup brings each amplitude from its layout-1
+    // place (after the exchange of lane bit 5 with slot bit 3) to its layout-2
+    // place
+    const uint32_t t1[8] = {1u, 2u, 4u, h.s2[0], h.s2[1], h.e, h.s2[2], h.s2[3]};
+    const uint32_t t2[8] = {1u, 2u, 4u, h.s0[0], h.s0[1], h.s0[2], h.s0[3], h.e};
+    const int L = FlipLds::e, *S0 = FlipLds::s0, *S2 = FlipLds::s2;
+    const int lw[8] = {1, 2, 4, S2[0], S2[1], h.lane5 ? S0[3] : L, S2[2], S2[3]};
+    const int lr[8] = {1, 2, 4, S0[0], S0[1], S0[2], S0[3], L};
+    std::vector<int64_t> at(FlipLds::kSize, -1);
+    std::vector<uint32_t> got;
+    for (int t = 0; t < 256; ++t)
+      for (int j = 0; j < 16; ++j) {
+        // the value that thread t holds in slot j when it writes the buffer
+        int ts = t, js = j;
+        if (h.lane5) {
+          ts = (t & ~32) | (((j >> 3) & 1) << 5);
+          js = (j & 7) | (((t >> 5) & 1) << 3);
+        }
+        uint32_t g = 0;
+        int l = h.lane5 ? FlipLds::w<true>(j) : FlipLds::w<false>(j);
+        for (int b = 0; b < 4; ++b)
+          if ((js >> b) & 1) g |= h.s0[b];
+        for (int i = 0; i < 8; ++i) {
+          if ((ts >> i) & 1) g |= t1[i];
+          if ((t >> i) & 1) l += lw[i];
+        }
+        if ((g & ~tile) || l >= FlipLds::kSize || at[l] >= 0)
+          return fail(SV_EINVAL, "pass %d: layout 1 does not cover its tile", p);
+        at[l] = g;
+        got.push_back(g);
+      }
+    std::sort(got.begin(), got.end());
+    if (std::unique(got.begin(), got.end()) != got.end()) return fail(SV_EINVAL, "pass %d: layout 1 repeats", p);
+    for (int t = 0; t < 256; ++t)
+      for (int j = 0; j < 16; ++j) {
+        uint32_t g = 0;
+        int l = FlipLds::r(j);
+        for (int b = 0; b < 4; ++b)
+          if ((j >> b) & 1) g |= h.s2[b];
+        for (int i = 0; i < 8; ++i)
+          if ((t >> i) & 1) {
+            g |= t2[i];
+            l += lr[i];
+          }
+        if (l >= FlipLds::kSize || at[l] != (int64_t)g) return fail(SV_EINVAL, "pass %d: regroup of amplitude %u", p, g);
+      }
+    // the store's slot pairs belong to one member of B each
+    const uint32_t* so = h.two ? h.s2 : h.s0;
+    for (int b = 0; b < 4 && h.lb > 0; ++b) {
+      const int own = b < 2 ? h.ord[h.lb > 1 ? h.lb - 2 : 0] : (h.lb > 1 ? h.ord[h.lb - 1] : -1);
+      for (int i = 0; i < h.lb; ++i)
+        for (int l = 0; l < h.bw[i]; ++l)
+          if (h.bq[i][l] == so[b] && i != own) return fail(SV_EINVAL, "pass %d: slot bit %d of check %d", p, b, i);
+    }
+    if (!h.lb && (tile != (1u << kTileMax) - 1 || !h.two || !h.plain))
+      return fail(SV_EINVAL, "pass %d: the last pass's tiles are not the lowest bits", p);
+    // places: one amplitude each, a tile's places within the tile's block
+    if (p == 0)
+      for (uint32_t g = 0; g < (1u << n); ++g) {
+        if ((flip_place<double>(g) ^ g) >> kTileMax || (flip_place<float>(g) ^ g) >> kTileMax)
+          return fail(SV_EINVAL, "amplitude %u leaves its block", g);
+      }
+    if (!h.two && (h.m2 || h.lane5)) return fail(SV_EINVAL, "pass %d: flips beyond the only layout", p);
+    uint32_t flipped = (uint32_t)h.low;
+    for (int b = 0; b < 4; ++b) {
+      if ((h.m0 >> b) & 1) flipped |= h.s0[b];
+      if ((h.m2 >> b) & 1) flipped |= h.s2[b];
+    }
+    if (h.lane5) flipped |= h.e;
+    if (flipped != F) return fail(SV_EINVAL, "pass %d: flips %x instead of %x", p, flipped, F);
+    uint32_t brel = 0;
+    for (int i = 0; i < h.lb; ++i)
+      for (int l = 0; l < h.bw[i]; ++l) brel |= h.bq[i][l];
+    for (int i = 0; i < h.n_outer; ++i)
+      if (((h.outer_bit[i] & brel) != 0) != (i < h.n_brel))
+        return fail(SV_EINVAL, "pass %d: the summed qubits do not lead the outer bits", p);
+  }
   return SV_OK;
 }
 
