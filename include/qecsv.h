@@ -259,8 +259,11 @@ typedef struct sv_result {
   double gpu_ms;        /* out: device time of the whole run (hipEvents) */
   double pass_ms;       /* out: mean device time per register pass of the last
                            trajectory (one pass applies an X check, a pair of
-                           them or a chain of Z checks; with speculative
-                           units, their prediction passes) */
+                           them or a chain of checks; with speculative units,
+                           their prediction passes); d <= 4, whose
+                           trajectories run side by side: per pass and
+                           trajectory of the last group, its decisions
+                           included */
   int passes_per_round; /* out: register passes per round (speculative units:
                            prediction passes per round) */
   int redo_passes;      /* out: speculative units' redo passes that ran, over

@@ -212,37 +212,72 @@ __device__ __forceinline__ double clamp_p1(double p1) {
 // ---------------------------------------------------------------- prepare --
 // Draws and Kraus pairs of every block instance of n_traj trajectories
 // (draw streams traj0 + i, or *stream for a single trajectory when given);
-// twirl_thr: per-site sin^2 eps of the Pauli-twirled model, or null.
-static __global__ void k_prepare(const TBlock* __restrict__ blocks, int n_stab, int rounds,
-                          int draws_per_round, uint64_t seed, uint64_t traj0, int n_traj,
-                          double p, const double* __restrict__ eps_site,
-                          BlockRT* __restrict__ out, int* __restrict__ err,
-                          const uint64_t* __restrict__ stream,
-                          const double* __restrict__ twirl_thr) {
+// cs: cos and sin of every gate site's angle; twirl_thr: per-site sin^2 eps of
+// the Pauli-twirled model, or null.  16 lanes per block instance: lane x
+// evaluates draws x, x + 16, ... (shared by shuffles) and then the circuit's
+// column x.  (One thread per instance, evaluating its angles' cos and sin for
+// all 16 columns, took 260 us however few the instances.)
+static __global__ __launch_bounds__(128) void k_prepare(
+    const TBlock* __restrict__ blocks, int n_stab, int rounds, int draws_per_round, uint64_t seed, uint64_t traj0,
+    int n_traj, double p, const double* __restrict__ cs, BlockRT* __restrict__ out, int* __restrict__ err,
+    const uint64_t* __restrict__ stream, const double* __restrict__ twirl_thr) {
   const int per_traj = rounds * n_stab;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (int64_t)per_traj * n_traj) return;
-  const int ti = (int)(gid / per_traj);
-  const int bi = (int)(gid % per_traj);
-  const int r = bi / n_stab, s = bi % n_stab;
-  const TBlock& b = blocks[s];
-  uint8_t pauli[kMaxOps];
-  BlockRT rt;
-  const uint64_t k0 = (uint64_t)r * (uint64_t)draws_per_round + (uint64_t)b.draw_off;
+  const int64_t inst = gid >> 4;
+  const int x = (int)(gid & 15);
+  const bool valid = inst < (int64_t)per_traj * n_traj;
+  const int ti = valid ? (int)(inst / per_traj) : 0;
+  const int bi = valid ? (int)(inst % per_traj) : 0;
+  const TBlock& b = blocks[bi % n_stab];
+  const uint64_t k0 = (uint64_t)(bi / n_stab) * (uint64_t)draws_per_round + (uint64_t)b.draw_off;
   const uint64_t t = stream ? *stream : traj0 + (uint64_t)ti;
-  draw_block(b, seed, t, k0, p, pauli, &rt.u, twirl_thr);
-  if (b.dense) {  // the Kraus pair comes from k_prepare_dense
-    for (int m = 0; m < 2; ++m)
-      for (int x = 0; x < 16; ++x) {
-        rt.D[m][x][0] = rt.D[m][x][1] = 0.0;
-        rt.W[m][x] = 0.0;
-      }
-    rt.F = 0;
-  } else if (!build_block(b, eps_site, pauli, rt)) {
-    atomicOr(err, 1);
+  double u[kMaxOps / 16];  // a block has fewer draws than kMaxOps
+#pragma unroll
+  for (int c = 0; c < kMaxOps / 16; ++c)
+    u[c] = valid && x + 16 * c < b.n_draws ? uniform(seed, t, k0 + (uint64_t)(x + 16 * c)) : 1.0;
+  auto draw = [&](int k) {  // by every lane of the group
+    double v = __shfl(u[0], k & 15, 16);
+#pragma unroll
+    for (int c = 1; c < kMaxOps / 16; ++c) {
+      const double w = __shfl(u[c], k & 15, 16);
+      if ((k >> 4) == c) v = w;
+    }
+    return v;
+  };
+  // every lane runs every shuffle (the op count differs between groups)
+  uint8_t pauli[kMaxOps];
+  int n_ops = b.n_ops;
+  for (int off = 32; off >= 16; off >>= 1) n_ops = max(n_ops, __shfl_xor(n_ops, off, 64));
+  for (int i = 0; i < n_ops; ++i) {
+    const bool drawn = i < b.n_ops && b.ops[i].draw >= 0;
+    const double ui = draw(drawn ? b.ops[i].draw : 0);
+    pauli[i] = 0;
+    if (!drawn) continue;
+    const TOp& op = b.ops[i];
+    if (is_rotation(op.kind)) pauli[i] = (uint8_t)(twirl_thr && ui < twirl_thr[op.site] ? 1 : 0);
+    else if (op.kind == OP_N1_ANC || op.kind == OP_N1_DATA) pauli[i] = (uint8_t)pick_pauli1(ui, p);
+    else pauli[i] = (uint8_t)pick_pauli2(ui, p);
   }
-  rt.pad = 0;
-  out[gid] = rt;
+  const double um = draw(b.n_draws - 1);
+  if (!valid) return;
+  BlockRT& o = out[inst];
+  const int nx = 1 << b.w;
+  const double norm = b.type == 0 ? 1.0 / (double)nx : 1.0;
+  cd v0{0.0, 0.0}, v1{0.0, 0.0};
+  uint32_t cur = 0;
+  // (a dense block's Kraus pair comes from k_prepare_dense)
+  if (x < nx && !b.dense && !track_column(b, CsFromTable{cs}, pauli, x, v0, v1, &cur)) atomicOr(err, 1);
+  o.D[0][x][0] = v0.re * norm;
+  o.D[0][x][1] = v0.im * norm;
+  o.D[1][x][0] = v1.re * norm;
+  o.D[1][x][1] = v1.im * norm;
+  o.W[0][x] = (v0.re * v0.re + v0.im * v0.im) * norm;
+  o.W[1][x] = (v1.re * v1.re + v1.im * v1.im) * norm;
+  if (x == 0) {
+    o.F = cur;
+    o.u = um;
+    o.pad = 0;
+  }
 }
 
 // Dense Kraus pairs of the blocks that are not monomial in their basis: one
@@ -251,7 +286,7 @@ static __global__ void k_prepare(const TBlock* __restrict__ blocks, int n_stab, 
 // and K_1 (the same draws as k_prepare).
 static __global__ __launch_bounds__(128) void k_prepare_dense(
     const TBlock* __restrict__ blocks, int n_stab, int rounds, int draws_per_round, uint64_t seed,
-    uint64_t traj0, int n_traj, double p, const double* __restrict__ eps_site,
+    uint64_t traj0, int n_traj, double p, const double* __restrict__ cs,
     BlockDense* __restrict__ out, int* __restrict__ err, const uint64_t* __restrict__ stream,
     const double* __restrict__ twirl_thr) {
   const int per_traj = rounds * n_stab;
@@ -276,7 +311,7 @@ static __global__ __launch_bounds__(128) void k_prepare_dense(
   const uint64_t t = stream ? *stream : traj0 + (uint64_t)ti;
   draw_block(b, seed, t, k0, p, pauli, &u, twirl_thr);
   cd psi[32];
-  if (!dense_column(b, CsFromEps{eps_site}, pauli, x, psi)) atomicOr(err, 1);
+  if (!dense_column(b, CsFromTable{cs}, pauli, x, psi)) atomicOr(err, 1);
   for (int m = 0; m < 2; ++m)
     for (int i = 0; i < 16; ++i) {
       const cd v = i < (1 << b.w) ? psi[(m << 4) | i] : cd{0.0, 0.0};
@@ -1769,12 +1804,33 @@ __device__ __forceinline__ void chain_tree_lds(int lb, V v, double* full) {
   __syncthreads();
 }
 
+// Sum of n values v(0..n-1): up to 16 are added in the order of a wave's
+// butterflies (as block_sum2 adds them over the lanes), so that both grid
+// modes of the decisions give the same bits for the few partials of a small
+// register; more, one after another.
+template <typename V>
+__device__ __forceinline__ double sum_in_order(int n, V v) {
+  double s = 0.0;
+  if (n <= 16) {
+    double t[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t[i] = i < n ? v(i) : 0.0;
+#pragma unroll
+    for (int h = 8; h >= 1; h >>= 1)
+#pragma unroll
+      for (int i = 0; i < h; ++i) t[i] += t[i + h];
+    return t[0];
+  }
+  for (int i = 0; i < n; ++i) s += v(i);
+  return s;
+}
+
 // Outcomes of unit B (a chain of lb checks; lb = 1 for an X check), reducing
 // each sum over the n per-workgroup partials in a fixed order.
 // split = 1, grid (nacc, slots): workgroup a reduces sum a; the last
 // workgroup of a slot to finish (ticket counter, reset for the next use)
 // decides.  split = 0, grid (slots): one workgroup per slot, thread a sums
-// sum a serially (few partials: many small registers side by side).
+// sum a (few partials: many small registers side by side).
 static __global__ __launch_bounds__(256) void k_udecide(const double* __restrict__ partials, int n,
                                                  int lb, const BlockRT* __restrict__ rtb,
                                                  Decision* __restrict__ dec_b,
@@ -1792,9 +1848,7 @@ static __global__ __launch_bounds__(256) void k_udecide(const double* __restrict
   __shared__ double full[kChainAcc];
   if (!split) {
     chain_tree_lds(lb, [&](int a) {
-      double s = 0.0;
-      for (int i = 0; i < n; ++i) s += partials[(size_t)a * n + i];
-      return s;
+      return sum_in_order(n, [&](int i) { return partials[(size_t)a * n + i]; });
     }, full);
     if (threadIdx.x == 0) decide_chain(full, lb, rtb, dec_b, rec_b, p1_b);
     return;
@@ -1913,12 +1967,9 @@ static __global__ __launch_bounds__(256) void k_sdecide(const double* __restrict
     if (threadIdx.x == 0) *ticket = 0u;
   } else {
     // one workgroup per slot (lockstep: few partials per sum): thread a
-    // sums sum a serially, in the order of the partials
-    for (int a = threadIdx.x; a < nacc; a += blockDim.x) {
-      double s = 0.0;
-      for (int i = 0; i < n; ++i) s += partials[(size_t)a * n + i];
-      col[a] = s;
-    }
+    // sums sum a
+    for (int a = threadIdx.x; a < nacc; a += blockDim.x)
+      col[a] = sum_in_order(n, [&](int i) { return partials[(size_t)a * n + i]; });
     __syncthreads();
   }
   if (tree) {
@@ -1969,10 +2020,13 @@ static __global__ void k_dec_init(Decision* __restrict__ d, int n, size_t stride
   if (i < n) d[(size_t)i * stride] = Decision{1.0, 0, 0u};
 }
 
-// The pending renormalisation 1 / sqrt(d->Sm) applied to a whole register.
+// The pending renormalisation 1 / sqrt(d->Sm) applied to a whole register
+// (blockIdx.y: trajectory slot, its decision at dec_stride).
 template <typename T>
-__global__ __launch_bounds__(256) void k_renorm(T* __restrict__ st, uint64_t na, const Decision* __restrict__ d) {
-  const double sc = 1.0 / sqrt(d->Sm);
+__global__ __launch_bounds__(256) void k_renorm(T* __restrict__ st, uint64_t na, const Decision* __restrict__ d,
+                                                size_t dec_stride) {
+  st += (size_t)blockIdx.y * 2 * na;
+  const double sc = 1.0 / sqrt(d[(size_t)blockIdx.y * dec_stride].Sm);
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < na; i += (uint64_t)gridDim.x * blockDim.x) {
     C2<T> a = ld2(st, i);
     a.re = (T)((double)a.re * sc);

@@ -796,14 +796,14 @@ UnitPass make_unit_pass(int n, int tb_max, const Template& tp, const Unit* A, co
 }
 
 
-// H on every one of the n register qubits, in groups of up to five, scaled
-// by 2^(-n/2) in the last group.
+// H on every one of the n qubits of each of `slots` registers, in groups of up
+// to five, scaled by 2^(-n/2) in the last group.
 template <typename T>
-void launch_wht_all(hipStream_t s, T* st, int n) {
+void launch_wht_all(hipStream_t s, T* st, int n, int slots) {
   for (int q0 = 0; q0 < n; q0 += 5) {
     const int K = std::min(5, n - q0);
     const double scale = (q0 + K == n) ? std::pow(2.0, -0.5 * n) : 1.0;
-    const uint64_t groups = 1ull << (n - K);
+    const uint64_t groups = (uint64_t)slots << (n - K);  // registers side by side: the slot is the index's high part
     const dim3 grid((unsigned)((groups + 255) / 256)), block(256);
     const int q[5] = {q0, q0 + 1, q0 + 2, q0 + 3, q0 + 4};
 #define QEC_WHT(KK)                                                                              \
@@ -1273,7 +1273,7 @@ struct RunStage {
   std::vector<TBlock> blocks;
   std::vector<UnitPass> pds;
   JobConst jc;
-  std::vector<double> eps, thr;
+  std::vector<double> cs, thr;  // cos and sin of every site's angle; twirl thresholds
   std::vector<UnitPass> spds;   // speculative passes
   std::vector<uint8_t> pred0;   // first-round predictions
   std::vector<FlipPass> fpds;   // passes with a basis change
@@ -1354,7 +1354,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   TBlock* dblocks = nullptr;
   UnitPass* dpass = nullptr;
   JobConst* djc = nullptr;
-  double* deps = nullptr;
+  double* dcs = nullptr;
   Decision* ddec = nullptr;
   uint8_t* drec = nullptr;
   uint8_t* dbits = nullptr;
@@ -1370,10 +1370,19 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   const size_t dn_per_traj = tp.any_dense ? sizeof(BlockDense) * (size_t)per_traj : 0;
   const int chunk = (int)std::max<size_t>(
       1, std::min<size_t>((size_t)job->n_traj, ((size_t)64 << 20) / (rt_per_traj + dn_per_traj)));
+  // small registers (d <= 4) run side by side, the trajectory being a grid
+  // dimension: a pass over one of them leaves the chip idle and costs its
+  // launch (500 d = 3 trajectories of five rounds one after another: 185 ms,
+  // 53 000 launches).  At most 256 MiB of registers at a time.
+  const bool small = n <= 16;
+  const size_t reg_bytes = sizeof(T) * 2 * na * (spec ? 2 : 1);
+  int slots = 1;
+  if (small && !(job->flags & SV_RUN_GRAPH))
+    slots = (int)std::max<size_t>(1, std::min<size_t>({(size_t)chunk, ((size_t)256 << 20) / reg_bytes, (size_t)32768}));
   const int n_angles = std::max(1, tp.zz_site >= 0 ? tp.zz_site + 1 : tp.n_sites);
   const size_t nrec = (size_t)job->n_traj * per_traj;
-  HIP_OK(M.alloc(&st, sizeof(T) * 2 * na));
-  HIP_OK(M.alloc(&partials, sizeof(double) * kChainAcc * n_tiles));
+  HIP_OK(M.alloc(&st, sizeof(T) * 2 * na * slots));
+  HIP_OK(M.alloc(&partials, sizeof(double) * kChainAcc * n_tiles * slots));
   double* dacc = nullptr;
   unsigned* dticket = nullptr;
   HIP_OK(M.alloc(&dacc, sizeof(double) * kChainAcc));
@@ -1382,13 +1391,13 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   HIP_OK(M.alloc(&dblocks, sizeof(TBlock) * ns));
   HIP_OK(M.alloc(&dpass, sizeof(UnitPass) * (nu + 2)));
   HIP_OK(M.alloc(&djc, sizeof(JobConst)));
-  HIP_OK(M.alloc(&deps, sizeof(double) * n_angles));
-  const int n_dec = std::max(per_units, per_units_s) + 1;
-  HIP_OK(M.alloc(&ddec, sizeof(Decision) * n_dec));
+  HIP_OK(M.alloc(&dcs, sizeof(double) * 2 * n_angles));
+  const int n_dec = (spec ? per_units_s : per_units) + 1;  // a trajectory's decisions
+  HIP_OK(M.alloc(&ddec, sizeof(Decision) * n_dec * slots));
   HIP_OK(M.alloc(&drec, nrec));
   HIP_OK(M.alloc(&dbits, (size_t)job->n_traj * n));
   if (res->p1_trace) HIP_OK(M.alloc(&dp1, sizeof(double) * nrec));
-  HIP_OK(M.alloc(&dsums, sizeof(double) << (n - cb)));
+  HIP_OK(M.alloc(&dsums, (sizeof(double) << (n - cb)) * slots));
   HIP_OK(M.alloc(&derr, sizeof(int)));
   HIP_OK(M.alloc(&drt, rt_per_traj * chunk));
   BlockDense* ddn = nullptr;  // dense Kraus pairs (blocks with crosstalk inside)
@@ -1408,9 +1417,9 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   if (spec) {
     for (const TBlock& b : tp.blocks)
       pred0.push_back(job->gateset == SV_GATESET_CR ? (uint8_t)((b.w / 2) % 2) : (uint8_t)0);
-    HIP_OK(M.alloc(&st2, sizeof(T) * 2 * na));
+    HIP_OK(M.alloc(&st2, sizeof(T) * 2 * na * slots));
     HIP_OK(M.alloc(&dspass, sizeof(UnitPass) * spds.size()));
-    HIP_OK(M.alloc(&dctl, sizeof(SpecCtl) * per_units_s));
+    HIP_OK(M.alloc(&dctl, sizeof(SpecCtl) * per_units_s * slots));
     HIP_OK(M.alloc(&dpred0, pred0.size()));
     HIP_OK(M.alloc(&dredos, sizeof(int)));
     HIP_OK(hipMemsetAsync(dredos, 0, sizeof(int), s));
@@ -1433,10 +1442,18 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     }
     HIP_OK(M.alloc(&dthr, sizeof(double) * thr.size()));
   }
+  std::vector<double> cs(2 * (size_t)n_angles, 0.0);
+  for (const TBlock& b : tp.blocks)
+    for (int i = 0; i < b.n_ops; ++i)
+      if (b.ops[i].site >= 0) {
+        const double beta = op_angle(b.ops[i], eps.data());
+        cs[2 * b.ops[i].site] = std::cos(beta);
+        cs[2 * b.ops[i].site + 1] = std::sin(beta);
+      }
   {
     // set-up copies from a staging block that a host function on the stream
     // deletes once the stream has passed them (the call may return first)
-    RunStage* stage = new RunStage{tp.blocks, pds, make_job_const(d, job->zeta, xbasis), eps, thr, spds, pred0,
+    RunStage* stage = new RunStage{tp.blocks, pds, make_job_const(d, job->zeta, xbasis), cs, thr, spds, pred0,
                                    fplan.passes};
     const hipError_t e = [&]() -> hipError_t {
       hipError_t r;
@@ -1446,8 +1463,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                               s)))
         return r;
       if ((r = hipMemcpyAsync(djc, &stage->jc, sizeof(JobConst), hipMemcpyHostToDevice, s))) return r;
-      if ((r = hipMemcpyAsync(deps, stage->eps.data(), sizeof(double) * stage->eps.size(),
-                              hipMemcpyHostToDevice, s)))
+      if ((r = hipMemcpyAsync(dcs, stage->cs.data(), sizeof(double) * stage->cs.size(), hipMemcpyHostToDevice, s)))
         return r;
       if (dthr && (r = hipMemcpyAsync(dthr, stage->thr.data(), sizeof(double) * stage->thr.size(),
                                       hipMemcpyHostToDevice, s)))
@@ -1469,20 +1485,20 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     }
   }
   HIP_OK(hipMemsetAsync(derr, 0, sizeof(int), s));
-  HIP_OK(hipMemsetAsync(ddec, 0, sizeof(Decision) * n_dec, s));
-  if (spec) {  // the register logical |0> is written in: norm 1, frame 0
-    static const Decision d0{1.0, 0, 0u};
-    HIP_OK(hipMemcpyAsync(ddec, &d0, sizeof d0, hipMemcpyHostToDevice, s));
-  }
+  HIP_OK(hipMemsetAsync(ddec, 0, sizeof(Decision) * n_dec * slots, s));
+  if (spec)  // the registers logical |0> is written in: norm 1, frame 0
+    hipLaunchKernelGGL(k_dec_init, dim3((unsigned)((slots + 255) / 256)), dim3(256), 0, s, ddec, slots, (size_t)n_dec);
 
   // whole-run events plus one pair around every pass of the last trajectory
+  // (small registers: one pair around the last group's passes and decisions,
+  // an event between launches of a few microseconds would cost as much)
   struct Events {
     std::vector<hipEvent_t> ev;
     ~Events() {
       for (hipEvent_t e : ev) (void)hipEventDestroy(e);
     }
   } E;
-  E.ev.resize(async ? 0 : 2 + 2 * std::max(per_units, per_units_s), nullptr);
+  E.ev.resize(async ? 0 : 2 + (small ? 2 : 2 * std::max(per_units, per_units_s)), nullptr);
   for (auto& e : E.ev) HIP_OK(hipEventCreate(&e));
   hipEvent_t ev0 = async ? nullptr : E.ev[0], ev1 = async ? nullptr : E.ev[1];
   hipEvent_t* evs = async ? nullptr : E.ev.data() + 2;
@@ -1498,13 +1514,15 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   // passes with a basis change: as many workgroups as run at once (two per CU
   // in complex128, three in complex64; see FlipShape)
   const unsigned flip_wgs = (unsigned)device_cu_count() * (sizeof(T) == 8 ? 2u : 3u);
-  const SlotStrides ss0{0, 0, 0};
+  const SlotStrides ss0{(size_t)2 * na, (size_t)per_traj, (size_t)n_dec};
   const int draws_round = tp.n_draws;
   const int last_t = job->n_traj - 1;
+  const bool time_passes = !async && !small;
   // block instance of the first member of unit instance ui
   auto inst = [&](int ui) { return (ui / nu) * ns + units[ui % nu].first; };
-  // passes and decisions of one trajectory whose block tables are at rt
-  auto traj_passes = [&](hipStream_t q, const BlockRT* rt, const BlockDense* dn, uint8_t* rec, double* p1,
+  // passes and decisions of cnt trajectories side by side, the block tables of
+  // the first at rt
+  auto traj_passes = [&](hipStream_t q, int cnt, const BlockRT* rt, const BlockDense* dn, uint8_t* rec, double* p1,
                          bool timed) -> sv_status {
     auto dense = [&](int ui) { return dn ? dn + inst(ui) : (const BlockDense*)nullptr; };
     // pass pidx: unit instance ui applied (-1: the initial state), the next
@@ -1521,16 +1539,17 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                                           partials, rev, (int)fg.n_cls_wg, last && !xbasis ? dsums : nullptr, ss0));
       }
       *parts = grid.x;
-      return pass_status(launch_upass<T>(pds[pidx], grid, block, q, st, &dpass[pidx], djc, ra, rb, da, &ddec[ui + 1], partials,
-                             rev, ss0, ui < 0 ? nullptr : dense(ui), last ? nullptr : dense(ui + 1)));
+      return pass_status(launch_upass<T>(pds[pidx], dim3(grid.x, cnt), block, q, st, &dpass[pidx], djc, ra, rb, da,
+                                         &ddec[ui + 1], partials, rev, ss0, ui < 0 ? nullptr : dense(ui),
+                                         last ? nullptr : dense(ui + 1)));
     };
     auto decide = [&](int ui, unsigned parts) {
       const int bi = inst(ui);
       const int lb = units[ui % nu].len;
       // one partial per pass workgroup
-      hipLaunchKernelGGL(k_udecide, dim3(unit_sums(lb)), dim3(256), 0, q, partials, (int)parts, lb,
-                         rt + bi, &ddec[ui], rec + bi, p1 ? p1 + bi : nullptr, ss0, (size_t)0, dacc,
-                         dticket, 1);
+      hipLaunchKernelGGL(k_udecide, small ? dim3(cnt) : dim3(unit_sums(lb)), dim3(small ? 64 : 256), 0, q, partials,
+                         (int)parts, lb, rt + bi, &ddec[ui], rec + bi, p1 ? p1 + bi : nullptr, ss0, (size_t)per_traj,
+                         dacc, dticket, small ? 0 : 1);
     };
     unsigned parts = 0;
     SV_OK_OR_RETURN(pass(0, -1, false, 0, &parts));
@@ -1551,30 +1570,31 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   // instance its prediction pass (st <-> st2 alternate), the decision and the
   // redos it may need (an X pair two, with a decision between them; a single
   // check or a chain one).  Returns the register that holds the result.
-  auto traj_spec = [&](hipStream_t q, const BlockRT* rt, uint8_t* rec, double* p1, bool timed,
+  auto traj_spec = [&](hipStream_t q, int cnt, const BlockRT* rt, uint8_t* rec, double* p1, bool timed,
                        T** out) -> sv_status {
     T* cur = st;
     T* oth = st2;
-    SV_OK_OR_RETURN(pass_status(launch_upass<T>(spds[0], grid, block, q, cur, &dspass[0], djc, nullptr, nullptr, nullptr,
-                                    &ddec[0], partials, 0, ss0)));
+    SV_OK_OR_RETURN(pass_status(launch_upass<T>(spds[0], dim3(grid.x, cnt), block, q, cur, &dspass[0], djc, nullptr,
+                                                nullptr, nullptr, &ddec[0], partials, 0, ss0)));
     for (int ui = 0; ui < per_units_s; ++ui) {
       const int u = ui % nus, r = ui / nus;
       const Unit& U = sunits[u];
       const bool zb = U.kind == U_Z;
       const size_t bi = (size_t)r * ns + U.first;
       const uint8_t* pred = r == 0 ? dpred0 + U.first : rec + bi - ns;
-      const SpecArgs sa{oth, &dctl[ui], pred, dredos, 0, 0};
+      const SpecArgs sa{oth, &dctl[ui], pred, dredos, (size_t)per_units_s, r == 0 ? (size_t)0 : (size_t)per_traj};
       const BlockRT* rta = zb ? nullptr : rt + bi;
       const BlockRT* rtb = zb ? rt + bi : nullptr;
       const int rev = snake ? (ui & 1) : 0;
       auto pass = [&](bool redo) {
-        return pass_status(launch_spass<T>(spds[1 + u], redo, grid, block, q, cur, &dspass[1 + u], djc, rta, rtb, &ddec[ui],
+        return pass_status(launch_spass<T>(spds[1 + u], redo, dim3(grid.x, cnt), block, q, cur, &dspass[1 + u], djc, rta, rtb, &ddec[ui],
                                &ddec[ui + 1], partials, rev, sa, ss0));
       };
       auto decide = [&]() {
-        hipLaunchKernelGGL(k_sdecide, dim3(zb ? unit_sums(U.len) : 2 * U.len), dim3(256), 0, q, partials,
-                           (int)grid.x, U.len, zb ? 1 : 0, rt + bi, &ddec[ui], &ddec[ui + 1], rec + bi,
-                           p1 ? p1 + bi : nullptr, &dctl[ui], dacc, dticket, ss0, (size_t)0, (size_t)0, 1);
+        hipLaunchKernelGGL(k_sdecide, small ? dim3(cnt) : dim3(zb ? unit_sums(U.len) : 2 * U.len),
+                           dim3(small ? 64 : 256), 0, q, partials, (int)grid.x, U.len, zb ? 1 : 0, rt + bi, &ddec[ui],
+                           &ddec[ui + 1], rec + bi, p1 ? p1 + bi : nullptr, &dctl[ui], dacc, dticket, ss0,
+                           (size_t)per_traj, (size_t)per_units_s, small ? 0 : 1);
       };
       if (timed) HIP_OK(hipEventRecord(evs[2 * ui], q));
       SV_OK_OR_RETURN(pass(false));
@@ -1591,22 +1611,23 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     *out = cur;
     return SV_OK;
   };
-  // final Z measurement of the data register buf (draw stream t, or *tptr);
+  // final Z measurement of cnt data registers at buf (draw streams t on, or *tptr);
   // in the X basis a Walsh-Hadamard transform of the whole register first,
   // which removes the Pauli-X frame from the outcome probabilities (the
   // outcome probabilities are ratios: a pending renormalisation is harmless)
-  auto traj_final = [&](hipStream_t q, T* buf, uint8_t* bits, uint64_t t, const uint64_t* tptr) {
-    if (xbasis) launch_wht_all<T>(q, buf, n);
+  auto traj_final = [&](hipStream_t q, int cnt, T* buf, uint8_t* bits, uint64_t t, const uint64_t* tptr) {
+    if (xbasis) launch_wht_all<T>(q, buf, n, cnt);
     // (the last pass with a basis change has left the sums)
     if (!flip || xbasis)
-      hipLaunchKernelGGL(k_final_sums<T>, dim3(1u << (n - cb)), dim3(256), 0, q, buf, cb, dsums, (size_t)0);
-    hipLaunchKernelGGL(k_final_measure<T>, dim3(1), dim3(1024), 0, q, buf, n, cb, dsums, job->seed, t,
-                       (uint64_t)R * (uint64_t)draws_round, bits, (size_t)0, (const uint64_t*)nullptr,
+      hipLaunchKernelGGL(k_final_sums<T>, dim3(1u << (n - cb), cnt), dim3(256), 0, q, buf, cb, dsums, ss0.st);
+    hipLaunchKernelGGL(k_final_measure<T>, dim3(cnt), dim3(1024), 0, q, buf, n, cb, dsums, job->seed, t,
+                       (uint64_t)R * (uint64_t)draws_round, bits, ss0.st, (const uint64_t*)nullptr,
                        tptr, (const int*)nullptr, (uint64_t)0,
                        xbasis && !flip ? (const Decision*)nullptr : (const Decision*)&ddec[fin],
-                       (size_t)0, xbasis ? 1 : 0);
+                       ss0.dec, xbasis ? 1 : 0);
   };
   double pass_ms_graph = -1.0;
+  int last_cnt = 1;  // trajectories of the last group (small registers)
   std::vector<Decision> fin_host(res->final_states ? job->n_traj : 0);
   if (job->flags & SV_RUN_GRAPH) {
     // one trajectory's sequence, staged through fixed buffers and a device
@@ -1644,17 +1665,18 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     HIP_OK(hipStreamBeginCapture(G.q, hipStreamCaptureModeThreadLocal));
     sv_status cst = SV_OK;
     {
-      hipLaunchKernelGGL(k_prepare, dim3((unsigned)((per_traj + 127) / 128)), dim3(128), 0, G.q,
-                         dblocks, ns, R, draws_round, job->seed, job->traj0, 1, job->p, deps, rt_s,
+      hipLaunchKernelGGL(k_prepare, dim3((unsigned)((per_traj * 16 + 127) / 128)), dim3(128), 0, G.q,
+                         dblocks, ns, R, draws_round, job->seed, job->traj0, 1, job->p, dcs, rt_s,
                          derr, (const uint64_t*)(dcur + 1), (const double*)dthr);
       if (dn_s)
         hipLaunchKernelGGL(k_prepare_dense, dim3((unsigned)((per_traj * 16 + 127) / 128)), dim3(128), 0, G.q,
-                           dblocks, ns, R, draws_round, job->seed, job->traj0, 1, job->p, deps, dn_s, derr,
+                           dblocks, ns, R, draws_round, job->seed, job->traj0, 1, job->p, dcs, dn_s, derr,
                            (const uint64_t*)(dcur + 1), (const double*)dthr);
       T* fbuf = st;
-      cst = spec ? traj_spec(G.q, rt_s, rec_s, p1_s, false, &fbuf) : traj_passes(G.q, rt_s, dn_s, rec_s, p1_s, false);
+      cst = spec ? traj_spec(G.q, 1, rt_s, rec_s, p1_s, false, &fbuf)
+                 : traj_passes(G.q, 1, rt_s, dn_s, rec_s, p1_s, false);
       if (cst == SV_OK) {
-        traj_final(G.q, fbuf, bits_s, 0, dcur + 1);
+        traj_final(G.q, 1, fbuf, bits_s, 0, dcur + 1);
         hipLaunchKernelGGL(k_commit, dim3(1), dim3(256), 0, G.q, rec_s, p1_s, bits_s, drec, dp1, dbits,
                            per_traj, n, dcur, dcur + 1, job->traj0);
       }
@@ -1682,40 +1704,49 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     for (int c0 = 0; c0 < job->n_traj; c0 += chunk) {
       const int cn = std::min(chunk, job->n_traj - c0);
       const int64_t nthreads = (int64_t)cn * per_traj;
-      hipLaunchKernelGGL(k_prepare, dim3((unsigned)((nthreads + 127) / 128)), dim3(128), 0, s, dblocks,
-                         ns, R, draws_round, job->seed, job->traj0 + (uint64_t)c0, cn, job->p, deps,
+      hipLaunchKernelGGL(k_prepare, dim3((unsigned)((nthreads * 16 + 127) / 128)), dim3(128), 0, s, dblocks,
+                         ns, R, draws_round, job->seed, job->traj0 + (uint64_t)c0, cn, job->p, dcs,
                          drt, derr, (const uint64_t*)nullptr, (const double*)dthr);
       if (ddn)
         hipLaunchKernelGGL(k_prepare_dense, dim3((unsigned)((nthreads * 16 + 127) / 128)), dim3(128), 0, s,
-                           dblocks, ns, R, draws_round, job->seed, job->traj0 + (uint64_t)c0, cn, job->p, deps,
+                           dblocks, ns, R, draws_round, job->seed, job->traj0 + (uint64_t)c0, cn, job->p, dcs,
                            ddn, derr, (const uint64_t*)nullptr, (const double*)dthr);
       HIP_OK(hipGetLastError());
-      for (int ti = 0; ti < cn; ++ti) {
+      for (int ti = 0; ti < cn; ti += slots) {
         if (cancel && cancel->load(std::memory_order_relaxed)) {
           (void)hipStreamSynchronize(s);
           return fail(SV_EBUSY, "cancelled");
         }
-        const int tg = c0 + ti;
+        const int tg = c0 + ti, cnt = std::min(slots, cn - ti);
+        const bool is_last = tg + cnt - 1 == last_t;
+        const bool timed = time_passes && is_last;
         T* buf = st;
+        if (!async && small && is_last) HIP_OK(hipEventRecord(evs[0], s));
         if (spec) {
-          SV_OK_OR_RETURN(traj_spec(s, drt + (size_t)ti * per_traj, drec + (size_t)tg * per_traj,
-                                    dp1 ? dp1 + (size_t)tg * per_traj : nullptr, tg == last_t && !async, &buf));
+          SV_OK_OR_RETURN(traj_spec(s, cnt, drt + (size_t)ti * per_traj, drec + (size_t)tg * per_traj,
+                                    dp1 ? dp1 + (size_t)tg * per_traj : nullptr, timed, &buf));
         } else {
-          SV_OK_OR_RETURN(traj_passes(s, drt + (size_t)ti * per_traj, ddn ? ddn + (size_t)ti * per_traj : nullptr,
+          SV_OK_OR_RETURN(traj_passes(s, cnt, drt + (size_t)ti * per_traj,
+                                      ddn ? ddn + (size_t)ti * per_traj : nullptr,
                                       drec + (size_t)tg * per_traj,
-                                      dp1 ? dp1 + (size_t)tg * per_traj : nullptr, tg == last_t && !async));
+                                      dp1 ? dp1 + (size_t)tg * per_traj : nullptr, timed));
+        }
+        if (!async && small && is_last) {
+          HIP_OK(hipEventRecord(evs[1], s));
+          last_cnt = cnt;
         }
         if (res->final_states) {
           // a speculative run leaves the last unit's renormalisation pending
           if (spec)
-            hipLaunchKernelGGL(k_renorm<T>, dim3((unsigned)std::min<uint64_t>(na / 256, 65536)), dim3(256), 0, s,
-                               buf, na, (const Decision*)&ddec[fin]);
+            hipLaunchKernelGGL(k_renorm<T>, dim3((unsigned)std::min<uint64_t>((na + 255) / 256, 65536), cnt), dim3(256),
+                               0, s, buf, na, (const Decision*)&ddec[fin], ss0.dec);
           HIP_OK(hipMemcpyAsync((char*)res->final_states + (size_t)tg * sizeof(T) * 2 * na, buf,
-                                sizeof(T) * 2 * na, hipMemcpyDeviceToHost, s));
-          HIP_OK(hipMemcpyAsync(&fin_host[tg], &ddec[fin], sizeof(Decision), hipMemcpyDeviceToHost, s));
+                                sizeof(T) * 2 * na * cnt, hipMemcpyDeviceToHost, s));
+          HIP_OK(hipMemcpy2DAsync(&fin_host[tg], sizeof(Decision), &ddec[fin], sizeof(Decision) * n_dec,
+                                  sizeof(Decision), cnt, hipMemcpyDeviceToHost, s));
           HIP_OK(hipStreamSynchronize(s));
         }
-        traj_final(s, buf, dbits + (size_t)tg * n, job->traj0 + (uint64_t)tg, nullptr);
+        traj_final(s, cnt, buf, dbits + (size_t)tg * n, job->traj0 + (uint64_t)tg, nullptr);
         HIP_OK(hipGetLastError());
       }
     }
@@ -1763,7 +1794,11 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   HIP_OK(hipEventElapsedTime(&ms, ev0, ev1));
   double pass_sum = 0.0;
   const int timed_units = spec ? per_units_s : per_units;
-  if (pass_ms_graph < 0.0) {
+  if (pass_ms_graph < 0.0 && small && job->n_traj > 0) {
+    float tm = 0.f;
+    HIP_OK(hipEventElapsedTime(&tm, evs[0], evs[1]));
+    pass_ms_graph = tm / ((double)(timed_units + 1) * last_cnt);
+  } else if (pass_ms_graph < 0.0 && job->n_traj > 0) {
     for (int ui = 0; ui < timed_units; ++ui) {
       float pm = 0.f;
       HIP_OK(hipEventElapsedTime(&pm, evs[2 * ui], evs[2 * ui + 1]));
@@ -1771,8 +1806,9 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     }
   }
   res->gpu_ms = ms;
-  // replayed graphs: the last trajectory's device time per pass (an upper
-  // bound that includes its decisions, draws and final measurement)
+  // replayed graphs and small registers: device time per pass and trajectory
+  // of the last replay or group (an upper bound that includes the decisions,
+  // for graphs also the draws and the final measurement)
   res->pass_ms = pass_ms_graph >= 0.0 ? pass_ms_graph : pass_sum / timed_units;
   res->passes_per_round = spec ? nus : nu;
   res->redo_passes = 0;
