@@ -31,7 +31,9 @@
 // register is s Z^phix X^phiz |psi> written in the mixed basis; a Z member
 // moves F into phiz, an X member moves F into phix and turns the sign s by
 // the parity of F & phiz.
-#include "qec_common.h"
+#pragma once
+
+#include "kernels.hip"
 
 namespace qec {
 

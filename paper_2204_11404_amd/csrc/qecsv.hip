@@ -29,6 +29,7 @@
 #include "qec_common.h"
 #include "kernels.hip"
 #include "passes.h"
+#include "kernels_flip.hip"
 #include "kernels_ops.hip"
 #include "kernels_batch.hip"
 
@@ -393,7 +394,7 @@ sv_tuning default_tuning() {
   sv_tuning t{};
   t.zchain = 4;  // chains of five or six: the autotuner's choice
   t.snake = 1;
-  t.batch_waves_per_cu = 8;
+  t.batch_waves_per_cu = 16;  // 20 000 d = 3 trajectories with the ZZ layer: 1.57 ms with 8, 1.18 with 16
   t.lockstep_mib = 4096;
   t.pass_wgs_per_cu = 0;
   t.xpair = 0;
@@ -1931,6 +1932,45 @@ bool batch_is_small(const Template& tp, int d) {
 template <typename T, typename Alloc>
 sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEvent_t ev_a, hipEvent_t ev_b);
 
+// Descriptor of k_batch_flip; false if the template is not the d = 3 one its
+// lane and register bits are chosen for.
+bool make_flip_small(int d, const Template& tp, FlipSmallDesc& fd) {
+  if (d != 3 || tp.blocks.size() != 8) return false;
+  fd = FlipSmallDesc{};
+  if (tp.n_sites > kFlipSmallSites || tp.n_draws > kFlipSmallDraws) return false;
+  int cols = 0;
+  for (int w : {4, 2})  // the larger checks first: every first column is a multiple of its labels
+    for (int c = 0; c < 8; ++c)
+      if (tp.blocks[c].w == w) {
+        fd.col[c] = cols;
+        for (int x = 0; x < (1 << w); ++x)
+          if (cols < kFlipSmallCols) fd.col_of[cols++] = c << 4 | x;
+      }
+  if (cols != kFlipSmallCols) return false;
+  for (int c = 0; c < 8; ++c) {
+    const TBlock& b = tp.blocks[c];
+    if (b.type != (c < 4 ? 0 : 1) || b.dense || b.n_ops > kMaxOpsBatch) return false;
+    fd.w[c] = b.w;
+    fd.meas[c] = b.draw_off + b.n_draws - 1;
+    for (int l = 0; l < b.w; ++l) {
+      const int q = b.qubit[l];
+      fd.q[c][l] = 1u << q;
+      if (c < 4) fd.parity[c] |= 1u << q;
+      for (int k = 0; k < 6; ++k)
+        if (kFlipLaneQubit[k] == q) fd.lane_pack[k] |= 1u << (4 * c + l);
+      for (int k = 0; k < 3; ++k) {
+        if (kFlipRegQubit[k] != q) continue;
+        if ((c < 4 ? kFlipOwnX[k] : 4 + kFlipOwnZ[k]) != c) return false;  // a corner of another check
+        fd.reg_bit[c < 4 ? 0 : 1][k] = 1u << l;
+      }
+    }
+  }
+  for (const auto& t : fd.reg_bit)
+    for (uint32_t bit : t)
+      if (!bit) return false;
+  return true;
+}
+
 template <typename T>
 sv_status run_batch_core(BatchInputs& in, const Template& tp) {
   const int d = in.d, n = d * d;
@@ -1968,6 +2008,8 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
   const size_t neps = in.eps_stride ? (size_t)nt * in.eps_stride : (size_t)std::max(1, tp.n_sites);
   HIP_OK(M.alloc(&dblocks, sizeof(TBlock) * ns));
   HIP_OK(M.alloc(&dsd, sizeof(SmallDesc) * ns));
+  FlipSmallDesc* dfd = nullptr;
+  HIP_OK(M.alloc(&dfd, sizeof(FlipSmallDesc)));
   HIP_OK(M.alloc(&djc, sizeof(JobConst)));
   HIP_OK(M.alloc(&dorder, sizeof(int) * nt));
   HIP_OK(M.alloc(&drounds, sizeof(int) * nt));
@@ -2000,6 +2042,10 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
   int nw = nt <= 2 * simds ? 2 : 1;
   const int forced = env_int("QECSV_BATCH_SPLIT", 0);
   if (forced == 1 || forced == 2 || forced == 4) nw = forced;
+  // d = 3 without the data ZZ layer: the register in one wave's registers and
+  // the checks in chains of four (k_batch_flip), unless a split is asked for
+  FlipSmallDesc fd;
+  const bool flip = in.zeta == 0.0 && forced == 0 && make_flip_small(d, tp, fd);
   const std::vector<SmallDesc> sd = make_small_descs(n, tp, nw);
   const JobConst jc = make_job_const(d, in.zeta);
   // the op of every gate site (index = site)
@@ -2077,7 +2123,18 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
                          (const SmallShared<T>*)dshared, (const uint32_t*)dinit, (const uint8_t*)dkind);
       return hipGetLastError();
     };
-    if (nw == 4) HIP_OK(launch(k_batch_small<T, 4>, 4));
+    if (flip) {
+      HIP_OK(hipMemcpyAsync(dfd, &fd, sizeof fd, hipMemcpyHostToDevice, s));
+      int per_cu = tuning_for(in.d, sizeof(T) == 8 ? SV_C128 : SV_C64).batch_waves_per_cu, resident = 0;
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, k_batch_flip<T>, 64, 0) == hipSuccess && resident > 0)
+        per_cu = std::min(per_cu, resident);
+      const int grid = std::max(1, std::min(nt, device_cu_count() * per_cu));
+      HIP_OK(hipEventRecord(ev_a, s));
+      hipLaunchKernelGGL(k_batch_flip<T>, dim3(grid), dim3(64), 0, s, dblocks, dfd, tp.n_draws, dseed, dstream, dorder,
+                         nt, drounds, dp, deps, in.eps_stride, drec, in.max_rounds, dbits, derr, (const TOp*)dsites,
+                         tp.n_sites, (const SmallShared<T>*)dshared, (const uint8_t*)dkind);
+      HIP_OK(hipGetLastError());
+    } else if (nw == 4) HIP_OK(launch(k_batch_small<T, 4>, 4));
     else if (nw == 2) HIP_OK(launch(k_batch_small<T, 2>, 2));
     else HIP_OK(launch(k_batch_small<T, 1>, 1));
   }
