@@ -15,8 +15,10 @@
 #include <condition_variable>
 #include <deque>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <thread>
+#include <type_traits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -97,6 +99,198 @@ struct DevBufs {
     return e;
   }
 };
+
+// Pinned host blocks of a call's set-up copies and results: a copy to or from
+// pageable memory waits for an intermediate one (50 KiB: 33 us there, 45 us
+// back, against 13 us).  At most kMost exist, each with one call at a time; a
+// call that finds none free takes pageable memory.  Blocks that the last
+// kWindow calls had no use for are given back, down to one.
+class PinnedPool {
+ public:
+  static constexpr size_t kBlock = (size_t)1 << 20;
+  void* get() {
+    std::lock_guard<std::mutex> lk(mu_);
+    void* p = nullptr;
+    if (!idle_.empty()) {
+      p = idle_.back();
+      idle_.pop_back();
+    } else if (made_ < kMost && hipHostMalloc(&p, kBlock, hipHostMallocPortable) == hipSuccess) {
+      ++made_;
+    } else {
+      return nullptr;
+    }
+    peak_ = std::max(peak_, made_ - (int)idle_.size());
+    return p;
+  }
+  void put(void* p) {
+    void* spare = nullptr;
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      idle_.push_back(p);
+      if (++calls_ < kWindow) return;
+      if (made_ > peak_) {
+        spare = idle_.front();
+        idle_.erase(idle_.begin());
+        --made_;
+      }
+      calls_ = 0;
+      peak_ = made_ - (int)idle_.size();
+    }
+    if (spare) (void)hipHostFree(spare);
+  }
+
+ private:
+  static constexpr int kMost = 8, kWindow = 1024;
+  std::mutex mu_;
+  std::vector<void*> idle_;
+  int made_ = 0, peak_ = 0, calls_ = 0;
+};
+PinnedPool& pinned_pool() {
+  static PinnedPool* pool = new PinnedPool;  // outlives every caller, threads at exit included
+  return *pool;
+}
+
+// Host memory of a call's copies on stream s: `pinned_bytes` in a pinned
+// block where that is allowed, fits and is free, else `heap_bytes` of
+// pageable memory.  `busy` while copies may be in flight: released only
+// after they have ended.
+struct HostBlock {
+  char* p = nullptr;
+  bool pinned = false, busy = false;
+  hipStream_t s;
+  HostBlock(size_t pinned_bytes, size_t heap_bytes, hipStream_t stream, bool pageable) : s(stream) {
+    if (!pageable && pinned_bytes <= PinnedPool::kBlock) p = static_cast<char*>(pinned_pool().get());
+    pinned = p != nullptr;
+    if (!p) p = static_cast<char*>(std::malloc(heap_bytes ? heap_bytes : 1));
+  }
+  HostBlock(const HostBlock&) = delete;
+  HostBlock& operator=(const HostBlock&) = delete;
+  ~HostBlock() {
+    if (busy) (void)hipStreamSynchronize(s);
+    if (pinned) pinned_pool().put(p);
+    else std::free(p);
+  }
+};
+
+// The device buffers of one call in one allocation: inputs (one copy to the
+// device), results (cleared, one copy back) and work space, each 256-byte
+// aligned.  put / out / work name a buffer; commit takes the memory, sets
+// every pointer and enqueues the upload; fetch enqueues the copies back, and
+// collect hands them out once the stream has been waited for.
+class Packed {
+ public:
+  explicit Packed(hipStream_t s, bool pageable = false) : s_(s), pageable_(pageable) {}
+  template <typename P>
+  void put(P** d, const void* src, size_t bytes) {
+    const size_t off = reserve(in_, bytes);
+    host_.resize(in_);
+    std::memcpy(host_.data() + off, src, bytes);
+    at_.push_back({reinterpret_cast<void**>(d), 0, off});
+  }
+  // user: where collect puts the result (null: result() reads it)
+  template <typename P>
+  void out(P** d, size_t bytes, void* user = nullptr) {
+    const size_t off = reserve(out_, bytes);
+    at_.push_back({reinterpret_cast<void**>(d), 1, off});
+    res_.push_back({reinterpret_cast<void**>(d), off, bytes, user});
+  }
+  template <typename P>
+  void work(P** d, size_t bytes) {
+    at_.push_back({reinterpret_cast<void**>(d), 2, reserve(work_, bytes)});
+  }
+  // keep != nullptr: the upload's host memory is pageable and handed over (an
+  // asynchronous call's host function deletes it)
+  template <typename Alloc>
+  hipError_t commit(Alloc& M, HostBlock** keep = nullptr) {
+    const size_t a = align(in_), b = align(out_);
+    char* base = nullptr;
+    hipError_t e = M.alloc(&base, work_ ? a + b + work_ : out_ ? a + out_ : in_);
+    if (e != hipSuccess) return e;
+    const size_t start[3] = {0, a, a + b};
+    for (const Place& q : at_) *q.d = base + start[q.region] + q.off;
+    dev_out_ = base + a;
+    block_.reset(new HostBlock(a + out_, in_, s_, pageable_ || keep));
+    if (!block_->p) return hipErrorOutOfMemory;
+    std::memcpy(block_->p, host_.data(), in_);
+    if (out_ && (e = hipMemsetAsync(dev_out_, 0, out_, s_)) != hipSuccess) return e;
+    block_->busy = true;
+    if (in_) e = hipMemcpyAsync(base, block_->p, in_, hipMemcpyHostToDevice, s_);
+    if (keep) {
+      block_->busy = false;
+      *keep = block_.release();
+    }
+    return e;
+  }
+  hipError_t fetch() {
+    if (block_ && block_->pinned) {
+      return hipMemcpyAsync(block_->p + align(in_), dev_out_, out_, hipMemcpyDeviceToHost, s_);
+    }
+    for (Result& r : res_) {
+      if (!r.user) r.own.resize(r.bytes);
+      const hipError_t e = hipMemcpyAsync(r.user ? r.user : r.own.data(), *r.d, r.bytes, hipMemcpyDeviceToHost, s_);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  void collect() {  // after the stream has been waited for
+    block_->busy = false;
+    if (!block_->pinned) return;
+    for (const Result& r : res_)
+      if (r.user) std::memcpy(r.user, block_->p + align(in_) + r.off, r.bytes);
+  }
+  const void* result(const void* d) const {
+    for (const Result& r : res_)
+      if (*r.d == d) return block_->pinned ? block_->p + align(in_) + r.off : r.own.data();
+    return nullptr;
+  }
+
+ private:
+  struct Place {
+    void** d;
+    int region;
+    size_t off;
+  };
+  struct Result {
+    void** d;
+    size_t off, bytes;
+    void* user;
+    std::vector<char> own = {};
+  };
+  static size_t align(size_t n) { return (n + 255) & ~(size_t)255; }
+  static size_t reserve(size_t& used, size_t bytes) {
+    const size_t off = align(used);
+    used = off + std::max<size_t>(bytes, 16);
+    return off;
+  }
+  hipStream_t s_;
+  bool pageable_;
+  size_t in_ = 0, out_ = 0, work_ = 0;
+  std::vector<char> host_;
+  std::vector<Place> at_;
+  std::vector<Result> res_;
+  char* dev_out_ = nullptr;
+  std::unique_ptr<HostBlock> block_;
+};
+
+// No infinity or NaN among n doubles (exponents compared in bulk).
+bool all_finite(const double* v, size_t n) {
+  uint64_t bad = 0;
+  for (size_t i = 0; i < n; ++i) {
+    uint64_t b;
+    std::memcpy(&b, v + i, 8);
+    bad |= (b & 0x7FF0000000000000ull) + 0x0010000000000000ull;
+  }
+  return !(bad >> 63);
+}
+
+// Trajectory indices by rounds, longest first, equal ones in order.
+std::vector<int> by_rounds(const int* rounds, int n, int max_rounds) {
+  std::vector<int> first(max_rounds + 2, 0), order(n);
+  for (int i = 0; i < n; ++i) first[max_rounds - rounds[i] + 1]++;
+  for (int r = 1; r <= max_rounds + 1; ++r) first[r] += first[r - 1];
+  for (int i = 0; i < n; ++i) order[first[max_rounds - rounds[i]]++] = i;
+  return order;
+}
 
 // --------------------------------------------------------------- layout --
 struct Stab {
@@ -1267,19 +1461,6 @@ FlipGrid flip_grid(const FlipPass& h, unsigned want) {
 
 namespace {
 
-// Host-side inputs of one run's set-up copies.  An asynchronous run keeps
-// them alive until its stream has passed the copies (a host function on the
-// stream deletes them), so they may come from pageable memory.
-struct RunStage {
-  std::vector<TBlock> blocks;
-  std::vector<UnitPass> pds;
-  JobConst jc;
-  std::vector<double> cs, thr;  // cos and sin of every site's angle; twirl thresholds
-  std::vector<UnitPass> spds;   // speculative passes
-  std::vector<uint8_t> pred0;   // first-round predictions
-  std::vector<FlipPass> fpds;   // passes with a basis change
-};
-
 // Every block of the template builds a monomial Kraus pair with no Pauli
 // drawn (Paulis keep that form), i.e. the device-side check of the prepare
 // kernels cannot fire; used where the run cannot wait to read that check.
@@ -1383,47 +1564,39 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   const int n_angles = std::max(1, tp.zz_site >= 0 ? tp.zz_site + 1 : tp.n_sites);
   const size_t nrec = (size_t)job->n_traj * per_traj;
   HIP_OK(M.alloc(&st, sizeof(T) * 2 * na * slots));
-  HIP_OK(M.alloc(&partials, sizeof(double) * kChainAcc * n_tiles * slots));
   double* dacc = nullptr;
   unsigned* dticket = nullptr;
-  HIP_OK(M.alloc(&dacc, sizeof(double) * kChainAcc));
-  HIP_OK(M.alloc(&dticket, sizeof(unsigned)));
-  HIP_OK(hipMemsetAsync(dticket, 0, sizeof(unsigned), s));
-  HIP_OK(M.alloc(&dblocks, sizeof(TBlock) * ns));
-  HIP_OK(M.alloc(&dpass, sizeof(UnitPass) * (nu + 2)));
-  HIP_OK(M.alloc(&djc, sizeof(JobConst)));
-  HIP_OK(M.alloc(&dcs, sizeof(double) * 2 * n_angles));
   const int n_dec = (spec ? per_units_s : per_units) + 1;  // a trajectory's decisions
-  HIP_OK(M.alloc(&ddec, sizeof(Decision) * n_dec * slots));
-  HIP_OK(M.alloc(&drec, nrec));
-  HIP_OK(M.alloc(&dbits, (size_t)job->n_traj * n));
-  if (res->p1_trace) HIP_OK(M.alloc(&dp1, sizeof(double) * nrec));
-  HIP_OK(M.alloc(&dsums, (sizeof(double) << (n - cb)) * slots));
-  HIP_OK(M.alloc(&derr, sizeof(int)));
+  int* dredos = nullptr;
+  Packed K(s);
+  K.out(&derr, sizeof(int));
+  K.out(&dredos, sizeof(int));
+  K.out(&dticket, sizeof(unsigned));
+  K.out(&drec, nrec, async ? nullptr : res->records);
+  K.out(&dbits, (size_t)job->n_traj * n, async ? nullptr : res->final_bits);
+  if (res->p1_trace) K.out(&dp1, sizeof(double) * nrec, async ? nullptr : res->p1_trace);
+  K.work(&partials, sizeof(double) * kChainAcc * n_tiles * slots);
+  K.work(&dacc, sizeof(double) * kChainAcc);
+  K.work(&ddec, sizeof(Decision) * n_dec * slots);
+  K.work(&dsums, (sizeof(double) << (n - cb)) * slots);
   HIP_OK(M.alloc(&drt, rt_per_traj * chunk));
   BlockDense* ddn = nullptr;  // dense Kraus pairs (blocks with crosstalk inside)
   if (tp.any_dense) HIP_OK(M.alloc(&ddn, dn_per_traj * chunk));
 
   const std::vector<UnitPass> pds = flip ? std::vector<UnitPass>(nu + 2) : make_unit_passes(n, tb, tp, units);
   FlipPass* dfpass = nullptr;
-  if (flip) HIP_OK(M.alloc(&dfpass, sizeof(FlipPass) * (nu + 2)));
   // speculative runs: the second register, pass descriptors, control records,
-  // first-round predictions (the trivial outcome of every check), redo count
+  // first-round predictions (the trivial outcome of every check)
   T* st2 = nullptr;
   UnitPass* dspass = nullptr;
   SpecCtl* dctl = nullptr;
   uint8_t* dpred0 = nullptr;
-  int* dredos = nullptr;
   std::vector<uint8_t> pred0;
   if (spec) {
     for (const TBlock& b : tp.blocks)
       pred0.push_back(job->gateset == SV_GATESET_CR ? (uint8_t)((b.w / 2) % 2) : (uint8_t)0);
     HIP_OK(M.alloc(&st2, sizeof(T) * 2 * na * slots));
-    HIP_OK(M.alloc(&dspass, sizeof(UnitPass) * spds.size()));
-    HIP_OK(M.alloc(&dctl, sizeof(SpecCtl) * per_units_s * slots));
-    HIP_OK(M.alloc(&dpred0, pred0.size()));
-    HIP_OK(M.alloc(&dredos, sizeof(int)));
-    HIP_OK(hipMemsetAsync(dredos, 0, sizeof(int), s));
+    K.work(&dctl, sizeof(SpecCtl) * per_units_s * slots);
   }
   std::vector<double> eps(n_angles, job->eps);
   if (job->eps_site)
@@ -1441,7 +1614,6 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
       const double sn = std::sin(eps[i]);
       thr[i] = sn * sn;
     }
-    HIP_OK(M.alloc(&dthr, sizeof(double) * thr.size()));
   }
   std::vector<double> cs(2 * (size_t)n_angles, 0.0);
   for (const TBlock& b : tp.blocks)
@@ -1451,41 +1623,33 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
         cs[2 * b.ops[i].site] = std::cos(beta);
         cs[2 * b.ops[i].site + 1] = std::sin(beta);
       }
-  {
-    // set-up copies from a staging block that a host function on the stream
-    // deletes once the stream has passed them (the call may return first)
-    RunStage* stage = new RunStage{tp.blocks, pds, make_job_const(d, job->zeta, xbasis), cs, thr, spds, pred0,
-                                   fplan.passes};
-    const hipError_t e = [&]() -> hipError_t {
-      hipError_t r;
-      if ((r = hipMemcpyAsync(dblocks, stage->blocks.data(), sizeof(TBlock) * ns, hipMemcpyHostToDevice, s)))
-        return r;
-      if ((r = hipMemcpyAsync(dpass, stage->pds.data(), sizeof(UnitPass) * (nu + 2), hipMemcpyHostToDevice,
-                              s)))
-        return r;
-      if ((r = hipMemcpyAsync(djc, &stage->jc, sizeof(JobConst), hipMemcpyHostToDevice, s))) return r;
-      if ((r = hipMemcpyAsync(dcs, stage->cs.data(), sizeof(double) * stage->cs.size(), hipMemcpyHostToDevice, s)))
-        return r;
-      if (dthr && (r = hipMemcpyAsync(dthr, stage->thr.data(), sizeof(double) * stage->thr.size(),
-                                      hipMemcpyHostToDevice, s)))
-        return r;
-      if (flip && (r = hipMemcpyAsync(dfpass, stage->fpds.data(), sizeof(FlipPass) * stage->fpds.size(),
-                                      hipMemcpyHostToDevice, s)))
-        return r;
-      if (spec && (r = hipMemcpyAsync(dspass, stage->spds.data(), sizeof(UnitPass) * stage->spds.size(),
-                                      hipMemcpyHostToDevice, s)))
-        return r;
-      if (spec && (r = hipMemcpyAsync(dpred0, stage->pred0.data(), stage->pred0.size(), hipMemcpyHostToDevice, s)))
-        return r;
-      return hipLaunchHostFunc(s, [](void* q) { delete static_cast<RunStage*>(q); }, stage);
-    }();
+  const JobConst jc = make_job_const(d, job->zeta, xbasis);
+  K.put(&dblocks, tp.blocks.data(), sizeof(TBlock) * ns);
+  K.put(&djc, &jc, sizeof jc);
+  K.put(&dcs, cs.data(), sizeof(double) * cs.size());
+  if (!thr.empty()) K.put(&dthr, thr.data(), sizeof(double) * thr.size());
+  if (flip) K.put(&dfpass, fplan.passes.data(), sizeof(FlipPass) * fplan.passes.size());
+  else if (!spec) K.put(&dpass, pds.data(), sizeof(UnitPass) * pds.size());
+  if (spec) {
+    K.put(&dspass, spds.data(), sizeof(UnitPass) * spds.size());
+    K.put(&dpred0, pred0.data(), pred0.size());
+  }
+  if (async) {
+    // the call may return before the stream has passed the upload: a host
+    // function on the stream releases its host memory
+    HostBlock* keep = nullptr;
+    hipError_t e = K.commit(M, &keep);
+    if (e == hipSuccess) e = hipLaunchHostFunc(s, [](void* q) { delete static_cast<HostBlock*>(q); }, keep);
     if (e != hipSuccess) {
-      (void)hipStreamSynchronize(s);
-      delete stage;
+      if (keep) {
+        (void)hipStreamSynchronize(s);
+        delete keep;
+      }
       return fail(SV_EDEVICE, "set-up copies: %s", hipGetErrorString(e));
     }
+  } else {
+    HIP_OK(K.commit(M));
   }
-  HIP_OK(hipMemsetAsync(derr, 0, sizeof(int), s));
   HIP_OK(hipMemsetAsync(ddec, 0, sizeof(Decision) * n_dec * slots, s));
   if (spec)  // the registers logical |0> is written in: norm 1, frame 0
     hipLaunchKernelGGL(k_dec_init, dim3((unsigned)((slots + 255) / 256)), dim3(256), 0, s, ddec, slots, (size_t)n_dec);
@@ -1767,15 +1931,11 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     }
     HIP_OK(hipEventRecord(ev1, s));
   }
-  int herr = 0;
-  HIP_OK(hipMemcpyAsync(&herr, derr, sizeof herr, hipMemcpyDeviceToHost, s));
+  HIP_OK(K.fetch());
   HIP_OK(hipStreamSynchronize(s));
-  if (herr) return fail(SV_EINVAL, "circuit template is not monomial in its block basis");
-  HIP_OK(hipMemcpyAsync(res->records, drec, nrec, hipMemcpyDeviceToHost, s));
-  HIP_OK(hipMemcpyAsync(res->final_bits, dbits, (size_t)job->n_traj * n, hipMemcpyDeviceToHost, s));
-  if (res->p1_trace)
-    HIP_OK(hipMemcpyAsync(res->p1_trace, dp1, sizeof(double) * nrec, hipMemcpyDeviceToHost, s));
-  HIP_OK(hipStreamSynchronize(s));
+  if (*static_cast<const int*>(K.result(derr)))
+    return fail(SV_EINVAL, "circuit template is not monomial in its block basis");
+  K.collect();
   // registers handed back in the logical frame: amplitude x sits at x ^ phi,
   // after a basis-change pass with the sign of neg and of phix & (x ^ phi)
   if (res->final_states)
@@ -1812,11 +1972,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   // for graphs also the draws and the final measurement)
   res->pass_ms = pass_ms_graph >= 0.0 ? pass_ms_graph : pass_sum / timed_units;
   res->passes_per_round = spec ? nus : nu;
-  res->redo_passes = 0;
-  if (spec) {  // on the job's stream (a plain copy would wait for every stream of the device)
-    HIP_OK(hipMemcpyAsync(&res->redo_passes, dredos, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_OK(hipStreamSynchronize(s));
-  }
+  res->redo_passes = spec ? *static_cast<const int*>(K.result(dredos)) : 0;
   return SV_OK;
 }
 
@@ -1927,8 +2083,8 @@ bool batch_is_small(const Template& tp, int d) {
 }
 
 // The LDS-resident launch with its device buffers from M (DevBufs or Arena);
-// ev_a / ev_b bracket the kernel.  Every buffer is taken before anything is
-// enqueued, so a failed allocation leaves nothing in flight.
+// ev_a / ev_b bracket the kernel.  The buffers are taken at once, before
+// anything is enqueued, so a failed allocation leaves nothing in flight.
 template <typename T, typename Alloc>
 sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEvent_t ev_a, hipEvent_t ev_b);
 
@@ -2006,33 +2162,14 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
   uint8_t *drec = nullptr, *dbits = nullptr;
   const size_t nrec = (size_t)nt * in.max_rounds * ns;
   const size_t neps = in.eps_stride ? (size_t)nt * in.eps_stride : (size_t)std::max(1, tp.n_sites);
-  HIP_OK(M.alloc(&dblocks, sizeof(TBlock) * ns));
-  HIP_OK(M.alloc(&dsd, sizeof(SmallDesc) * ns));
-  FlipSmallDesc* dfd = nullptr;
-  HIP_OK(M.alloc(&dfd, sizeof(FlipSmallDesc)));
-  HIP_OK(M.alloc(&djc, sizeof(JobConst)));
-  HIP_OK(M.alloc(&dorder, sizeof(int) * nt));
-  HIP_OK(M.alloc(&drounds, sizeof(int) * nt));
-  HIP_OK(M.alloc(&derr, sizeof(int)));
-  HIP_OK(M.alloc(&dp, sizeof(double) * nt));
-  HIP_OK(M.alloc(&dseed, sizeof(uint64_t) * nt));
-  HIP_OK(M.alloc(&dstream, sizeof(uint64_t) * nt));
-  HIP_OK(M.alloc(&deps, sizeof(double) * neps));
-  HIP_OK(M.alloc(&drec, nrec));
-  HIP_OK(M.alloc(&dbits, (size_t)nt * n));
   TOp* dsites = nullptr;
-  HIP_OK(M.alloc(&dsites, sizeof(TOp) * std::max(1, tp.n_sites)));
   SmallShared<T>* dshared = nullptr;
-  if (in.eps_stride == 0) HIP_OK(M.alloc(&dshared, sizeof(SmallShared<T>)));
   uint32_t* dinit = nullptr;
-  HIP_OK(M.alloc(&dinit, sizeof(uint32_t) * 16));
   uint8_t* dkind = nullptr;
-  HIP_OK(M.alloc(&dkind, (size_t)std::max(1, tp.n_draws)));
+  FlipSmallDesc* dfd = nullptr;
+  Packed K(s, std::is_same<Alloc, Arena>::value);  // the no-allocation call: no pinned memory either
   // longest trajectories first, so the static assignment balances
-  std::vector<int> order(nt);
-  for (int i = 0; i < nt; ++i) order[i] = i;
-  std::stable_sort(order.begin(), order.end(),
-                   [&](int a, int b) { return in.rounds[a] > in.rounds[b]; });
+  const std::vector<int> order = by_rounds(in.rounds, nt, in.max_rounds);
   // waves per trajectory: a launch of at most two trajectories per SIMD
   // splits each one over 2 waves (more waves hide the latency of the
   // per-circuit chain: 1000 d=3 trajectories 0.090 -> 0.085 ms; 4 waves take
@@ -2053,7 +2190,7 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
   for (const TBlock& b : tp.blocks)
     for (int i = 0; i < b.n_ops; ++i)
       if (b.ops[i].site >= 0) sites[b.ops[i].site] = b.ops[i];
-  HIP_OK(hipMemcpyAsync(dsites, sites.data(), sizeof(TOp) * sites.size(), hipMemcpyHostToDevice, s));
+  K.put(&dsites, sites.data(), sizeof(TOp) * sites.size());
   // angles common to every trajectory: the angle table and noise-free Kraus
   // pairs once, here
   if (in.eps_stride == 0) {
@@ -2076,7 +2213,7 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
         sh.Wc[b][0][x] = (v0.re * v0.re + v0.im * v0.im) * norm;
         sh.Wc[b][1][x] = (v1.re * v1.re + v1.im * v1.im) * norm;
       }
-    HIP_OK(hipMemcpyAsync(dshared, &sh, sizeof sh, hipMemcpyHostToDevice, s));
+    K.put(&dshared, &sh, sizeof sh);
   }
   // logical |0> of the register: bit x set on the X-stabilizer orbit of 0
   std::vector<uint32_t> init_mask(16, 0u);
@@ -2086,24 +2223,32 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
       if (r & jc.span_piv[i]) r ^= jc.span_vec[i];
     if (r == 0) init_mask[x >> 5] |= 1u << (x & 31);
   }
-  HIP_OK(hipMemcpyAsync(dinit, init_mask.data(), sizeof(uint32_t) * init_mask.size(), hipMemcpyHostToDevice, s));
+  K.put(&dinit, init_mask.data(), sizeof(uint32_t) * init_mask.size());
   // kind of every draw of a round: 0 one-qubit location, 1 two-qubit
   // location, 2 measurement
   std::vector<uint8_t> kind(std::max(1, tp.n_draws), 2);
   for (const TBlock& b : tp.blocks)
     for (int k = 0; k + 1 < b.n_draws; ++k) kind[b.draw_off + k] = (uint8_t)((b.n2mask >> k) & 1);
-  HIP_OK(hipMemcpyAsync(dkind, kind.data(), kind.size(), hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(dblocks, tp.blocks.data(), sizeof(TBlock) * ns, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(dsd, sd.data(), sizeof(SmallDesc) * ns, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(djc, &jc, sizeof jc, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(dorder, order.data(), sizeof(int) * nt, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(drounds, in.rounds, sizeof(int) * nt, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(dp, in.p, sizeof(double) * nt, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(dseed, in.seed, sizeof(uint64_t) * nt, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(dstream, in.stream, sizeof(uint64_t) * nt, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(deps, in.eps, sizeof(double) * neps, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemsetAsync(drec, 0, nrec, s));
-  HIP_OK(hipMemsetAsync(derr, 0, sizeof(int), s));
+  K.put(&dkind, kind.data(), kind.size());
+  K.put(&dblocks, tp.blocks.data(), sizeof(TBlock) * ns);
+  K.put(&dsd, sd.data(), sizeof(SmallDesc) * ns);
+  K.put(&djc, &jc, sizeof jc);
+  if (flip) K.put(&dfd, &fd, sizeof fd);
+  K.put(&dorder, order.data(), sizeof(int) * nt);
+  K.put(&drounds, in.rounds, sizeof(int) * nt);
+  K.put(&dp, in.p, sizeof(double) * nt);
+  K.put(&dseed, in.seed, sizeof(uint64_t) * nt);
+  K.put(&dstream, in.stream, sizeof(uint64_t) * nt);
+  // angles per trajectory of a large launch go straight from the caller's
+  // array (29 MB for 65 536 trajectories)
+  const bool eps_apart = sizeof(double) * neps > ((size_t)1 << 18);
+  if (eps_apart) K.work(&deps, sizeof(double) * neps);
+  else K.put(&deps, in.eps, sizeof(double) * neps);
+  K.out(&derr, sizeof(int));
+  K.out(&drec, nrec, in.records);
+  K.out(&dbits, (size_t)nt * n, in.final_bits);
+  HIP_OK(K.commit(M));
+  if (eps_apart) HIP_OK(hipMemcpyAsync(deps, in.eps, sizeof(double) * neps, hipMemcpyHostToDevice, s));
   {
     // a persistent launch: no more workgroups than stay resident at once
     // (the tuned waves per CU, nw waves per workgroup)
@@ -2124,7 +2269,6 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
       return hipGetLastError();
     };
     if (flip) {
-      HIP_OK(hipMemcpyAsync(dfd, &fd, sizeof fd, hipMemcpyHostToDevice, s));
       int per_cu = tuning_for(in.d, sizeof(T) == 8 ? SV_C128 : SV_C64).batch_waves_per_cu, resident = 0;
       if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, k_batch_flip<T>, 64, 0) == hipSuccess && resident > 0)
         per_cu = std::min(per_cu, resident);
@@ -2140,12 +2284,11 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
   }
   HIP_OK(hipGetLastError());
   HIP_OK(hipEventRecord(ev_b, s));
-  int herr = 0;
-  HIP_OK(hipMemcpyAsync(&herr, derr, sizeof herr, hipMemcpyDeviceToHost, s));
-  HIP_OK(hipMemcpyAsync(in.records, drec, nrec, hipMemcpyDeviceToHost, s));
-  HIP_OK(hipMemcpyAsync(in.final_bits, dbits, (size_t)nt * n, hipMemcpyDeviceToHost, s));
+  HIP_OK(K.fetch());
   HIP_OK(hipStreamSynchronize(s));
-  if (herr) return fail(SV_EINVAL, "circuit template is not monomial in its block basis");
+  if (*static_cast<const int*>(K.result(derr)))
+    return fail(SV_EINVAL, "circuit template is not monomial in its block basis");
+  K.collect();
   float ms = 0.f;
   HIP_OK(hipEventElapsedTime(&ms, ev_a, ev_b));
   in.gpu_ms = ms;
@@ -2203,83 +2346,53 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
   double *dp = nullptr, *deps = nullptr, *dsums = nullptr;
   int *drounds = nullptr, *derr = nullptr;
   uint8_t *drec = nullptr, *dbits = nullptr;
-  HIP_OK(M.alloc(&dblocks, sizeof(TBlock) * ns));
-  HIP_OK(M.alloc(&dpass, sizeof(UnitPass) * (nu + 2)));
-  HIP_OK(M.alloc(&djc, sizeof(JobConst)));
   HIP_OK(M.alloc(&st, per_reg_bytes * G));
-  HIP_OK(M.alloc(&partials, sizeof(double) * kChainAcc * n_tiles * G));
-  double* dacc = nullptr;
+  double *dacc = nullptr, *dcs = nullptr;
   unsigned* dticket = nullptr;
-  HIP_OK(M.alloc(&dacc, sizeof(double) * kChainAcc * G));
-  HIP_OK(M.alloc(&dticket, sizeof(unsigned) * G));
-  HIP_OK(hipMemsetAsync(dticket, 0, sizeof(unsigned) * G, s));
-  HIP_OK(M.alloc(&ddec, sizeof(Decision) * dec_stride * G));
-  HIP_OK(M.alloc(&rtA, sizeof(BlockRT) * (size_t)ns * G));
-  HIP_OK(M.alloc(&rtB, sizeof(BlockRT) * (size_t)ns * G));
-  HIP_OK(M.alloc(&dseed, sizeof(uint64_t) * G));
-  HIP_OK(M.alloc(&dstream, sizeof(uint64_t) * G));
-  HIP_OK(M.alloc(&dp, sizeof(double) * G));
-  HIP_OK(M.alloc(&deps, sizeof(double) * (size_t)n_sites * G));
-  double* dcs = nullptr;
-  HIP_OK(M.alloc(&dcs, sizeof(double) * 2 * (size_t)n_sites * G));
-  HIP_OK(M.alloc(&dsums, (sizeof(double) << (n - cb)) * G));
-  HIP_OK(M.alloc(&drounds, sizeof(int) * G));
-  HIP_OK(M.alloc(&derr, sizeof(int)));
-  HIP_OK(M.alloc(&drec, (size_t)per_traj * G));
-  HIP_OK(M.alloc(&dbits, (size_t)n * G));
+  Packed K(s);
+  int* dredos = nullptr;
+  K.out(&derr, sizeof(int));
+  K.out(&dredos, sizeof(int));
+  K.out(&dticket, sizeof(unsigned) * G);
+  K.work(&partials, sizeof(double) * kChainAcc * n_tiles * G);
+  K.work(&dacc, sizeof(double) * kChainAcc * G);
+  K.work(&ddec, sizeof(Decision) * dec_stride * G);
+  K.work(&rtA, sizeof(BlockRT) * (size_t)ns * G);
+  K.work(&rtB, sizeof(BlockRT) * (size_t)ns * G);
+  K.work(&dcs, sizeof(double) * 2 * (size_t)n_sites * G);
+  K.work(&dsums, (sizeof(double) << (n - cb)) * G);
   T* st2 = nullptr;
   UnitPass* dspass = nullptr;
   SpecCtl* dctl = nullptr;
   uint8_t* dpred0 = nullptr;
-  int* dredos = nullptr;
   std::vector<uint8_t> pred0;
   if (spec) {
     for (const TBlock& b : tp.blocks)
       pred0.push_back(in.gateset == SV_GATESET_CR ? (uint8_t)((b.w / 2) % 2) : (uint8_t)0);
     HIP_OK(M.alloc(&st2, per_reg_bytes * G));
-    HIP_OK(M.alloc(&dspass, sizeof(UnitPass) * spds.size()));
-    HIP_OK(M.alloc(&dctl, sizeof(SpecCtl) * ctl_stride * G));
-    HIP_OK(M.alloc(&dpred0, pred0.size()));
-    HIP_OK(M.alloc(&dredos, sizeof(int)));
-    HIP_OK(hipMemcpyAsync(dspass, spds.data(), sizeof(UnitPass) * spds.size(), hipMemcpyHostToDevice, s));
-    HIP_OK(hipMemcpyAsync(dpred0, pred0.data(), pred0.size(), hipMemcpyHostToDevice, s));
-    HIP_OK(hipMemsetAsync(dredos, 0, sizeof(int), s));
+    K.put(&dspass, spds.data(), sizeof(UnitPass) * spds.size());
+    K.put(&dpred0, pred0.data(), pred0.size());
+    K.work(&dctl, sizeof(SpecCtl) * ctl_stride * G);
   }
-
   const std::vector<UnitPass> pds = flip ? std::vector<UnitPass>(nu + 2) : make_unit_passes(n, tb, tp, units);
   FlipPass* dfpass = nullptr;
-  if (flip) {
-    HIP_OK(M.alloc(&dfpass, sizeof(FlipPass) * (nu + 2)));
-    HIP_OK(hipMemcpyAsync(dfpass, fplan.passes.data(), sizeof(FlipPass) * (nu + 2), hipMemcpyHostToDevice, s));
-  }
+  if (flip) K.put(&dfpass, fplan.passes.data(), sizeof(FlipPass) * (nu + 2));
+  else if (!spec) K.put(&dpass, pds.data(), sizeof(UnitPass) * (nu + 2));
   const JobConst jc = make_job_const(d, in.zeta);
-  HIP_OK(hipMemcpyAsync(dblocks, tp.blocks.data(), sizeof(TBlock) * ns, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(dpass, pds.data(), sizeof(UnitPass) * (nu + 2), hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(djc, &jc, sizeof jc, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemsetAsync(derr, 0, sizeof(int), s));
+  K.put(&dblocks, tp.blocks.data(), sizeof(TBlock) * ns);
+  K.put(&djc, &jc, sizeof jc);
+  HIP_OK(K.commit(M));
 
-  std::vector<int> order(nt);
-  for (int i = 0; i < nt; ++i) order[i] = i;
-  std::stable_sort(order.begin(), order.end(),
-                   [&](int a, int b) { return in.rounds[a] > in.rounds[b]; });
-  // a: start, b: end; fork/join: the next round's Kraus pairs are built on a
-  // second stream while the current round's passes run
+  const std::vector<int> order = by_rounds(in.rounds, nt, in.max_rounds);
   struct Ev {
-    hipEvent_t a = nullptr, b = nullptr, fork = nullptr, join = nullptr;
-    hipStream_t s2 = nullptr;
+    hipEvent_t a = nullptr, b = nullptr;
     ~Ev() {
       if (a) (void)hipEventDestroy(a);
       if (b) (void)hipEventDestroy(b);
-      if (fork) (void)hipEventDestroy(fork);
-      if (join) (void)hipEventDestroy(join);
-      if (s2) (void)hipStreamDestroy(s2);
     }
   } ev;
   HIP_OK(hipEventCreate(&ev.a));
   HIP_OK(hipEventCreate(&ev.b));
-  HIP_OK(hipEventCreateWithFlags(&ev.fork, hipEventDisableTiming));
-  HIP_OK(hipEventCreateWithFlags(&ev.join, hipEventDisableTiming));
-  HIP_OK(hipStreamCreateWithFlags(&ev.s2, hipStreamNonBlocking));
   const dim3 block((unsigned)std::max(64, 1 << (tb - 4)));
   const SlotStrides ss{reg, (size_t)ns, dec_stride};
   // passes with a basis change: at least four workgroups per slot of four
@@ -2314,12 +2427,16 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
       for (int k = 0; k < tp.n_sites; ++k)
         heps[(size_t)i * n_sites + k] = in.eps[(size_t)t * in.eps_stride + k];
     }
-    HIP_OK(hipMemcpyAsync(dseed, hseed.data(), sizeof(uint64_t) * gn, hipMemcpyHostToDevice, s));
-    HIP_OK(hipMemcpyAsync(dstream, hstream.data(), sizeof(uint64_t) * gn, hipMemcpyHostToDevice, s));
-    HIP_OK(hipMemcpyAsync(dp, hp.data(), sizeof(double) * gn, hipMemcpyHostToDevice, s));
-    HIP_OK(hipMemcpyAsync(deps, heps.data(), sizeof(double) * n_sites * gn, hipMemcpyHostToDevice, s));
-    HIP_OK(hipMemcpyAsync(drounds, hrounds.data(), sizeof(int) * gn, hipMemcpyHostToDevice, s));
-    HIP_OK(hipMemsetAsync(drec, 0, (size_t)per_traj * gn, s));
+    DevBufs MG(s);  // the group's own buffers, released in stream order
+    Packed KG(s);
+    KG.put(&dseed, hseed.data(), sizeof(uint64_t) * gn);
+    KG.put(&dstream, hstream.data(), sizeof(uint64_t) * gn);
+    KG.put(&dp, hp.data(), sizeof(double) * gn);
+    KG.put(&drounds, hrounds.data(), sizeof(int) * gn);
+    KG.put(&deps, heps.data(), sizeof(double) * n_sites * gn);
+    KG.out(&drec, (size_t)per_traj * gn, hrec.data());
+    KG.out(&dbits, (size_t)n * gn, hbits.data());
+    HIP_OK(KG.commit(MG));
     auto active = [&](int r) {  // slots with more than r rounds (a prefix)
       int a = 0;
       while (a < gn && hrounds[a] > r) ++a;
@@ -2330,9 +2447,13 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
       hipLaunchKernelGGL(k_site_cs, dim3((unsigned)((nth + 255) / 256)), dim3(256), 0, s, dblocks, ns,
                          deps, n_sites, n_sites, gn, dcs);
     }
-    auto prepare = [&](hipStream_t q, int r, BlockRT* out, int slots) {
+    // round r's Kraus pairs.  On the passes' own stream: beside the passes of
+    // the round before, on a second one, they cost those passes more than they
+    // take (2048 trajectories complex64: 10.76 ms so, 10.45 here; with the
+    // data ZZ layer 24.2, 23.5; complex128 16.8, 16.4 and 42.6, 41.6)
+    auto prepare = [&](int r, BlockRT* out, int slots) {
       const int64_t nth = (int64_t)slots * ns * 16;
-      hipLaunchKernelGGL(k_prepare_round, dim3((unsigned)((nth + 255) / 256)), dim3(256), 0, q, dblocks,
+      hipLaunchKernelGGL(k_prepare_round, dim3((unsigned)((nth + 255) / 256)), dim3(256), 0, s, dblocks,
                          ns, r, tp.n_draws, dseed, dstream, dp, dcs, n_sites, slots, out, derr);
     };
     // outcomes of unit u of round r (tables of that round at rt) from the
@@ -2344,7 +2465,7 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
                          rt + units[u].first, ddec + (size_t)r * nu + u, drec + bi, (double*)nullptr,
                          ss, (size_t)per_traj, dacc, dticket, 0);
     };
-    prepare(s, 0, rtA, gn);
+    prepare(0, rtA, gn);
     const int R0 = hrounds[0];
     // final Z measurement of the slots [from, from + cnt) on register buffer
     // buf, their frames in the decision records at dfin
@@ -2371,12 +2492,7 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
         const int Ar = active(r), An = active(r + 1);
         BlockRT* rt_cur = (r & 1) ? rtB : rtA;
         BlockRT* rt_nxt = (r & 1) ? rtA : rtB;
-        if (An > 0) {
-          HIP_OK(hipEventRecord(ev.fork, s));
-          HIP_OK(hipStreamWaitEvent(ev.s2, ev.fork, 0));
-          prepare(ev.s2, r + 1, rt_nxt, An);
-          HIP_OK(hipEventRecord(ev.join, ev.s2));
-        }
+        if (An > 0) prepare(r + 1, rt_nxt, An);
         for (int u = 0; u < nus; ++u, ++ui) {
           const Unit& U = sunits[u];
           const bool zb = U.kind == U_Z;
@@ -2412,7 +2528,6 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
           }
           std::swap(cur, oth);
         }
-        if (An > 0) HIP_OK(hipStreamWaitEvent(s, ev.join, 0));
         if (Ar > An) measure(cur, An, Ar - An, ddec + (size_t)An * dec_stride + ui);
         HIP_OK(hipGetLastError());
       }
@@ -2439,17 +2554,9 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
       const int Ar = active(r), An = active(r + 1);
       BlockRT* rt_cur = (r & 1) ? rtB : rtA;
       BlockRT* rt_nxt = (r & 1) ? rtA : rtB;
-      if (An > 0) {
-        // rt_nxt was last read by the previous round's passes, enqueued above
-        HIP_OK(hipEventRecord(ev.fork, s));
-        HIP_OK(hipStreamWaitEvent(ev.s2, ev.fork, 0));
-        prepare(ev.s2, r + 1, rt_nxt, An);
-        HIP_OK(hipEventRecord(ev.join, ev.s2));
-      }
+      if (An > 0) prepare(r + 1, rt_nxt, An);
       for (int u = 0; u < nu; ++u) {
         const int ui = r * nu + u;
-        // the round's last pass sums the next round's first unit
-        if (u == nu - 1 && An > 0) HIP_OK(hipStreamWaitEvent(s, ev.join, 0));
         const int rev = (++pass_no) & 1;
         const BlockRT* rta = rt_cur + units[u].first;
         if (u < nu - 1) {
@@ -2457,7 +2564,7 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
           decide(Ar, rt_cur, r, u + 1, gx);
           continue;
         }
-        if (An > 0) {
+        if (An > 0) {  // the round's last pass sums the next round's first unit
           SV_OK_OR_RETURN(pass(1 + u, An, st, rta, rt_nxt + units[0].first, ddec + ui, ddec + ui + 1, rev, &gx));
           decide(An, rt_nxt, r + 1, 0, gx);
         }
@@ -2472,9 +2579,9 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
       HIP_OK(hipGetLastError());
     }
     }
-    HIP_OK(hipMemcpyAsync(hrec.data(), drec, (size_t)per_traj * gn, hipMemcpyDeviceToHost, s));
-    HIP_OK(hipMemcpyAsync(hbits.data(), dbits, (size_t)n * gn, hipMemcpyDeviceToHost, s));
+    HIP_OK(KG.fetch());
     HIP_OK(hipStreamSynchronize(s));
+    KG.collect();
     for (int i = 0; i < gn; ++i) {
       const int t = order[g0 + i];
       std::memcpy(in.records + (size_t)t * per_traj, hrec.data() + (size_t)i * per_traj,
@@ -2483,19 +2590,16 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
     }
   }
   HIP_OK(hipEventRecord(ev.b, s));
-  int herr = 0;
-  HIP_OK(hipMemcpyAsync(&herr, derr, sizeof herr, hipMemcpyDeviceToHost, s));
+  HIP_OK(K.fetch());
   HIP_OK(hipStreamSynchronize(s));
-  if (herr) return fail(SV_EINVAL, "circuit template is not monomial in its block basis");
+  K.collect();
+  if (*static_cast<const int*>(K.result(derr)))
+    return fail(SV_EINVAL, "circuit template is not monomial in its block basis");
   float ms = 0.f;
   HIP_OK(hipEventElapsedTime(&ms, ev.a, ev.b));
   in.gpu_ms = ms;
   in.passes_per_round = spec ? nus : nu;
-  in.redo_passes = 0;
-  if (spec) {
-    HIP_OK(hipMemcpyAsync(&in.redo_passes, dredos, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_OK(hipStreamSynchronize(s));
-  }
+  in.redo_passes = spec ? *static_cast<const int*>(K.result(dredos)) : 0;
   return SV_OK;
 }
 
@@ -3344,9 +3448,8 @@ static sv_status check_batch_job(const sv_batch_job* job, const sv_batch_result*
     if (!(job->p[i] >= 0.0 && job->p[i] <= 1.0)) return fail(SV_EINVAL, "p[%d] out of [0, 1]", i);
   }
   const int n_sites = build_template(job->d, job->gateset).n_sites;
-  if (job->eps_site)
-    for (size_t i = 0; i < (size_t)job->n_traj * n_sites; ++i)
-      if (!std::isfinite(job->eps_site[i])) return fail(SV_EINVAL, "non-finite eps_site");
+  if (job->eps_site && !all_finite(job->eps_site, (size_t)job->n_traj * n_sites))
+    return fail(SV_EINVAL, "non-finite eps_site");
   return SV_OK;
 }
 
