@@ -71,7 +71,8 @@ typedef enum {
 #define SV_RUN_GRAPH 1 /* capture one trajectory's launch sequence (draws,
                           passes, decisions, final measurement, record copy)
                           in a HIP graph once and replay it per trajectory;
-                          results are identical to the stream launches */
+                          results are identical to the stream launches (d <=
+                          3 runs that are one launch anyway ignore it) */
 #define SV_RUN_XBASIS 4 /* X-basis memory: logical |+> instead of |0> (the
                            2^(n - n_z) strings with even parity on every Z
                            check, equal amplitudes), and the data qubits
@@ -263,7 +264,8 @@ typedef struct sv_result {
                            their prediction passes); d <= 4, whose
                            trajectories run side by side: per pass and
                            trajectory of the last group, its decisions
-                           included */
+                           included (d <= 3 in one launch: that launch's
+                           share) */
   int passes_per_round; /* out: register passes per round (speculative units:
                            prediction passes per round) */
   int redo_passes;      /* out: speculative units' redo passes that ran, over
@@ -287,7 +289,9 @@ typedef struct sv_result {
  * or a chain of Z checks is summed and applied in one pass with predicted
  * outcomes (the trivial ones in the first round, the previous round's after
  * that) and the pass runs again when a drawn outcome differs.  Records, p1 and
- * states are those of the plain passes.  The environment variable QECSV_SPEC =
+ * states are those of the plain passes.  With d <= 3 and no flag but
+ * SV_RUN_VIRTUAL_Z the whole run is one launch that keeps each register on
+ * chip (passes_per_round then counts the passes it stands for).  The environment variable QECSV_SPEC =
  * 0 / 1 asks for the plain / the speculative passes whatever zeta is (not with
  * the dense crosstalk, which always uses the plain passes). */
 sv_status sv_run_rounds(const sv_job* job, sv_result* res);

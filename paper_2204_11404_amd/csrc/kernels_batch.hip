@@ -28,6 +28,8 @@
 //      ZZ layer and 1/sqrt(S_m) and writes the amplitudes back.
 // After the last round wave 0 measures the data qubits one by one from the
 // highest label down (two-level descent: lane sums, then within one lane).
+// TRACE: the probabilities of the outcomes and the registers before that
+// measurement are written too (single runs that ask for them).
 #include "kernels_flip.hip"
 
 namespace qec {
@@ -260,7 +262,7 @@ __device__ __forceinline__ void small_wht(C2<T>* v, int xreg, int xlanes, int ti
 
 // NW waves (64 NW threads) run one trajectory at a time; lane bits and the
 // wave index together form the thread-index bits of the register layout.
-template <typename T, int NW>
+template <typename T, int NW, bool TRACE>
 __global__ __launch_bounds__(64 * NW) void k_batch_small(
     const TBlock* __restrict__ blocks, const SmallDesc* __restrict__ sdesc, int ns, int n,
     int draws_round, const JobConst* __restrict__ jc, const uint64_t* __restrict__ tseed,
@@ -269,7 +271,8 @@ __global__ __launch_bounds__(64 * NW) void k_batch_small(
     const double* __restrict__ pvec, const double* __restrict__ eps, int eps_stride,
     uint8_t* __restrict__ rec, int max_rounds, uint8_t* __restrict__ bits, int* __restrict__ err,
     const TOp* __restrict__ sites, int n_sites, const SmallShared<T>* __restrict__ shared,
-    const uint32_t* __restrict__ init_mask, const uint8_t* __restrict__ draw_kind) {
+    const uint32_t* __restrict__ init_mask, const uint8_t* __restrict__ draw_kind, double* __restrict__ p1_out,
+    C2<T>* __restrict__ regs_out) {
   static_assert(NW == 1 || NW == 2 || NW == 4, "one, two or four waves per trajectory");
   constexpr int NL = 64 * NW;                       // threads of a trajectory
   constexpr int NA = NW == 1 ? 8 : NW == 2 ? 4 : 2;  // amplitudes per thread
@@ -422,12 +425,15 @@ __global__ __launch_bounds__(64 * NW) void k_batch_small(
         const double p1 = clamp_p1(s1 / (s0 + s1));
         const int m = (S.u[off + nnoise] < p1) ? 1 : 0;
         if (tid == 0) rec[((size_t)t * max_rounds + r) * ns + s] = (uint8_t)m;
+        if (TRACE && p1_out && tid == 0) p1_out[((size_t)t * max_rounds + r) * ns + s] = p1;
         const double scale = m ? r1 : r0;
         if (g_on) {
 #pragma unroll
           for (int j = 0; j < NA; ++j) {
             const uint32_t x = ((uint32_t)j & xm) | xhi;
-            v[j] = mulc(v[j], D[m][x].re, D[m][x].im);
+            // (TRACE: the renormalisation with the factor, one rounding less)
+            const C2<T> e = D[m][x];
+            v[j] = TRACE ? mulc(v[j], (T)((double)e.re * scale), (T)((double)e.im * scale)) : mulc(v[j], e.re, e.im);
           }
         }
         if (xb) small_wht<T, NA>(v, xreg, xlanes, tid);
@@ -447,14 +453,18 @@ __global__ __launch_bounds__(64 * NW) void k_batch_small(
               const int k = __popc((g ^ (g >> 1)) & hmask) + __popc((g ^ (g >> zd)) & vmask);
               o = mulc(o, lzz[k].re, lzz[k].im);
             }
-            o.re *= sc;
-            o.im *= sc;
+            if (!TRACE) {
+              o.re *= sc;
+              o.im *= sc;
+            }
             S.psi[sslot(g)] = o;
           }
         }
         __syncthreads();
       }
     }
+    if (TRACE && regs_out)
+      for (int i = tid; i < (1 << n); i += NL) regs_out[((size_t)t << n) + i] = S.psi[sslot((uint32_t)i)];
     // final Z measurement of the data register, highest label first, by wave
     // 0: lane l holds amplitudes 8 l .. 8 l + 7
     if (wave == 0) {

@@ -221,11 +221,29 @@ class Packed {
     }
     return e;
   }
+  // As commit for a call that may return before the stream has passed the
+  // upload: a host function on the stream releases its host memory.  (No
+  // result() or collect() afterwards; fetch copies into the user's memory.)
+  template <typename Alloc>
+  sv_status commit_async(Alloc& M) {
+    HostBlock* keep = nullptr;
+    hipError_t e = commit(M, &keep);
+    if (e == hipSuccess) e = hipLaunchHostFunc(s_, [](void* q) { delete static_cast<HostBlock*>(q); }, keep);
+    if (e != hipSuccess) {
+      if (keep) {
+        (void)hipStreamSynchronize(s_);
+        delete keep;
+      }
+      return fail(SV_EDEVICE, "set-up copies: %s", hipGetErrorString(e));
+    }
+    return SV_OK;
+  }
   hipError_t fetch() {
     if (block_ && block_->pinned) {
       return hipMemcpyAsync(block_->p + align(in_), dev_out_, out_, hipMemcpyDeviceToHost, s_);
     }
     for (Result& r : res_) {
+      if (!r.user && !block_) continue;
       if (!r.user) r.own.resize(r.bytes);
       const hipError_t e = hipMemcpyAsync(r.user ? r.user : r.own.data(), *r.d, r.bytes, hipMemcpyDeviceToHost, s_);
       if (e != hipSuccess) return e;
@@ -1572,9 +1590,9 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   K.out(&derr, sizeof(int));
   K.out(&dredos, sizeof(int));
   K.out(&dticket, sizeof(unsigned));
-  K.out(&drec, nrec, async ? nullptr : res->records);
-  K.out(&dbits, (size_t)job->n_traj * n, async ? nullptr : res->final_bits);
-  if (res->p1_trace) K.out(&dp1, sizeof(double) * nrec, async ? nullptr : res->p1_trace);
+  K.out(&drec, nrec, res->records);
+  K.out(&dbits, (size_t)job->n_traj * n, res->final_bits);
+  if (res->p1_trace) K.out(&dp1, sizeof(double) * nrec, res->p1_trace);
   K.work(&partials, sizeof(double) * kChainAcc * n_tiles * slots);
   K.work(&dacc, sizeof(double) * kChainAcc);
   K.work(&ddec, sizeof(Decision) * n_dec * slots);
@@ -1634,22 +1652,8 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     K.put(&dspass, spds.data(), sizeof(UnitPass) * spds.size());
     K.put(&dpred0, pred0.data(), pred0.size());
   }
-  if (async) {
-    // the call may return before the stream has passed the upload: a host
-    // function on the stream releases its host memory
-    HostBlock* keep = nullptr;
-    hipError_t e = K.commit(M, &keep);
-    if (e == hipSuccess) e = hipLaunchHostFunc(s, [](void* q) { delete static_cast<HostBlock*>(q); }, keep);
-    if (e != hipSuccess) {
-      if (keep) {
-        (void)hipStreamSynchronize(s);
-        delete keep;
-      }
-      return fail(SV_EDEVICE, "set-up copies: %s", hipGetErrorString(e));
-    }
-  } else {
-    HIP_OK(K.commit(M));
-  }
+  if (async) SV_OK_OR_RETURN(K.commit_async(M));
+  else HIP_OK(K.commit(M));
   HIP_OK(hipMemsetAsync(ddec, 0, sizeof(Decision) * n_dec * slots, s));
   if (spec)  // the registers logical |0> is written in: norm 1, frame 0
     hipLaunchKernelGGL(k_dec_init, dim3((unsigned)((slots + 255) / 256)), dim3(256), 0, s, ddec, slots, (size_t)n_dec);
@@ -1916,10 +1920,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
       }
     }
     if (async) {
-      HIP_OK(hipMemcpyAsync(res->records, drec, nrec, hipMemcpyDeviceToHost, s));
-      HIP_OK(hipMemcpyAsync(res->final_bits, dbits, (size_t)job->n_traj * n, hipMemcpyDeviceToHost, s));
-      if (res->p1_trace)
-        HIP_OK(hipMemcpyAsync(res->p1_trace, dp1, sizeof(double) * nrec, hipMemcpyDeviceToHost, s));
+      HIP_OK(K.fetch());
       HIP_OK(hipEventRecord(done, s));
       // the device buffers are released in stream order when M goes out of
       // scope
@@ -2044,6 +2045,11 @@ struct BatchInputs {
   double gpu_ms;
   int passes_per_round = 0;  // out: register passes per round (lockstep launches)
   int redo_passes = 0;       // out: speculative redos that ran, one per slot and unit
+  // d <= 3 only:
+  double* p1 = nullptr;         // host [n_traj][max_rounds][n_stab], or null
+  void* final_regs = nullptr;   // host [n_traj][2^(d^2)] amplitudes, or null
+  hipEvent_t done = nullptr;    // enqueue only, recorded after the results' copies
+  int waves = 0;                // waves per trajectory (0: by the number of trajectories)
 };
 
 template <typename T>
@@ -2176,13 +2182,15 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
   // 0.138 ms, the per-circuit reduction and decision then dominate);
   // QECSV_BATCH_SPLIT forces 1, 2 or 4
   const int simds = 4 * device_cu_count();
-  int nw = nt <= 2 * simds ? 2 : 1;
+  int nw = in.waves ? in.waves : nt <= 2 * simds ? 2 : 1;
   const int forced = env_int("QECSV_BATCH_SPLIT", 0);
   if (forced == 1 || forced == 2 || forced == 4) nw = forced;
   // d = 3 without the data ZZ layer: the register in one wave's registers and
-  // the checks in chains of four (k_batch_flip), unless a split is asked for
+  // the checks in chains of four (k_batch_flip), unless a split or what it
+  // does not keep - probabilities, registers - is asked for
   FlipSmallDesc fd;
-  const bool flip = in.zeta == 0.0 && forced == 0 && make_flip_small(d, tp, fd);
+  const bool trace = in.p1 || in.final_regs;
+  const bool flip = !trace && in.zeta == 0.0 && forced == 0 && make_flip_small(d, tp, fd);
   const std::vector<SmallDesc> sd = make_small_descs(n, tp, nw);
   const JobConst jc = make_job_const(d, in.zeta);
   // the op of every gate site (index = site)
@@ -2244,10 +2252,16 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
   const bool eps_apart = sizeof(double) * neps > ((size_t)1 << 18);
   if (eps_apart) K.work(&deps, sizeof(double) * neps);
   else K.put(&deps, in.eps, sizeof(double) * neps);
+  const bool async = in.done != nullptr;
+  double* dp1 = nullptr;
+  C2<T>* dregs = nullptr;
   K.out(&derr, sizeof(int));
   K.out(&drec, nrec, in.records);
   K.out(&dbits, (size_t)nt * n, in.final_bits);
-  HIP_OK(K.commit(M));
+  if (in.p1) K.out(&dp1, sizeof(double) * nrec, in.p1);
+  if (in.final_regs) K.out(&dregs, (sizeof(C2<T>) << n) * nt, in.final_regs);
+  if (async) SV_OK_OR_RETURN(K.commit_async(M));
+  else HIP_OK(K.commit(M));
   if (eps_apart) HIP_OK(hipMemcpyAsync(deps, in.eps, sizeof(double) * neps, hipMemcpyHostToDevice, s));
   {
     // a persistent launch: no more workgroups than stay resident at once
@@ -2265,7 +2279,7 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
       hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * nwv), 0, s, dblocks, dsd, ns, n, tp.n_draws, djc,
                          dseed, dstream, dorder, nt, drounds, dp, deps, in.eps_stride, drec,
                          in.max_rounds, dbits, derr, (const TOp*)dsites, tp.n_sites,
-                         (const SmallShared<T>*)dshared, (const uint32_t*)dinit, (const uint8_t*)dkind);
+                         (const SmallShared<T>*)dshared, (const uint32_t*)dinit, (const uint8_t*)dkind, dp1, dregs);
       return hipGetLastError();
     };
     if (flip) {
@@ -2278,13 +2292,17 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
                          nt, drounds, dp, deps, in.eps_stride, drec, in.max_rounds, dbits, derr, (const TOp*)dsites,
                          tp.n_sites, (const SmallShared<T>*)dshared, (const uint8_t*)dkind);
       HIP_OK(hipGetLastError());
-    } else if (nw == 4) HIP_OK(launch(k_batch_small<T, 4>, 4));
-    else if (nw == 2) HIP_OK(launch(k_batch_small<T, 2>, 2));
-    else HIP_OK(launch(k_batch_small<T, 1>, 1));
+    } else if (nw == 4) HIP_OK(trace ? launch(k_batch_small<T, 4, true>, 4) : launch(k_batch_small<T, 4, false>, 4));
+    else if (nw == 2) HIP_OK(trace ? launch(k_batch_small<T, 2, true>, 2) : launch(k_batch_small<T, 2, false>, 2));
+    else HIP_OK(trace ? launch(k_batch_small<T, 1, true>, 1) : launch(k_batch_small<T, 1, false>, 1));
   }
   HIP_OK(hipGetLastError());
   HIP_OK(hipEventRecord(ev_b, s));
   HIP_OK(K.fetch());
+  if (async) {  // the device buffers are released in stream order
+    HIP_OK(hipEventRecord(in.done, s));
+    return SV_OK;
+  }
   HIP_OK(hipStreamSynchronize(s));
   if (*static_cast<const int*>(K.result(derr)))
     return fail(SV_EINVAL, "circuit template is not monomial in its block basis");
@@ -2601,6 +2619,63 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
   in.passes_per_round = spec ? nus : nu;
   in.redo_passes = spec ? *static_cast<const int*>(K.result(dredos)) : 0;
   return SV_OK;
+}
+
+// A run of d <= 3 trajectories as one launch that keeps each register on chip
+// (run_batch_small), from beginning to end: the passes and decisions of a
+// register of 2^9 amplitudes take a launch of some 10 us each, whatever they
+// do (four trajectories of two rounds with probabilities and registers: 435 us
+// by passes, 156 here; 500 of five rounds, records only: 1020, 480).  Taken
+// with graph replay too: one launch has nothing to replay.
+template <typename T>
+sv_status run_rounds_small(const sv_job* job, sv_result* res, const Template& tp, const std::atomic<int>* cancel,
+                           hipEvent_t done) {
+  const int n = job->d * job->d, R = job->rounds;
+  const size_t per_traj = (size_t)R * tp.blocks.size(), reg = sizeof(C2<T>) << n;
+  // (at most 256 MiB of results on the device at a time)
+  const size_t bytes = per_traj * (res->p1_trace ? 9 : 1) + n + (res->final_states ? reg : 0);
+  const int most = done ? job->n_traj : (int)std::max<size_t>(1, std::min<size_t>(job->n_traj, ((size_t)256 << 20) / bytes));
+  std::vector<double> eps(std::max(1, tp.n_sites), job->eps);
+  if (job->eps_site) std::copy(job->eps_site, job->eps_site + tp.n_sites, eps.begin());
+  const std::vector<uint64_t> seeds(most, job->seed);
+  const std::vector<int> rounds(most, R);
+  const std::vector<double> p(most, job->p);
+  std::vector<uint64_t> streams(most);
+  double ms = 0.0;
+  for (int t0 = 0; t0 < job->n_traj; t0 += most) {
+    if (cancel && cancel->load(std::memory_order_relaxed)) return fail(SV_EBUSY, "cancelled");
+    const int cnt = std::min(most, job->n_traj - t0);
+    for (int i = 0; i < cnt; ++i) streams[i] = job->traj0 + (uint64_t)(t0 + i);
+    BatchInputs in{job->d, job->gateset, cnt, R, job->zeta, seeds.data(), streams.data(), rounds.data(), p.data(),
+                   eps.data(), 0, res->records + t0 * per_traj, res->final_bits + (size_t)t0 * n,
+                   (hipStream_t)job->hip_stream, 0.0};
+    if (res->p1_trace) in.p1 = res->p1_trace + t0 * per_traj;
+    if (res->final_states) in.final_regs = (char*)res->final_states + t0 * reg;
+    in.done = done;
+    in.waves = 2;  // (a trajectory's bits do not depend on how many run beside it)
+    SV_OK_OR_RETURN(run_batch_core<T>(in, tp));
+    ms += in.gpu_ms;
+  }
+  const int nu = (int)make_units_paired(tp, tuning_for(job->d, job->dtype).zchain, n,
+                                        tuning_for(job->d, job->dtype).xpair).size();
+  // (as for small registers that run by passes: time per pass and trajectory)
+  res->gpu_ms = done ? -1.0 : ms;
+  res->pass_ms = done ? -1.0 : ms / ((double)(R * nu + 1) * job->n_traj);
+  res->passes_per_round = nu;
+  res->redo_passes = 0;
+  return SV_OK;
+}
+
+// Every run of sv_run_rounds and the server.  What the on-chip launch does
+// not have - twirled angles, the X basis, idle noise (more draws), dense
+// blocks - keeps the passes, and so do d >= 4 and the forced pass kinds.
+template <typename T>
+sv_status run_job(const sv_job* job, sv_result* res, const Template& tp, const std::atomic<int>* cancel = nullptr,
+                  hipEvent_t done = nullptr) {
+  const bool plain = (job->flags & ~(uint32_t)(SV_RUN_GRAPH | SV_RUN_VIRTUAL_Z)) == 0;
+  if (plain && !tp.any_dense && env_int("QECSV_SPEC", -1) < 0 && batch_is_small(tp, job->d) && batch_template_fits(tp))
+    return run_rounds_small<T>(job, res, tp, cancel, done);
+  return run_rounds_t<T>(job, res, tp, cancel, done);
 }
 
 // Device bytes one batched launch of n_traj trajectories holds (admission).
@@ -3420,8 +3495,8 @@ static sv_status run_rounds_entry(const sv_job* job, sv_result* res, hipEvent_t 
     if (done) HIP_OK(hipEventRecord(done, (hipStream_t)job->hip_stream));
     return SV_OK;
   }
-  if (job->dtype == SV_C128) return run_rounds_t<double>(job, res, tp, nullptr, done);
-  return run_rounds_t<float>(job, res, tp, nullptr, done);
+  if (job->dtype == SV_C128) return run_job<double>(job, res, tp, nullptr, done);
+  return run_job<float>(job, res, tp, nullptr, done);
 }
 
 sv_status sv_run_rounds(const sv_job* job, sv_result* res) { return run_rounds_entry(job, res, nullptr); }

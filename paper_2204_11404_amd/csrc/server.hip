@@ -161,8 +161,8 @@ struct sv_server_s {
         st = SV_EBUSY;
       } else {
         const Template tp = build_template(job.d, job.gateset);
-        st = job.dtype == SV_C128 ? run_rounds_t<double>(&job, &res, tp, &cancel)
-                                  : run_rounds_t<float>(&job, &res, tp, &cancel);
+        st = job.dtype == SV_C128 ? run_job<double>(&job, &res, tp, &cancel)
+                                  : run_job<float>(&job, &res, tp, &cancel);
       }
       std::lock_guard<std::mutex> lk(mu);
       --running;
