@@ -212,72 +212,115 @@ __device__ __forceinline__ double clamp_p1(double p1) {
 // ---------------------------------------------------------------- prepare --
 // Draws and Kraus pairs of every block instance of n_traj trajectories
 // (draw streams traj0 + i, or *stream for a single trajectory when given);
+// Draws and Pauli codes of a block instance, 16 lanes each: lane x evaluates
+// draws x, x + 16, ... and the codes of ops x, x + 16, ..., which every lane
+// then holds packed, four bits an op.  Called with the same block on the whole
+// wave and every lane active.
+template <int W>
+struct DrawnOps {
+  const TOp* ops;
+  const double* cs;  // cos and sin of every site's angle
+  uint64_t codes[W];
+  double u_meas;
+  __device__ __forceinline__ TOp op(int i) const { return ops[i]; }
+  __device__ __forceinline__ int code(int i) const {
+    uint64_t w = codes[0];
+#pragma unroll
+    for (int c = 1; c < W; ++c)
+      if ((i >> 4) == c) w = codes[c];
+    return (int)((w >> (4 * (i & 15))) & 15);
+  }
+  __device__ __forceinline__ cd angle(int, const TOp& o) const { return cd{cs[2 * o.site], cs[2 * o.site + 1]}; }
+
+  __device__ __forceinline__ void draw(const TBlock& b, int x, uint64_t seed, uint64_t t, uint64_t k0, double p,
+                                       const double* twirl_thr) {
+    ops = b.ops;
+    const int n_ops = b.n_ops, n_draws = b.n_draws;
+    double u[W];
+#pragma unroll
+    for (int c = 0; c < W; ++c) {
+      u[c] = 1.0;
+      if (16 * c < n_draws && x + 16 * c < n_draws) u[c] = uniform(seed, t, k0 + (uint64_t)(x + 16 * c));
+    }
+    auto shared = [&](int k) {  // draw k (an index per lane)
+      double v = __shfl(u[0], k & 15, 16);
+#pragma unroll
+      for (int c = 1; c < W; ++c)
+        if (16 * c < n_draws) {
+          const double w = __shfl(u[c], k & 15, 16);
+          if ((k >> 4) == c) v = w;
+        }
+      return v;
+    };
+#pragma unroll
+    for (int c = 0; c < W; ++c) {
+      codes[c] = 0;
+      if (16 * c >= n_ops) continue;
+      const int i = x + 16 * c;
+      TOp o{};
+      o.draw = -1;
+      if (i < n_ops) o = b.ops[i];
+      const double ui = shared(o.draw >= 0 ? o.draw : 0);
+      int code = 0;
+      if (o.draw >= 0) {
+        if (is_rotation(o.kind)) code = twirl_thr && ui < twirl_thr[o.site] ? 1 : 0;
+        else if (o.kind == OP_N1_ANC || o.kind == OP_N1_DATA) code = pick_pauli1(ui, p);
+        else code = pick_pauli2(ui, p);
+      }
+      uint64_t m = (uint64_t)code << (4 * x);
+#pragma unroll
+      for (int off = 1; off < 16; off <<= 1) m |= (uint64_t)__shfl_xor((unsigned long long)m, off, 16);
+      codes[c] = m;
+    }
+    u_meas = shared(n_draws - 1);
+  }
+
+  // column x of the instance's Kraus pair
+  __device__ __forceinline__ void column(const TBlock& b, int x, BlockRT& o, int* err) const {
+    const int nx = 1 << b.w;
+    const double norm = b.type == 0 ? 1.0 / (double)nx : 1.0;
+    cd v0{0.0, 0.0}, v1{0.0, 0.0};
+    uint32_t cur = 0;
+    // (a dense block's Kraus pair comes from k_prepare_dense)
+    if (x < nx && !b.dense && !track_ops(b.type == 0, b.n_ops, *this, x, v0, v1, &cur)) atomicOr(err, 1);
+    o.D[0][x][0] = v0.re * norm;
+    o.D[0][x][1] = v0.im * norm;
+    o.D[1][x][0] = v1.re * norm;
+    o.D[1][x][1] = v1.im * norm;
+    o.W[0][x] = (v0.re * v0.re + v0.im * v0.im) * norm;
+    o.W[1][x] = (v1.re * v1.re + v1.im * v1.im) * norm;
+    if (x == 0) {
+      o.F = cur;
+      o.u = u_meas;
+      o.pad = 0;
+    }
+  }
+};
+
 // cs: cos and sin of every gate site's angle; twirl_thr: per-site sin^2 eps of
-// the Pauli-twirled model, or null.  16 lanes per block instance: lane x
-// evaluates draws x, x + 16, ... (shared by shuffles) and then the circuit's
-// column x.  (One thread per instance, evaluating its angles' cos and sin for
-// all 16 columns, took 260 us however few the instances.)
+// the Pauli-twirled model, or null.  16 lanes per block instance and four
+// instances of the same check a wave (its ops are then scalar and no lane
+// waits for another circuit's).  Bound by the chain of a circuit's ops: a d =
+// 4 run of six trajectories of three rounds 53 -> 16 us.
 static __global__ __launch_bounds__(128) void k_prepare(
     const TBlock* __restrict__ blocks, int n_stab, int rounds, int draws_per_round, uint64_t seed, uint64_t traj0,
     int n_traj, double p, const double* __restrict__ cs, BlockRT* __restrict__ out, int* __restrict__ err,
     const uint64_t* __restrict__ stream, const double* __restrict__ twirl_thr) {
-  const int per_traj = rounds * n_stab;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t inst = gid >> 4;
+  const int64_t n_inst = (int64_t)n_traj * rounds;  // of a check
+  const int64_t waves = (n_inst + 3) >> 2, wave = gid >> 6;
+  const int s = __builtin_amdgcn_readfirstlane((int)(wave / waves));
+  if (s >= n_stab) return;
+  const int64_t q = (wave % waves) * 4 + ((gid >> 4) & 3);
   const int x = (int)(gid & 15);
-  const bool valid = inst < (int64_t)per_traj * n_traj;
-  const int ti = valid ? (int)(inst / per_traj) : 0;
-  const int bi = valid ? (int)(inst % per_traj) : 0;
-  const TBlock& b = blocks[bi % n_stab];
-  const uint64_t k0 = (uint64_t)(bi / n_stab) * (uint64_t)draws_per_round + (uint64_t)b.draw_off;
-  const uint64_t t = stream ? *stream : traj0 + (uint64_t)ti;
-  double u[kMaxOps / 16];  // a block has fewer draws than kMaxOps
-#pragma unroll
-  for (int c = 0; c < kMaxOps / 16; ++c)
-    u[c] = valid && x + 16 * c < b.n_draws ? uniform(seed, t, k0 + (uint64_t)(x + 16 * c)) : 1.0;
-  auto draw = [&](int k) {  // by every lane of the group
-    double v = __shfl(u[0], k & 15, 16);
-#pragma unroll
-    for (int c = 1; c < kMaxOps / 16; ++c) {
-      const double w = __shfl(u[c], k & 15, 16);
-      if ((k >> 4) == c) v = w;
-    }
-    return v;
-  };
-  // every lane runs every shuffle (the op count differs between groups)
-  uint8_t pauli[kMaxOps];
-  int n_ops = b.n_ops;
-  for (int off = 32; off >= 16; off >>= 1) n_ops = max(n_ops, __shfl_xor(n_ops, off, 64));
-  for (int i = 0; i < n_ops; ++i) {
-    const bool drawn = i < b.n_ops && b.ops[i].draw >= 0;
-    const double ui = draw(drawn ? b.ops[i].draw : 0);
-    pauli[i] = 0;
-    if (!drawn) continue;
-    const TOp& op = b.ops[i];
-    if (is_rotation(op.kind)) pauli[i] = (uint8_t)(twirl_thr && ui < twirl_thr[op.site] ? 1 : 0);
-    else if (op.kind == OP_N1_ANC || op.kind == OP_N1_DATA) pauli[i] = (uint8_t)pick_pauli1(ui, p);
-    else pauli[i] = (uint8_t)pick_pauli2(ui, p);
-  }
-  const double um = draw(b.n_draws - 1);
-  if (!valid) return;
-  BlockRT& o = out[inst];
-  const int nx = 1 << b.w;
-  const double norm = b.type == 0 ? 1.0 / (double)nx : 1.0;
-  cd v0{0.0, 0.0}, v1{0.0, 0.0};
-  uint32_t cur = 0;
-  // (a dense block's Kraus pair comes from k_prepare_dense)
-  if (x < nx && !b.dense && !track_column(b, CsFromTable{cs}, pauli, x, v0, v1, &cur)) atomicOr(err, 1);
-  o.D[0][x][0] = v0.re * norm;
-  o.D[0][x][1] = v0.im * norm;
-  o.D[1][x][0] = v1.re * norm;
-  o.D[1][x][1] = v1.im * norm;
-  o.W[0][x] = (v0.re * v0.re + v0.im * v0.im) * norm;
-  o.W[1][x] = (v1.re * v1.re + v1.im * v1.im) * norm;
-  if (x == 0) {
-    o.F = cur;
-    o.u = um;
-    o.pad = 0;
-  }
+  const bool valid = q < n_inst;
+  const int ti = valid ? (int)(q / rounds) : 0, r = valid ? (int)(q % rounds) : 0;
+  const TBlock& b = blocks[s];
+  DrawnOps<kMaxOps / 16> ops;
+  ops.cs = cs;
+  ops.draw(b, x, seed, stream ? *stream : traj0 + (uint64_t)ti,
+           (uint64_t)r * (uint64_t)draws_per_round + (uint64_t)b.draw_off, p, twirl_thr);
+  if (valid) ops.column(b, x, out[((size_t)ti * rounds + r) * n_stab + s], err);
 }
 
 // Dense Kraus pairs of the blocks that are not monomial in their basis: one
@@ -339,60 +382,29 @@ static __global__ void k_site_cs(const TBlock* __restrict__ blocks, int n_stab,
 }
 
 // Kraus pairs of round r for `slots` trajectories with their own seed, draw
-// stream and p: 16 lanes per block instance, lane x evaluates draw x (shared
-// with the group by shuffles) and then the circuit's column x.
+// stream and p (as k_prepare).  Bound by vector instructions: d = 4, 2275
+// slots on average 178 -> 29 us (every lane picked every op's Pauli, with up
+// to 15 divisions, and four circuits' ops took turns in a wave).
 static __global__ __launch_bounds__(256) void k_prepare_round(
     const TBlock* __restrict__ blocks, int n_stab, int r, int draws_round,
     const uint64_t* __restrict__ seeds, const uint64_t* __restrict__ streams,
     const double* __restrict__ pvec, const double* __restrict__ cs, int n_sites, int slots,
     BlockRT* __restrict__ out, int* __restrict__ err) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t inst = gid >> 4;  // (slot, stabilizer)
+  const int64_t waves = (slots + 3) >> 2, wave = gid >> 6;
+  const int s = __builtin_amdgcn_readfirstlane((int)(wave / waves));
+  if (s >= n_stab) return;
+  const int q = (int)(wave % waves) * 4 + (int)((gid >> 4) & 3);
   const int x = (int)(gid & 15);
-  const bool valid = inst < (int64_t)slots * n_stab;
-  const int slot = valid ? (int)(inst / n_stab) : 0;
-  const int s = valid ? (int)(inst % n_stab) : 0;
+  const bool valid = q < slots;
+  const int slot = valid ? q : 0;
   const TBlock& b = blocks[s];
-  const double p = pvec[slot];
-  const uint64_t k0 = (uint64_t)r * (uint64_t)draws_round + (uint64_t)b.draw_off;
-  const double u = (valid && x < b.n_draws) ? uniform(seeds[slot], streams[slot], k0 + (uint64_t)x) : 1.0;
-  // every lane runs every shuffle (the op count differs between groups); the
-  // host admits templates of at most kMaxOpsBatch ops and 16 draws here
-  uint8_t pauli[kMaxOpsBatch];
-  for (int i = 0; i < kMaxOpsBatch; ++i) {
-    const TOp& op = b.ops[i];
-    const bool drawn = i < b.n_ops && op.draw >= 0;
-    const double ui = __shfl(u, drawn ? op.draw : 0, 16);
-    pauli[i] = 0;
-    if (drawn)
-      pauli[i] = (uint8_t)((op.kind == OP_N1_ANC || op.kind == OP_N1_DATA) ? pick_pauli1(ui, p)
-                                                                            : pick_pauli2(ui, p));
-  }
-  const double um = __shfl(u, b.n_draws - 1, 16);
-  if (!valid) return;
-  BlockRT& o = out[inst];
-  const int nx = 1 << b.w;
-  const double norm = b.type == 0 ? 1.0 / (double)nx : 1.0;
-  if (x < nx) {
-    cd v0, v1;
-    uint32_t cur = 0;
-    if (!track_column(b, CsFromTable{cs + (size_t)slot * n_sites * 2}, pauli, x, v0, v1, &cur))
-      atomicOr(err, 1);
-    o.D[0][x][0] = v0.re * norm;
-    o.D[0][x][1] = v0.im * norm;
-    o.D[1][x][0] = v1.re * norm;
-    o.D[1][x][1] = v1.im * norm;
-    o.W[0][x] = (v0.re * v0.re + v0.im * v0.im) * norm;
-    o.W[1][x] = (v1.re * v1.re + v1.im * v1.im) * norm;
-    if (x == 0) {
-      o.F = cur;
-      o.u = um;
-      o.pad = 0;
-    }
-  } else {
-    o.D[0][x][0] = o.D[0][x][1] = o.D[1][x][0] = o.D[1][x][1] = 0.0;
-    o.W[0][x] = o.W[1][x] = 0.0;
-  }
+  // (the host admits templates of at most kMaxOpsBatch ops here)
+  DrawnOps<(kMaxOpsBatch + 15) / 16> ops;
+  ops.cs = cs + (size_t)slot * n_sites * 2;
+  ops.draw(b, x, seeds[slot], streams[slot], (uint64_t)r * (uint64_t)draws_round + (uint64_t)b.draw_off, pvec[slot],
+           nullptr);
+  if (valid) ops.column(b, x, out[(size_t)slot * n_stab + s], err);
 }
 
 // -------------------------------------------------------------------- pass --

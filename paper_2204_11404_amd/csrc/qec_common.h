@@ -128,12 +128,16 @@ struct BlockDense {
 // Thresholds of the depolarizing channels: Pauli j is chosen for the first
 // j with u < j p / 3 (one-qubit, j = 1..3 -> X, Y, Z) or u < j p / 15
 // (two-qubit, j = 1..15 -> P[j >> 2] (x) P[j & 3] on (first, second)).
+// (The thresholds rise with j, so the last one tells whether any is above u:
+// one division for the draws that pick nothing, not 15.)
 QEC_HD int pick_pauli1(double u, double p) {
+  if (!(u < 3.0 * p / 3.0)) return 0;
   for (int j = 1; j <= 3; ++j)
     if (u < (double)j * p / 3.0) return j;
   return 0;
 }
 QEC_HD int pick_pauli2(double u, double p) {
+  if (!(u < 15.0 * p / 15.0)) return 0;
   for (int j = 1; j <= 15; ++j)
     if (u < (double)j * p / 15.0) return j;
   return 0;

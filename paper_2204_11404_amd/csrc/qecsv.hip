@@ -1655,6 +1655,8 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   if (async) SV_OK_OR_RETURN(K.commit_async(M));
   else HIP_OK(K.commit(M));
   HIP_OK(hipMemsetAsync(ddec, 0, sizeof(Decision) * n_dec * slots, s));
+  // four instances of a check a wave
+  auto prepare_grid = [&](int n_traj) { return (unsigned)(((((int64_t)n_traj * R + 3) / 4) * ns + 1) / 2); };
   if (spec)  // the registers logical |0> is written in: norm 1, frame 0
     hipLaunchKernelGGL(k_dec_init, dim3((unsigned)((slots + 255) / 256)), dim3(256), 0, s, ddec, slots, (size_t)n_dec);
 
@@ -1834,7 +1836,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     HIP_OK(hipStreamBeginCapture(G.q, hipStreamCaptureModeThreadLocal));
     sv_status cst = SV_OK;
     {
-      hipLaunchKernelGGL(k_prepare, dim3((unsigned)((per_traj * 16 + 127) / 128)), dim3(128), 0, G.q,
+      hipLaunchKernelGGL(k_prepare, dim3(prepare_grid(1)), dim3(128), 0, G.q,
                          dblocks, ns, R, draws_round, job->seed, job->traj0, 1, job->p, dcs, rt_s,
                          derr, (const uint64_t*)(dcur + 1), (const double*)dthr);
       if (dn_s)
@@ -1873,7 +1875,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     for (int c0 = 0; c0 < job->n_traj; c0 += chunk) {
       const int cn = std::min(chunk, job->n_traj - c0);
       const int64_t nthreads = (int64_t)cn * per_traj;
-      hipLaunchKernelGGL(k_prepare, dim3((unsigned)((nthreads * 16 + 127) / 128)), dim3(128), 0, s, dblocks,
+      hipLaunchKernelGGL(k_prepare, dim3(prepare_grid(cn)), dim3(128), 0, s, dblocks,
                          ns, R, draws_round, job->seed, job->traj0 + (uint64_t)c0, cn, job->p, dcs,
                          drt, derr, (const uint64_t*)nullptr, (const double*)dthr);
       if (ddn)
@@ -2470,7 +2472,7 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
     // take (2048 trajectories complex64: 10.76 ms so, 10.45 here; with the
     // data ZZ layer 24.2, 23.5; complex128 16.8, 16.4 and 42.6, 41.6)
     auto prepare = [&](int r, BlockRT* out, int slots) {
-      const int64_t nth = (int64_t)slots * ns * 16;
+      const int64_t nth = (int64_t)((slots + 3) / 4) * ns * 64;
       hipLaunchKernelGGL(k_prepare_round, dim3((unsigned)((nth + 255) / 256)), dim3(256), 0, s, dblocks,
                          ns, r, tp.n_draws, dseed, dstream, dp, dcs, n_sites, slots, out, derr);
     };
