@@ -259,7 +259,7 @@ typedef struct sv_result {
                            final measurement, or NULL */
   double gpu_ms;        /* out: device time of the whole run (hipEvents) */
   double pass_ms;       /* out: mean device time per register pass of the last
-                           trajectory (one pass applies an X check, a pair of
+                           trajectory's second round, or its only one (one pass applies an X check, a pair of
                            them or a chain of checks; with speculative units,
                            their prediction passes); d <= 4, whose
                            trajectories run side by side: per pass and

@@ -1660,7 +1660,9 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   if (spec)  // the registers logical |0> is written in: norm 1, frame 0
     hipLaunchKernelGGL(k_dec_init, dim3((unsigned)((slots + 255) / 256)), dim3(256), 0, s, ddec, slots, (size_t)n_dec);
 
-  // whole-run events plus one pair around every pass of the last trajectory
+  // whole-run events plus one pair around every pass of the last trajectory's
+  // second round (its only one for rounds = 1): an event between two kernels
+  // keeps them some 5 us apart
   // (small registers: one pair around the last group's passes and decisions,
   // an event between launches of a few microseconds would cost as much)
   struct Events {
@@ -1669,7 +1671,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
       for (hipEvent_t e : ev) (void)hipEventDestroy(e);
     }
   } E;
-  E.ev.resize(async ? 0 : 2 + (small ? 2 : 2 * std::max(per_units, per_units_s)), nullptr);
+  E.ev.resize(async ? 0 : 2 + (small ? 2 : 2 * std::max(nu, nus)), nullptr);
   for (auto& e : E.ev) HIP_OK(hipEventCreate(&e));
   hipEvent_t ev0 = async ? nullptr : E.ev[0], ev1 = async ? nullptr : E.ev[1];
   hipEvent_t* evs = async ? nullptr : E.ev.data() + 2;
@@ -1689,6 +1691,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   const int draws_round = tp.n_draws;
   const int last_t = job->n_traj - 1;
   const bool time_passes = !async && !small;
+  const int timed_round = std::min(1, R - 1);
   // block instance of the first member of unit instance ui
   auto inst = [&](int ui) { return (ui / nu) * ns + units[ui % nu].first; };
   // passes and decisions of cnt trajectories side by side, the block tables of
@@ -1729,9 +1732,10 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
       const int u = ui % nu;
       const bool last = (ui == per_units - 1);
       const int pidx = last ? nu + 1 : 1 + u;
-      if (timed) HIP_OK(hipEventRecord(evs[2 * ui], q));
+      const bool tm = timed && ui / nu == timed_round;
+      if (tm) HIP_OK(hipEventRecord(evs[2 * u], q));
       SV_OK_OR_RETURN(pass(pidx, ui, last, snake ? ((ui + 1) & 1) : 0, &parts));
-      if (timed) HIP_OK(hipEventRecord(evs[2 * ui + 1], q));
+      if (tm) HIP_OK(hipEventRecord(evs[2 * u + 1], q));
       if (!last) decide(ui + 1, parts);
     }
     HIP_OK(hipGetLastError());
@@ -1767,9 +1771,10 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                            &ddec[ui + 1], rec + bi, p1 ? p1 + bi : nullptr, &dctl[ui], dacc, dticket, ss0,
                            (size_t)per_traj, (size_t)per_units_s, small ? 0 : 1);
       };
-      if (timed) HIP_OK(hipEventRecord(evs[2 * ui], q));
+      const bool tm = timed && r == timed_round;
+      if (tm) HIP_OK(hipEventRecord(evs[2 * u], q));
       SV_OK_OR_RETURN(pass(false));
-      if (timed) HIP_OK(hipEventRecord(evs[2 * ui + 1], q));
+      if (tm) HIP_OK(hipEventRecord(evs[2 * u + 1], q));
       decide();
       const int redos = (!zb && U.len == 2) ? 2 : 1;
       for (int k = 0; k < redos; ++k) {
@@ -1957,11 +1962,11 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   float ms = 0.f;
   HIP_OK(hipEventElapsedTime(&ms, ev0, ev1));
   double pass_sum = 0.0;
-  const int timed_units = spec ? per_units_s : per_units;
+  const int timed_units = spec ? nus : nu;
   if (pass_ms_graph < 0.0 && small && job->n_traj > 0) {
     float tm = 0.f;
     HIP_OK(hipEventElapsedTime(&tm, evs[0], evs[1]));
-    pass_ms_graph = tm / ((double)(timed_units + 1) * last_cnt);
+    pass_ms_graph = tm / ((double)(R * timed_units + 1) * last_cnt);
   } else if (pass_ms_graph < 0.0 && job->n_traj > 0) {
     for (int ui = 0; ui < timed_units; ++ui) {
       float pm = 0.f;
