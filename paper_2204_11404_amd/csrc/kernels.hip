@@ -2073,10 +2073,20 @@ __global__ __launch_bounds__(256) void k_final_sums(const T* __restrict__ st, in
 // Each phase builds the pairwise sum tree of its leaves (the chunk sums, then
 // |psi|^2 over the selected chunk) in LDS, one level per step, and one thread
 // walks it from the root: at each level the two child sums give p1, the
-// qubit's draw picks a child.  The bottom level of leaves stays in memory.
+// qubit's draw picks a child.  Up to 2^12 leaves are kept in LDS as well.
 // Slot blockIdx.x: its register at st + slot * st_stride, its draw stream
 // (seed[slot], t[slot]) when the arrays are given, else (seed0, t0 + slot).
-template <typename T>
+// FLIP: the register is one that a pass with a basis change has summed without
+// applying its chain A (descriptor ff.pd, tables ff.rta, decision ff.da of
+// the first slot): the leaves take A's weights, and amplitude g sits at
+// flip_place(g) (1024 threads, cb = 12: every leaf once, by thread i % 1024).
+struct FlipFinal {
+  const FlipPass* pd;
+  const BlockRT* rta;
+  const Decision* da;
+  size_t rt_stride;
+};
+template <typename T, bool FLIP>
 __global__ __launch_bounds__(1024) void k_final_measure(const T* __restrict__ st, int n, int cb,
                                                          const double* __restrict__ sums,
                                                          uint64_t seed0, uint64_t t0, uint64_t k0,
@@ -2086,7 +2096,7 @@ __global__ __launch_bounds__(1024) void k_final_measure(const T* __restrict__ st
                                                          const int* __restrict__ rounds,
                                                          uint64_t draws_round,
                                                          const Decision* __restrict__ dfin,
-                                                         size_t dfin_stride, int xframe) {
+                                                         size_t dfin_stride, int xframe, FlipFinal ff) {
   const int slot = blockIdx.x;
   // Pauli frame of the register: logical bit q = physical bit q ^ phi_q (the
   // X-type frame, or after a transform of every qubit the Z-type one)
@@ -2106,8 +2116,13 @@ __global__ __launch_bounds__(1024) void k_final_measure(const T* __restrict__ st
     if (h == 0) return 0;
     const int N = 1 << h;
     __syncthreads();
-    for (int k = N / 2 + (int)threadIdx.x; k < N; k += (int)blockDim.x) tree[k] = leaf(2 * k - N) + leaf(2 * k + 1 - N);
-    for (int lev = h - 2; lev >= 0; --lev) {
+    const bool held = 2 * N <= 8192;
+    if (held) {
+      for (int i = threadIdx.x; i < N; i += (int)blockDim.x) tree[N + i] = leaf(i);
+    } else {
+      for (int k = N / 2 + (int)threadIdx.x; k < N; k += (int)blockDim.x) tree[k] = leaf(2 * k - N) + leaf(2 * k + 1 - N);
+    }
+    for (int lev = held ? h - 1 : h - 2; lev >= 0; --lev) {
       __syncthreads();
       for (int k = (1 << lev) + (int)threadIdx.x; k < (2 << lev); k += (int)blockDim.x)
         tree[k] = tree[2 * k] + tree[2 * k + 1];
@@ -2118,7 +2133,7 @@ __global__ __launch_bounds__(1024) void k_final_measure(const T* __restrict__ st
       for (int i = 0; i < h; ++i) {
         const int level = level0 + i;
         const int fq = (phi >> (n - 1 - level)) & 1;
-        const bool bottom = i == h - 1;
+        const bool bottom = !held && i == h - 1;
         const double P0 = bottom ? leaf(2 * c - N) : tree[2 * c];
         const double P1 = bottom ? leaf(2 * c + 1 - N) : tree[2 * c + 1];
         const double S0 = fq ? P1 : P0, S1 = fq ? P0 : P1;
@@ -2136,11 +2151,42 @@ __global__ __launch_bounds__(1024) void k_final_measure(const T* __restrict__ st
   const int hb = n - cb;  // bits resolved by chunk sums
   const int chunk = descend(hb, 0, [&](int i) { return sums[i]; });
   const uint64_t cbase = (uint64_t)chunk << cb;
-  descend(cb, hb, [&](int i) {
-    const C2<T> a = ld2(st, cbase + (uint64_t)i);
-    const double re = (double)a.re, im = (double)a.im;
-    return re * re + im * im;
-  });
+  if constexpr (FLIP) {
+    const FlipPass* const pd = ff.pd;
+    const BlockRT* const rta = ff.rta + (size_t)slot * ff.rt_stride;
+    const Decision* const da = ff.da + (size_t)slot * dfin_stride;
+    const int la = pd->la, mbits = da->m;
+    __shared__ double wt[kChainMax][16];
+    for (int i = threadIdx.x; i < 16 * la; i += blockDim.x) wt[i >> 4][i & 15] = rta[i >> 4].W[(mbits >> (i >> 4)) & 1][i & 15];
+    uint32_t fx = da->phix, fz = da->phi, ca = 0;  // members' frames (see k_flip)
+    for (int i = 0; i < la; ++i) {
+      uint32_t& f = ((pd->ax >> i) & 1) ? fx : fz;
+      ca |= gather_loc(f, pd->aq[i], pd->aw[i]) << (4 * i);
+      f ^= scatter_loc(rta[i].F, pd->aq[i], pd->aw[i]);
+    }
+    // packed local indices: those of the thread's first leaf, and of leaf bits
+    // above the thread's ten
+    auto packed = [&](uint32_t g) {
+      uint32_t x = 0;
+      for (int k = 0; k < la; ++k) x |= gather_loc(g, pd->aq[k], pd->aw[k]) << (4 * k);
+      return x;
+    };
+    const uint32_t x0 = ca ^ packed((uint32_t)cbase | threadIdx.x), xu[2] = {packed(1024u), packed(2048u)};
+    descend(cb, hb, [&](int i) {
+      const C2<T> a = ld2(st, (uint64_t)flip_place<T>((uint32_t)cbase + (uint32_t)i));
+      const double re = (double)a.re, im = (double)a.im;
+      const uint32_t x = x0 ^ (i & 1024 ? xu[0] : 0u) ^ (i & 2048 ? xu[1] : 0u);
+      double w = re * re + im * im;
+      for (int k = 0; k < la; ++k) w *= wt[k][(x >> (4 * k)) & 15u];
+      return w;
+    });
+  } else {
+    descend(cb, hb, [&](int i) {
+      const C2<T> a = ld2(st, cbase + (uint64_t)i);
+      const double re = (double)a.re, im = (double)a.im;
+      return re * re + im * im;
+    });
+  }
 }
 
 // Replayed trajectories: copy the staged records, p1 trace and final bits of

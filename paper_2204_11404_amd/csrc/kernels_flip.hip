@@ -25,7 +25,7 @@
 // (4.9-5.3 TB/s; 95 us without flips).  Above that rate lie the waits between
 // a tile's load, regroup and store.  A round: complex64 1.55 -> 0.63 ms,
 // complex128 2.4 -> 1.2 ms against the eight speculative passes and their
-// redos; 4096 d = 4 trajectories (complex64) 42.7 -> 19.9 ms.
+// redos; 4096 d = 4 trajectories (complex64) 42.7 -> 17.6 ms.
 //
 // Pauli frames: the XOR permutations are not carried out.  The stored
 // register is s Z^phix X^phiz |psi> written in the mixed basis; a Z member
@@ -94,13 +94,22 @@ template <typename T> struct FlipShape {
   static constexpr bool kAhead = sizeof(T) == 8;
 };
 
-template <typename T, int LB, bool INIT, bool L5>
+// kFlipPass: the steps above.  The first two passes of a trajectory know the
+// register without reading it: kFlipSums sums B over the initial code state
+// (nothing is stored), kFlipFirst applies A to that state as it forms it.
+// The last pass (LB = 0) only sums the final measurement's chunks unless the
+// register is wanted (keep): k_final_measure applies A to the chunk it reads.
+// d = 5: the two 155 -> 108 us in complex64 and 297 -> 171 in complex128, the
+// last one 96 -> 53 and 194 -> 142 (with k_final_measure 117 -> 88 and 217 -> 180).
+template <typename T, int LB, int MODE, bool L5>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T>::kWaves))) void k_flip(
     T* __restrict__ st, const FlipPass* __restrict__ pd, const BlockRT* __restrict__ rta,
     const BlockRT* __restrict__ rtb, const Decision* __restrict__ dec_a, Decision* __restrict__ dec_b,
-    double* __restrict__ partials, int reverse, int n_cls_wg, double* __restrict__ chunk_sums, SlotStrides ss) {
+    double* __restrict__ partials, int reverse, int n_cls_wg, double* __restrict__ chunk_sums, int keep,
+    SlotStrides ss) {
+  constexpr bool INIT = MODE == kFlipSums, FIRST = MODE == kFlipFirst;
   constexpr uint32_t kAmp = 2 * sizeof(T);
-  constexpr bool kAhead = FlipShape<T>::kAhead && !INIT;
+  constexpr bool kAhead = FlipShape<T>::kAhead && MODE == kFlipPass;
   const size_t slot = reverse ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
   st += slot * ss.st;
   if (rta) rta += slot * ss.rt;
@@ -124,6 +133,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T
   uint32_t phz = 0, phx = 0, ca = 0, cb = 0;
   int neg = 0, mbits = 0;
   double scale = pd->norm;
+  const T amp = (T)pd->amp;
   if constexpr (!INIT) {
     phz = dec_a->phi;
     phx = dec_a->phix;
@@ -238,8 +248,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T
 #pragma unroll
   for (int k = 0; k < kGroups; ++k) total[k] = 0.0;
 
-  // the initial state's linear conditions: parts of the thread and the slots
-  uint32_t syn_t = 0, rep_t = 0, syn_s[4] = {}, rep_s[4] = {};
+  // the initial state's linear conditions: parts of the thread and the slots;
+  // its sign, a quadratic form of the index, over the 16 slots as a bit mask:
+  // the slots' own part here, what a tile and a thread add to it is linear in
+  // the slot
+  uint32_t syn_t = 0, rep_t = 0, syn_s[4] = {}, rep_s[4] = {}, sign_s = 0;
+  int count[INIT ? 16 : 1];
+#pragma unroll
+  for (int j = 0; j < (INIT ? 16 : 1); ++j) count[j] = 0;
   auto lin = [&](uint32_t g, uint32_t& syn, uint32_t& rep) {
     uint32_t c = 0;
     for (int i = 0; i < pd->n_piv; ++i)
@@ -248,10 +264,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T
     rep = c & ~pd->zmask;
     for (int i = 0; i < pd->n_par; ++i) syn ^= (uint32_t)(__popc(g & pd->par_vec[i]) & 1) << pd->par_pos[i];
   };
-  if constexpr (INIT) {
+  if constexpr (INIT || FIRST) {
     lin(g1, syn_t, rep_t);
 #pragma unroll
     for (int b = 0; b < 4; ++b) lin(pd->s0[b], syn_s[b], rep_s[b]);
+    for (int j = 0; j < 16; ++j) sign_s |= (uint32_t)(__popc(at(pd->s0, j) & at(rep_s, j)) & 1) << j;
   }
 
   C2<T> nv[kAhead ? 16 : 1];
@@ -282,56 +299,73 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T
       locate(cls, step, nbase, nxa);
       if constexpr (kAhead) fetch(nv, nbase);
     }
-    if constexpr (INIT) {
-      // the initial code state in the mixed basis of this pass's output:
-      // amplitude g is +-amp where every linear condition holds; its sign is
-      // the parity of the transformed bits and of the code word that matches
-      // the untransformed ones
+    uint32_t on = 0;
+    if constexpr (INIT || FIRST) {
+      // the initial code state in the mixed basis it starts in: amplitude g is
+      // +-amp where every linear condition holds; its sign is the parity of
+      // the transformed bits and of the code word that matches the
+      // untransformed ones
       uint32_t syn_b, rep_b;
       lin(base, syn_b, rep_b);
       syn_b ^= syn_t;
       rep_b ^= rep_t;
-      const uint32_t gb = base | g1, w = out_place(base) ^ p2;
+      if constexpr (INIT) {
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const bool on = (syn_b ^ at(syn_s, j)) == 0;
-        const bool minus = __popc((gb | at(pd->s0, j)) & (rep_b ^ at(rep_s, j))) & 1;
-        v[j] = C2<T>{on ? (minus ? (T)-scale : (T)scale) : (T)0, (T)0};
-        reg.st(w ^ at(o2, j), 0, v[j]);
-      }
-    } else {
-      if constexpr (!kAhead) fetch(v, base);
-      // chain A: the tables that see the same index in all 16 slots as one
-      // factor, the others slot by slot
-      const uint32_t oa = pa ^ xa;
-      cd f{1.0, 0.0};
-#pragma unroll
-      for (int k = 0; k < kChainMax / 2; ++k)
-        if (2 * k < la && !((touch >> k) & 1)) f = cmul(f, pt[k][(oa >> (8 * k)) & 255]);
-      if (touch == 0) {
-        const T fr = (T)f.re, fi = (T)f.im;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) v[j] = mulc(v[j], fr, fi);
+        for (int j = 0; j < 16; ++j) count[j] += syn_b == at(syn_s, j) ? 1 : 0;
       } else {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const uint32_t oj = oa ^ at(pd->a_slot, j);
-          cd e = f;
+        for (int j = 0; j < 16; ++j) on |= syn_b == at(syn_s, j) ? 1u << j : 0u;
+        const uint32_t gb = base | g1;
+        const uint32_t lines[4] = {0xAAAAu, 0xCCCCu, 0xF0F0u, 0xFF00u};
+        uint32_t minus = sign_s ^ ((__popc(gb & rep_b) & 1) ? 0xFFFFu : 0u);
 #pragma unroll
-          for (int k = 0; k < kChainMax / 2; ++k)
-            if ((touch >> k) & 1) e = cmul(e, pt[k][(oj >> (8 * k)) & 255]);
-          v[j] = mulc(v[j], (T)e.re, (T)e.im);
+        for (int b = 0; b < 4; ++b)
+          if ((__popc(gb & rep_s[b]) ^ __popc(pd->s0[b] & rep_b)) & 1) minus ^= lines[b];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          const T a = (on >> j) & 1 ? amp : (T)0;
+          v[j] = C2<T>{(minus >> j) & 1 ? -a : a, (T)0};
         }
       }
-      flip_slots(v, m0);
-      if (low & 1) flip_lane<0>(v, tid);
-      if (low & 2) flip_lane<1>(v, tid);
-      if (low & 4) flip_lane<2>(v, tid);
-      if constexpr (L5) {
-        // e, on lane bit 5, changes places with slot bit 3
+    } else if constexpr (!kAhead) {
+      fetch(v, base);
+    }
+    // (FIRST: a wave without an amplitude stays zero until the regroup)
+    const bool some = !FIRST || __ballot(on != 0) != 0;
+    if constexpr (!INIT) {
+      if (some) {
+        // chain A: the tables that see the same index in all 16 slots as one
+        // factor, the others slot by slot
+        const uint32_t oa = pa ^ xa;
+        cd f{1.0, 0.0};
 #pragma unroll
-        for (int j = 0; j < 8; ++j) swap_c2<T, true>(v[j], v[j + 8]);
-        wht_reg_stage<8>(v);
+        for (int k = 0; k < kChainMax / 2; ++k)
+          if (2 * k < la && !((touch >> k) & 1)) f = cmul(f, pt[k][(oa >> (8 * k)) & 255]);
+        if (touch == 0) {
+          const T fr = (T)f.re, fi = (T)f.im;
+#pragma unroll
+          for (int j = 0; j < 16; ++j) v[j] = FIRST ? C2<T>{v[j].re * fr, v[j].re * fi} : mulc(v[j], fr, fi);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const uint32_t oj = oa ^ at(pd->a_slot, j);
+            cd e = f;
+#pragma unroll
+            for (int k = 0; k < kChainMax / 2; ++k)
+              if ((touch >> k) & 1) e = cmul(e, pt[k][(oj >> (8 * k)) & 255]);
+            v[j] = FIRST ? C2<T>{v[j].re * (T)e.re, v[j].re * (T)e.im} : mulc(v[j], (T)e.re, (T)e.im);
+          }
+        }
+        flip_slots(v, m0);
+        if (low & 1) flip_lane<0>(v, tid);
+        if (low & 2) flip_lane<1>(v, tid);
+        if (low & 4) flip_lane<2>(v, tid);
+        if constexpr (L5) {
+          // e, on lane bit 5, changes places with slot bit 3
+#pragma unroll
+          for (int j = 0; j < 8; ++j) swap_c2<T, true>(v[j], v[j + 8]);
+          wht_reg_stage<8>(v);
+        }
       }
       if (two) {
         E* const bw = buf + lw;
@@ -359,17 +393,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T
         }
         flip_slots(v, m2);
       }
-      const uint32_t w = out_place(base) ^ p2;
+      if (LB > 0 || keep) {
+        const uint32_t w = out_place(base) ^ p2;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) reg.st(w ^ at(o2, j), 0, v[j]);
+        for (int j = 0; j < 16; ++j) reg.st(w ^ at(o2, j), 0, v[j]);
+      }
     }
     if constexpr (LB > 0) {
+      if constexpr (!INIT) {
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const double re = (double)v[j].re, im = (double)v[j].im;
-        acc[j] = fma(re, re, fma(im, im, acc[j]));
+        for (int j = 0; j < 16; ++j) {
+          const double re = (double)v[j].re, im = (double)v[j].im;
+          acc[j] = fma(re, re, fma(im, im, acc[j]));
+        }
       }
       if (!more || cls != cls_now) {
+        if constexpr (INIT) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            acc[j] = (double)count[j] * ((double)amp * (double)amp);
+            count[j] = 0;
+          }
+        }
         // the class's norms against B's weights: the two members that slot
         // bits belong to take those bits in (16 norms -> four, one per pair
         // of their outcomes), the other members' weights are the thread's own

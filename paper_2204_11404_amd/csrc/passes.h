@@ -24,7 +24,7 @@ int launch_spass(const UnitPass& h, bool redo, dim3 g, dim3 b, hipStream_t s, T*
                  Decision* db, double* part, int rev, SpecArgs sa, SlotStrides ss);
 
 template <typename T>
-int launch_flip(const FlipPass& h, bool init, dim3 g, hipStream_t s, T* st, const FlipPass* pd,
+int launch_flip(const FlipPass& h, int mode, bool keep, dim3 g, hipStream_t s, T* st, const FlipPass* pd,
                  const BlockRT* rta, const BlockRT* rtb, const Decision* da, Decision* db, double* part, int rev,
                  int n_cls_wg, double* chunk_sums, SlotStrides ss);
 

@@ -111,17 +111,19 @@ int launch_spass(const UnitPass& h, bool redo, dim3 g, dim3 b, hipStream_t s, T*
 
 #if !defined(QEC_PART) || QEC_PART == 2
 template <typename T>
-int launch_flip(const FlipPass& h, bool init, dim3 g, hipStream_t s, T* st, const FlipPass* pd,
+int launch_flip(const FlipPass& h, int mode, bool keep, dim3 g, hipStream_t s, T* st, const FlipPass* pd,
                  const BlockRT* rta, const BlockRT* rtb, const Decision* da, Decision* db, double* part, int rev,
                  int n_cls_wg, double* chunk_sums, SlotStrides ss) {
-#define QEC_FL(LBV, INITV, L5V)                                                                                   \
-  if (h.lb == LBV && init == INITV && (h.lane5 != 0) == L5V) {                                                    \
-    hipLaunchKernelGGL((k_flip<T, LBV, INITV, L5V>), g, dim3(256), 0, s, st, pd, rta, rtb, da, db, part, rev, \
-                       n_cls_wg, chunk_sums, ss);                                                                 \
+#define QEC_FL(LBV, MODEV, L5V)                                                                                   \
+  if (h.lb == LBV && mode == MODEV && (h.lane5 != 0) == L5V) {                                                    \
+    hipLaunchKernelGGL((k_flip<T, LBV, MODEV, L5V>), g, dim3(256), 0, s, st, pd, rta, rtb, da, db, part, rev, \
+                       n_cls_wg, chunk_sums, keep ? 1 : 0, ss);                                                   \
     return 0;                                                                                                     \
   }
-#define QEC_FL_B(LBV) QEC_FL(LBV, false, false) QEC_FL(LBV, false, true) QEC_FL(LBV, true, false)
-  QEC_FL(0, false, false) QEC_FL_B(1) QEC_FL_B(2) QEC_FL_B(3) QEC_FL_B(4) QEC_FL_B(5) QEC_FL_B(6)
+#define QEC_FL_B(LBV)                                                                                        \
+  QEC_FL(LBV, kFlipPass, false) QEC_FL(LBV, kFlipPass, true) QEC_FL(LBV, kFlipSums, false)                   \
+  QEC_FL(LBV, kFlipFirst, false) QEC_FL(LBV, kFlipFirst, true)
+  QEC_FL(0, kFlipPass, false) QEC_FL_B(1) QEC_FL_B(2) QEC_FL_B(3) QEC_FL_B(4) QEC_FL_B(5) QEC_FL_B(6)
 #undef QEC_FL_B
 #undef QEC_FL
   return kLaunchNoKernel;
@@ -142,7 +144,7 @@ int launch_flip(const FlipPass& h, bool init, dim3 g, hipStream_t s, T* st, cons
 #endif
 #if !defined(QEC_PART) || QEC_PART == 2
 #define QEC_INSTANCE_2(QEC_TT) \
-  template int launch_flip<QEC_TT>(const FlipPass& h, bool init, dim3 g, hipStream_t s, QEC_TT* st, const FlipPass* pd, const BlockRT* rta, const BlockRT* rtb, const Decision* da, Decision* db, double* part, int rev, int n_cls_wg, double* chunk_sums, SlotStrides ss);
+  template int launch_flip<QEC_TT>(const FlipPass& h, int mode, bool keep, dim3 g, hipStream_t s, QEC_TT* st, const FlipPass* pd, const BlockRT* rta, const BlockRT* rtb, const Decision* da, Decision* db, double* part, int rev, int n_cls_wg, double* chunk_sums, SlotStrides ss);
 #else
 #define QEC_INSTANCE_2(QEC_TT)
 #endif

@@ -676,6 +676,7 @@ struct UnitPass {
 // Slot bits 0, 1 of the layout of the store carry qubits of B's member mp
 // alone (or none), slot bits 2, 3 of member mq alone; ord lists B's members
 // with mp and mq last.
+enum FlipMode { kFlipPass, kFlipSums, kFlipFirst };  // see k_flip
 struct FlipPass {
   int n_outer;
   int la, lb;
@@ -686,7 +687,8 @@ struct FlipPass {
   int two;
   int plain;           // the store writes amplitude g at place g (the last pass of a trajectory)
   int n_brel;          // leading outer bits that carry qubits of B
-  double norm;         // 2^(-flips / 2); the initial state's pass: its amplitude
+  double norm;         // 2^(-flips / 2)
+  double amp;          // amplitude of the initial state
   uint32_t outer_bit[20];
   uint32_t s0[4], s2[4], e;
   uint32_t a_tid[8], a_slot[4], a_outer[20];  // packed local indices of A (layout 1)
@@ -694,8 +696,9 @@ struct FlipPass {
   uint32_t aq[kChainMax][4], bq[kChainMax][4];
   int aw[kChainMax], bw[kChainMax];
   int ord[kChainMax];
-  // the initial state's pass: code words with a pivot among the
-  // untransformed bits (zmask), and parity conditions on the transformed ones
+  // the initial state (its pass and the first that applies a unit): code
+  // words with a pivot among the untransformed bits (zmask), and parity
+  // conditions on the transformed ones
   int n_piv, n_par;
   uint32_t zmask;
   uint32_t piv_bit[16], piv_vec[16], par_vec[16];

@@ -1440,7 +1440,7 @@ void flip_init_state(const Template& tp, int d, bool plus, uint32_t T, FlipPass&
     pd.par_vec[i] = tv[i];
     pd.par_pos[i] = __builtin_ctz(tpv[i]);
   }
-  pd.norm = std::pow(2.0, pd.n_par - 0.5 * (pd.n_piv + pd.n_par) - 0.5 * __builtin_popcount(T));
+  pd.amp = std::pow(2.0, pd.n_par - 0.5 * (pd.n_piv + pd.n_par) - 0.5 * __builtin_popcount(T));
 }
 
 FlipPlan make_flip_plan(int d, const Template& tp, bool plus) {
@@ -1455,6 +1455,7 @@ FlipPlan make_flip_plan(int d, const Template& tp, bool plus) {
     const int v = (u + 1) % nu;
     P.passes[1 + u] = make_flip_pass(n, tp, &P.units[u], &P.units[v], P.flips[v]);
   }
+  flip_init_state(tp, d, plus, P.flips[0], P.passes[1]);
   P.passes[nu + 1] = make_flip_pass(n, tp, &P.units[nu - 1], nullptr, 0u);
   for (const FlipPass& h : P.passes)
     if (h.lb < 0) return FlipPlan{};
@@ -1687,6 +1688,8 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   // passes with a basis change: as many workgroups as run at once (two per CU
   // in complex128, three in complex64; see FlipShape)
   const unsigned flip_wgs = (unsigned)device_cu_count() * (sizeof(T) == 8 ? 2u : 3u);
+  // the register after the last pass is wanted (else that pass only sums)
+  const bool keep = xbasis || res->final_states;
   const SlotStrides ss0{(size_t)2 * na, (size_t)per_traj, (size_t)n_dec};
   const int draws_round = tp.n_draws;
   const int last_t = job->n_traj - 1;
@@ -1709,7 +1712,8 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
         const FlipPass& h = fplan.passes[pidx];
         const FlipGrid fg = flip_grid(h, flip_wgs);
         *parts = fg.wgs;
-        return pass_status(launch_flip<T>(h, ui < 0, dim3(fg.wgs), q, st, &dfpass[pidx], ra, rb, da, &ddec[ui + 1],
+        const int mode = ui < 0 ? kFlipSums : ui == 0 ? kFlipFirst : kFlipPass;
+        return pass_status(launch_flip<T>(h, mode, keep, dim3(fg.wgs), q, st, &dfpass[pidx], ra, rb, da, &ddec[ui + 1],
                                           partials, rev, (int)fg.n_cls_wg, last && !xbasis ? dsums : nullptr, ss0));
       }
       *parts = grid.x;
@@ -1791,16 +1795,24 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   // in the X basis a Walsh-Hadamard transform of the whole register first,
   // which removes the Pauli-X frame from the outcome probabilities (the
   // outcome probabilities are ratios: a pending renormalisation is harmless)
-  auto traj_final = [&](hipStream_t q, int cnt, T* buf, uint8_t* bits, uint64_t t, const uint64_t* tptr) {
+  auto traj_final = [&](hipStream_t q, int cnt, T* buf, const BlockRT* rt, uint8_t* bits, uint64_t t,
+                        const uint64_t* tptr) {
+    if (flip && !keep) {
+      hipLaunchKernelGGL((k_final_measure<T, true>), dim3(cnt), dim3(1024), 0, q, buf, n, cb, dsums, job->seed, t,
+                         (uint64_t)R * (uint64_t)draws_round, bits, ss0.st, (const uint64_t*)nullptr, tptr,
+                         (const int*)nullptr, (uint64_t)0, (const Decision*)&ddec[fin], ss0.dec, 0,
+                         FlipFinal{&dfpass[nu + 1], rt + inst(per_units - 1), &ddec[per_units - 1], ss0.rt});
+      return;
+    }
     if (xbasis) launch_wht_all<T>(q, buf, n, cnt);
     // (the last pass with a basis change has left the sums)
     if (!flip || xbasis)
       hipLaunchKernelGGL(k_final_sums<T>, dim3(1u << (n - cb), cnt), dim3(256), 0, q, buf, cb, dsums, ss0.st);
-    hipLaunchKernelGGL(k_final_measure<T>, dim3(cnt), dim3(1024), 0, q, buf, n, cb, dsums, job->seed, t,
+    hipLaunchKernelGGL((k_final_measure<T, false>), dim3(cnt), dim3(1024), 0, q, buf, n, cb, dsums, job->seed, t,
                        (uint64_t)R * (uint64_t)draws_round, bits, ss0.st, (const uint64_t*)nullptr,
                        tptr, (const int*)nullptr, (uint64_t)0,
                        xbasis && !flip ? (const Decision*)nullptr : (const Decision*)&ddec[fin],
-                       ss0.dec, xbasis ? 1 : 0);
+                       ss0.dec, xbasis ? 1 : 0, FlipFinal{});
   };
   double pass_ms_graph = -1.0;
   int last_cnt = 1;  // trajectories of the last group (small registers)
@@ -1852,7 +1864,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
       cst = spec ? traj_spec(G.q, 1, rt_s, rec_s, p1_s, false, &fbuf)
                  : traj_passes(G.q, 1, rt_s, dn_s, rec_s, p1_s, false);
       if (cst == SV_OK) {
-        traj_final(G.q, 1, fbuf, bits_s, 0, dcur + 1);
+        traj_final(G.q, 1, fbuf, rt_s, bits_s, 0, dcur + 1);
         hipLaunchKernelGGL(k_commit, dim3(1), dim3(256), 0, G.q, rec_s, p1_s, bits_s, drec, dp1, dbits,
                            per_traj, n, dcur, dcur + 1, job->traj0);
       }
@@ -1922,7 +1934,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                                   sizeof(Decision), cnt, hipMemcpyDeviceToHost, s));
           HIP_OK(hipStreamSynchronize(s));
         }
-        traj_final(s, cnt, buf, dbits + (size_t)tg * n, job->traj0 + (uint64_t)tg, nullptr);
+        traj_final(s, cnt, buf, drt + (size_t)ti * per_traj, dbits + (size_t)tg * n, job->traj0 + (uint64_t)tg, nullptr);
         HIP_OK(hipGetLastError());
       }
     }
@@ -2494,14 +2506,22 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
     const int R0 = hrounds[0];
     // final Z measurement of the slots [from, from + cnt) on register buffer
     // buf, their frames in the decision records at dfin
-    auto measure = [&](const T* buf, int from, int cnt, const Decision* dfin) {
-      // (the last pass with a basis change has left the sums)
-      if (!flip)
-        hipLaunchKernelGGL(k_final_sums<T>, dim3(1u << (n - cb), cnt), dim3(256), 0, s, buf + (size_t)from * reg, cb,
+    // (rt, da: tables and decision of the last unit, which a pass with a basis
+    // change has summed but not applied)
+    auto measure = [&](const T* buf, int from, int cnt, const Decision* dfin, const BlockRT* rt = nullptr,
+                       const Decision* da = nullptr) {
+      if (flip) {
+        hipLaunchKernelGGL((k_final_measure<T, true>), dim3(cnt), dim3(1024), 0, s, buf + (size_t)from * reg, n, cb,
+                           dsums, (uint64_t)0, (uint64_t)0, (uint64_t)0, dbits + (size_t)from * n, reg, dseed + from,
+                           dstream + from, drounds + from, (uint64_t)tp.n_draws, dfin, dec_stride, 0,
+                           FlipFinal{&dfpass[nu + 1], rt, da, (size_t)ns});
+        return;
+      }
+      hipLaunchKernelGGL(k_final_sums<T>, dim3(1u << (n - cb), cnt), dim3(256), 0, s, buf + (size_t)from * reg, cb,
                            dsums, reg);
-      hipLaunchKernelGGL(k_final_measure<T>, dim3(cnt), dim3(1024), 0, s, buf + (size_t)from * reg, n, cb, dsums,
+      hipLaunchKernelGGL((k_final_measure<T, false>), dim3(cnt), dim3(1024), 0, s, buf + (size_t)from * reg, n, cb, dsums,
                          (uint64_t)0, (uint64_t)0, (uint64_t)0, dbits + (size_t)from * n, reg, dseed + from,
-                         dstream + from, drounds + from, (uint64_t)tp.n_draws, dfin, dec_stride, 0);
+                         dstream + from, drounds + from, (uint64_t)tp.n_draws, dfin, dec_stride, 0, FlipFinal{});
     };
     if (spec) {
       // speculative units: logical |0> into st, then per unit of every round
@@ -2560,12 +2580,12 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
     // pass pidx over cnt slots from `from` on (register, tables and decisions
     // of the first of them given); workgroups per slot in *gx
     auto pass = [&](int pidx, int cnt, T* reg0, const BlockRT* ra, const BlockRT* rb, const Decision* da, Decision* db,
-                    int rev, unsigned* gx) -> sv_status {
+                    int rev, unsigned* gx, int mode = kFlipPass) -> sv_status {
       if (flip) {
         const FlipPass& h = fplan.passes[pidx];
         const FlipGrid fg = flip_grid(h, std::max(4u, flip_wgs / (unsigned)cnt));
         *gx = fg.wgs;
-        return pass_status(launch_flip<T>(h, pidx == 0, dim3(fg.wgs, cnt), s, reg0, &dfpass[pidx], ra, rb, da, db,
+        return pass_status(launch_flip<T>(h, mode, false, dim3(fg.wgs, cnt), s, reg0, &dfpass[pidx], ra, rb, da, db,
                                           partials, rev, (int)fg.n_cls_wg, rb ? nullptr : dsums, ss));
       }
       *gx = gx_of(pds[pidx]);
@@ -2573,7 +2593,7 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
                              rev, ss));
     };
     unsigned gx = 0;
-    SV_OK_OR_RETURN(pass(0, gn, st, nullptr, rtA + units[0].first, nullptr, ddec, 0, &gx));
+    SV_OK_OR_RETURN(pass(0, gn, st, nullptr, rtA + units[0].first, nullptr, ddec, 0, &gx, kFlipSums));
     decide(gn, rtA, 0, 0, gx);
     for (int r = 0; r < R0; ++r) {
       const int Ar = active(r), An = active(r + 1);
@@ -2585,7 +2605,8 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
         const int rev = (++pass_no) & 1;
         const BlockRT* rta = rt_cur + units[u].first;
         if (u < nu - 1) {
-          SV_OK_OR_RETURN(pass(1 + u, Ar, st, rta, rt_cur + units[u + 1].first, ddec + ui, ddec + ui + 1, rev, &gx));
+          SV_OK_OR_RETURN(pass(1 + u, Ar, st, rta, rt_cur + units[u + 1].first, ddec + ui, ddec + ui + 1, rev, &gx,
+                               ui == 0 ? kFlipFirst : kFlipPass));
           decide(Ar, rt_cur, r, u + 1, gx);
           continue;
         }
@@ -2598,7 +2619,7 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
           Decision* dfin = ddec + (size_t)An * dec_stride + ui + 1;
           SV_OK_OR_RETURN(pass(nu + 1, cnt, st + (size_t)An * reg, rta + (size_t)An * ns, nullptr,
                                ddec + (size_t)An * dec_stride + ui, dfin, rev, &gx));
-          measure(st, An, cnt, dfin);
+          measure(st, An, cnt, dfin, rta + (size_t)An * ns, ddec + (size_t)An * dec_stride + ui);
         }
       }
       HIP_OK(hipGetLastError());

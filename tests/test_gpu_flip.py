@@ -79,3 +79,28 @@ def test_flip_matches_plain_passes_batch_d4(monkeypatch, dtype, mib):
     R, p, eps = workloads.batch_params(70, n_sites, 75, p=(1e-3, 3e-2), theta=(0.0, 0.1))
     a, b = _both(monkeypatch, lambda: qs.run_batch(4, "cr", R, p, 75, eps_site=eps, dtype=dtype, max_rounds=9))
     assert a["passes_per_round"] == 3
+
+
+# First and last passes of a trajectory: the first two form the initial state
+# instead of reading it (one round: they are two of the five passes; the X
+# basis starts from another state), the last one only sums unless the register
+# is wanted.
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("rounds", [1, 2])
+@pytest.mark.parametrize("xbasis", [False, True])
+def test_first_and_last_pass(monkeypatch, rounds, xbasis, dtype):
+    n_sites = qs.template_info(5, "cr")[1]
+    eps = np.random.default_rng(17).normal(0.0, 0.05, n_sites)
+    kw = dict(d=5, gateset="cr", rounds=rounds, n_traj=2, seed=31, p=0.02, eps_site=eps, dtype=dtype, traj0=3,
+              want_p1=True, xbasis=xbasis)
+    monkeypatch.setenv("QECSV_SPEC", "0")
+    want = qs.run_rounds(**kw)
+    monkeypatch.delenv("QECSV_SPEC")
+    got = qs.run_rounds(**kw)
+    kept = qs.run_rounds(want_states=True, **kw)
+    # 24 checks a round, some fifty roundings an amplitude each
+    tol = 24 * rounds * 50 * (2.0**-53 if dtype == "c128" else 2.0**-24)
+    for g in (got, kept):
+        assert np.array_equal(g["records"], want["records"])
+        assert np.array_equal(g["final_bits"], want["final_bits"])
+        assert np.abs(g["p1"] - want["p1"]).max() <= tol
