@@ -655,6 +655,14 @@ sv_tuning tuning_for(int d, int dtype) {
   return t;
 }
 
+// Whether chain length and pass workgroups of (d, dtype) were set, tuned or
+// given in the environment.
+bool passes_tuned(int d, int dtype) {
+  if (std::getenv("QECSV_ZCHAIN") || std::getenv("QECSV_PASS_WGS_PER_CU")) return true;
+  std::lock_guard<std::mutex> lk(g_tune_mu);
+  return g_tune.count(TuneKey{current_device(), d, dtype}) != 0;
+}
+
 // Units of one round: every X check alone, runs of consecutive Z checks cut
 // into chains of at most max_chain members.
 std::vector<Unit> make_units(const Template& tp, int max_chain) {
@@ -1524,8 +1532,18 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   const int d = job->d, n = d * d, ns = (int)tp.blocks.size(), R = job->rounds;
   const int tb = std::min(kTileMax, n);
   const int per_traj = R * ns;  // block instances (records) per trajectory
-  const sv_tuning tune = tuning_for(d, job->dtype);
+  sv_tuning tune = tuning_for(d, job->dtype);
   const int spec_env = env_int("QECSV_SPEC", -1);
+  // A d = 5 register nobody tuned: two chains of six Z checks instead of three
+  // of four (14 passes a round), and 16 workgroups a CU, complex64 four, each
+  // taking tiles grid-stride.  Five rounds with the data ZZ layer: complex128
+  // 15.43 ms (three chains, a workgroup a tile), 14.69 (two), 14.50 (and 16 a
+  // CU); complex64 9.11, 8.85, 7.91 (four a CU; 8.05 with 3, 7.99 with 8, 8.18
+  // with 16).  Smaller registers have too few tiles; dense checks not measured.
+  if (n > 16 && !tp.any_dense && !passes_tuned(d, job->dtype) && !(spec_env > 0)) {
+    tune.zchain = kChainMax;
+    tune.pass_wgs_per_cu = sizeof(T) == 8 ? 16 : 4;
+  }
   const bool xbasis = (job->flags & SV_RUN_XBASIS) != 0;
   FlipPlan fplan;
   if (spec_env < 0 && job->zeta == 0.0 && n > 16 && !tp.any_dense) fplan = make_flip_plan(d, tp, xbasis);
