@@ -2762,7 +2762,10 @@ struct sv_state_s {
   hipEvent_t mat_ev[8] = {};
   bool mat_used[8] = {};
   int mat_next = 0;
+  int back = 0;  // direction of the last pass over the register (walk_thread)
 };
+// Direction of the next pass over s's register.
+static int next_walk(sv_state s) { return s->back ^= 1; }
 
 static constexpr int kMeasGrid = 1024;
 static constexpr int kMatSlots = 8;
@@ -2940,10 +2943,10 @@ sv_status sv_apply_gate(sv_state s, int k, const int* qubits, const double* m) {
     const uint64_t np = na >> 1;
     if (s->dt == SV_C128)
       hipLaunchKernelGGL(k_gate1<double>, dim3(grid_for(np, 256)), dim3(256), 0, s->stream,
-                         (double*)s->ptr, np, qubits[0], M);
+                         (double*)s->ptr, np, qubits[0], M, next_walk(s));
     else
       hipLaunchKernelGGL(k_gate1<float>, dim3(grid_for(np, 256)), dim3(256), 0, s->stream,
-                         (float*)s->ptr, np, qubits[0], M);
+                         (float*)s->ptr, np, qubits[0], M, next_walk(s));
   } else if (qubits[0] + qubits[1] == 1 && s->n >= 9) {
     // qubits 0 and 1: one amplitude per thread, quadruples exchanged within
     // DPP quads (whole 256-thread blocks)
@@ -2952,20 +2955,20 @@ sv_status sv_apply_gate(sv_state s, int k, const int* qubits, const double* m) {
     const dim3 g((unsigned)(na / 256)), b(256);
     const int swap = qubits[0] == 1;
     if (s->dt == SV_C128)
-      hipLaunchKernelGGL(k_gate2_quad<double>, g, b, 0, s->stream, (double*)s->ptr, swap, M);
+      hipLaunchKernelGGL(k_gate2_quad<double>, g, b, 0, s->stream, (double*)s->ptr, swap, M, next_walk(s));
     else  // two amplitudes per thread: half the threads
       hipLaunchKernelGGL(k_gate2_pair_f32, dim3((unsigned)(na / 512)), b, 0, s->stream, (float*)s->ptr,
-                         swap, M);
+                         swap, M, next_walk(s));
   } else {
     Mat4 M;
     std::memcpy(M.m, m, sizeof M.m);
     const uint64_t nq = na >> 2;
     if (s->dt == SV_C128)
       hipLaunchKernelGGL(k_gate2<double>, dim3(grid_for(nq, 256)), dim3(256), 0, s->stream,
-                         (double*)s->ptr, nq, qubits[0], qubits[1], M);
+                         (double*)s->ptr, nq, qubits[0], qubits[1], M, next_walk(s));
     else
       hipLaunchKernelGGL(k_gate2<float>, dim3(grid_for(nq, 256)), dim3(256), 0, s->stream,
-                         (float*)s->ptr, nq, qubits[0], qubits[1], M);
+                         (float*)s->ptr, nq, qubits[0], qubits[1], M, next_walk(s));
   }
   HIP_OK(hipGetLastError());
   return SV_OK;
@@ -2982,10 +2985,10 @@ sv_status sv_apply_diag(sv_state s, int k, const int* qubits, const double* phas
   const uint64_t na = 1ull << s->n;
   if (s->dt == SV_C128)
     hipLaunchKernelGGL(k_diag<double>, dim3(grid_for(na, 256)), dim3(256), 0, s->stream,
-                       (double*)s->ptr, na, k, q[0], q[1], q[2], q[3], q[4], D);
+                       (double*)s->ptr, na, k, q[0], q[1], q[2], q[3], q[4], D, next_walk(s));
   else
     hipLaunchKernelGGL(k_diag<float>, dim3(grid_for(na, 256)), dim3(256), 0, s->stream,
-                       (float*)s->ptr, na, k, q[0], q[1], q[2], q[3], q[4], D);
+                       (float*)s->ptr, na, k, q[0], q[1], q[2], q[3], q[4], D, next_walk(s));
   HIP_OK(hipGetLastError());
   return SV_OK;
 }
@@ -3072,28 +3075,29 @@ sv_status sv_apply_fused(sv_state s, int k, const int* qubits, const double* m) 
   bool low = mfma && s->dt == SV_C64;
   for (int i = 0; i < k; ++i) low = low && q[i] < k;
   const dim3 g(grid_for(ng, 256)), b(256);
+  const int back = next_walk(s);
 #define QEC_FUSED(K)                                                                             \
   case K:                                                                                       \
     if (s->dt == SV_C128)                                                                       \
       hipLaunchKernelGGL((k_fused<double, K>), g, b, 0, s->stream, (double*)s->ptr, ng, dm, q[0], \
-                         q[1], q[2], q[3], q[4]);                                               \
+                         q[1], q[2], q[3], q[4], back);                                               \
     else                                                                                        \
       hipLaunchKernelGGL((k_fused<float, K>), g, b, 0, s->stream, (float*)s->ptr, ng, dm, q[0],   \
-                         q[1], q[2], q[3], q[4]);                                               \
+                         q[1], q[2], q[3], q[4], back);                                               \
     break;
 #define QEC_FUSED_MFMA(K)                                                                        \
   case K:                                                                                       \
     if (low)                                                                                    \
       hipLaunchKernelGGL((k_fused_mfma_low<float, K>), dim3(fused_mfma_grid<float, K, true>(ng / 16)), \
-                         b, 0, s->stream, (float*)s->ptr, ng / 16, dm, q[0], q[1], q[2], q[3], q[4]); \
+                         b, 0, s->stream, (float*)s->ptr, ng / 16, dm, q[0], q[1], q[2], q[3], q[4], back); \
     else if (s->dt == SV_C128)                                                                  \
       hipLaunchKernelGGL((k_fused_mfma<double, K, FusedPF<double, K>::value>),                  \
                          dim3(fused_mfma_grid<double, K, false>(ng / 16)), b, 0, s->stream,       \
-                         (double*)s->ptr, ng / 16, dm, q[0], q[1], q[2], q[3], q[4]);            \
+                         (double*)s->ptr, ng / 16, dm, q[0], q[1], q[2], q[3], q[4], back);            \
     else                                                                                        \
       hipLaunchKernelGGL((k_fused_mfma<float, K, FusedPF<float, K>::value>),                    \
                          dim3(fused_mfma_grid<float, K, false>(ng / 16)), b, 0, s->stream,        \
-                         (float*)s->ptr, ng / 16, dm, q[0], q[1], q[2], q[3], q[4]);             \
+                         (float*)s->ptr, ng / 16, dm, q[0], q[1], q[2], q[3], q[4], back);             \
     break;
   if (mfma) {
     switch (k) { QEC_FUSED_MFMA(4) QEC_FUSED_MFMA(5) }
@@ -3129,6 +3133,7 @@ static sv_status measure_common(sv_state s, int anc, double u, int forced, int* 
   else
     hipLaunchKernelGGL(k_measure_sums<float>, dim3(grid), dim3(256), 0, s->stream,
                        (const float*)s->ptr, na, anc, s->partials);
+  s->back = 0;  // (the sums run forwards: their order is fixed)
   hipLaunchKernelGGL(k_measure_decide, dim3(1), dim3(256), 0, s->stream, s->partials, (int)grid, u,
                      forced, s->mo);
   HIP_OK(hipGetLastError());
@@ -3143,10 +3148,10 @@ static sv_status measure_common(sv_state s, int anc, double u, int forced, int* 
   const uint64_t np = na >> 1;
   if (s->dt == SV_C128)
     hipLaunchKernelGGL(k_project<double>, dim3(grid_for(np, 256)), dim3(256), 0, s->stream,
-                       (double*)s->ptr, np, anc, s->mo);
+                       (double*)s->ptr, np, anc, s->mo, next_walk(s));
   else
     hipLaunchKernelGGL(k_project<float>, dim3(grid_for(np, 256)), dim3(256), 0, s->stream,
-                       (float*)s->ptr, np, anc, s->mo);
+                       (float*)s->ptr, np, anc, s->mo, next_walk(s));
   HIP_OK(hipGetLastError());
   MeasOut mo;
   HIP_OK(hipMemcpyAsync(&mo, s->mo, sizeof mo, hipMemcpyDeviceToHost, s->stream));
