@@ -331,6 +331,116 @@ __global__ __launch_bounds__(256) void k_fused_mfma(T* __restrict__ st, uint64_t
   }
 }
 
+// The same product for complex64 registers whose bit 0 is no target: a lane
+// moves two neighbouring amplitudes at a time, the same element of two groups
+// (16-byte accesses, runs of 256 bytes instead of 128), and a wave owns 32
+// groups, two B tiles against one copy of the matrix.  Bound by HBM in pieces
+// of 256 bytes (26 qubits, k = 5: 257 -> 232-240 us, 4.6 TB/s; the products
+// alone take some 110 us; two, three or four waves a SIMD, with the next
+// tile's loads ahead or without, are within 3 %).
+template <int K>
+__global__ __launch_bounds__(256) void k_fused_mfma_wide(float* __restrict__ st, uint64_t n_tiles,
+                                                         const double* __restrict__ mat, int q0, int q1,
+                                                         int q2, int q3, int q4, int back) {
+  static_assert(K == 4 || K == 5, "MFMA tiles need 16 or 32 rows");
+  constexpr int N = 1 << K, RT = N / 16, KS = N / 4;
+  using M16 = Mfma16<float>;
+  using V4 = M16::V4;
+  const int lane = threadIdx.x & 63, c = lane & 15, q = lane >> 4;
+  const int qs[5] = {q0, q1, q2, q3, q4};
+  int sorted[5];
+#pragma unroll
+  for (int j = 0; j < K; ++j) sorted[j] = qs[j];
+#pragma unroll
+  for (int a = 1; a < K; ++a)
+#pragma unroll
+    for (int b = a; b > 0; --b)
+      if (sorted[b - 1] > sorted[b]) {
+        const int t = sorted[b]; sorted[b] = sorted[b - 1]; sorted[b - 1] = t;
+      }
+  const uint64_t xq = ((q & 1) ? 1ull << q0 : 0) | ((q & 2) ? 1ull << q1 : 0);
+  uint64_t xh[KS];  // (uniform: bits 2.. of the local element)
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    uint64_t o = 0;
+#pragma unroll
+    for (int j = 2; j < K; ++j)
+      if ((s >> (j - 2)) & 1) o |= 1ull << qs[j];
+    xh[s] = o;
+  }
+  float ar[RT][KS], ai[RT][KS];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int row = 16 * t + (M16::kPermuteRows ? 4 * (c & 3) + (c >> 2) : c);
+      const int col = 4 * s + q;
+      ar[t][s] = (float)mat[2 * (N * row + col)];
+      ai[t][s] = (float)mat[2 * (N * row + col) + 1];
+    }
+  const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const uint64_t n_waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
+  auto tile = [&](uint64_t tl) {  // in pairs of amplitudes
+    uint64_t b = (back ? n_tiles - 1 - tl : tl) * 32 + 2 * c;
+#pragma unroll
+    for (int j = 0; j < K; ++j) b = insert_zero(b, sorted[j]);
+    return reinterpret_cast<float4*>(st) + ((b | xq) >> 1);
+  };
+  // the next tile's loads are issued before this tile's products
+  float4 nv[KS];
+  float4* at = nullptr;
+  uint64_t tl = wave;
+  if (tl < n_tiles) {
+    at = tile(tl);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) nv[s] = at[xh[s] >> 1];
+  }
+  while (tl < n_tiles) {
+    float4 v[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) v[s] = nv[s];
+    float4* const out = at;
+    tl += n_waves;
+    if (tl < n_tiles) {
+      at = tile(tl);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) nv[s] = at[xh[s] >> 1];
+    }
+    V4 yr[2][RT], yi[2][RT];
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        yr[g][t] = V4{0, 0, 0, 0};
+        yi[g][t] = V4{0, 0, 0, 0};
+      }
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const float re[2] = {v[s].x, v[s].z}, im[2] = {v[s].y, v[s].w};
+      // (independent products between two on the same accumulator)
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          yr[g][t] = M16::op(ar[t][s], re[g], yr[g][t]);
+          yi[g][t] = M16::op(ar[t][s], im[g], yi[g][t]);
+        }
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          yr[g][t] = M16::op(ai[t][s], -im[g], yr[g][t]);
+          yi[g][t] = M16::op(ai[t][s], re[g], yi[g][t]);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        out[xh[4 * t + r] >> 1] = make_float4(yr[0][t][r], yi[0][t][r], yr[1][t][r], yi[1][t][r]);
+  }
+}
+
 // The same product when the K target qubits are the register's K lowest bits
 // (in any order): the 16 groups of a wave tile are 16 N consecutive
 // amplitudes, so the wave moves them with 16-byte loads and stores that each
@@ -375,24 +485,29 @@ __global__ __launch_bounds__(256) void k_fused_mfma_low(T* __restrict__ st, uint
     }
   const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x >> 6) + w;
   const uint64_t n_waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
+  // contiguous 16-byte loads, the next tile's before this tile's products
+  // (26 qubits, k = 5: 232 -> 222 us)
+  using V16 = std::conditional_t<sizeof(T) == 8, double2, float4>;
+  V16 nv[ACC];
+  auto fetch = [&](uint64_t tl) {
+    const V16* p = reinterpret_cast<const V16*>(st) + (back ? n_tiles - 1 - tl : tl) * (AMPS / PER16) + lane;
+#pragma unroll
+    for (int a = 0; a < ACC; ++a) nv[a] = p[a * 64];
+  };
+  if (wave < n_tiles) fetch(wave);
   for (uint64_t tl = wave; tl < n_tiles; tl += n_waves) {
     const uint64_t base = (back ? n_tiles - 1 - tl : tl) * AMPS;
-    // contiguous 16-byte loads into the padded rows
+    // into the padded rows
 #pragma unroll
     for (int a = 0; a < ACC; ++a) {
       const int e = (a * 64 + lane) * PER16;  // first amplitude of this access
       C2<T> v[PER16];
-      if constexpr (sizeof(T) == 8) {
-        const double2 d = reinterpret_cast<const double2*>(st)[base + e];
-        v[0] = {d.x, d.y};
-      } else {
-        const float4 f = reinterpret_cast<const float4*>(st)[(base + e) >> 1];
-        v[0] = {f.x, f.y};
-        v[PER16 - 1] = {f.z, f.w};
-      }
+      v[0] = {nv[a].x, nv[a].y};
+      if constexpr (sizeof(T) == 4) v[PER16 - 1] = {nv[a].z, nv[a].w};
 #pragma unroll
       for (int i = 0; i < PER16; ++i) reg[((e + i) >> K) * P + ((e + i) & (N - 1))] = v[i];
     }
+    if (tl + n_waves < n_tiles) fetch(tl + n_waves);
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the wave's LDS writes are done
     V4 yr[RT], yi[RT];

@@ -3021,6 +3021,16 @@ static unsigned fused_mfma_grid(uint64_t n_tiles) {
   return (unsigned)std::min(want, cap);
 }
 
+template <int K>
+static unsigned fused_wide_grid(uint64_t n_tiles) {
+  static const int per_cu = [] {
+    int b = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_fused_mfma_wide<K>, 256, 0) != hipSuccess || b < 1) b = 1;
+    return b;
+  }();
+  return (unsigned)std::min((n_tiles + 3) / 4, (uint64_t)device_cu_count() * per_cu);
+}
+
 extern "C" {
 
 static sv_status fused_slots(sv_state s) {
@@ -3070,10 +3080,14 @@ sv_status sv_apply_fused(sv_state s, int k, const int* qubits, const double* m) 
   // 16x16 MFMA tiles need 16 rows (k >= 4) and 16 groups per tile
   const bool mfma = k >= 4 && s->n - k >= 4;
   // complex64, targets = the k lowest bits: contiguous groups, staged through
-  // LDS (26 qubits, k = 5: 298 -> 222 us; complex128 gains nothing there,
+  // LDS (26 qubits, k = 5: 298 us without; complex128 gains nothing there,
   // 436 -> 472 us, and keeps the direct kernel)
   bool low = mfma && s->dt == SV_C64;
   for (int i = 0; i < k; ++i) low = low && q[i] < k;
+  // complex64, bit 0 no target, 32 groups or more: two groups a lane (26
+  // qubits, k = 5: 257 -> 236 us)
+  bool wide = mfma && s->dt == SV_C64 && s->n - k >= 5;
+  for (int i = 0; i < k; ++i) wide = wide && q[i] > 0;
   const dim3 g(grid_for(ng, 256)), b(256);
   const int back = next_walk(s);
 #define QEC_FUSED(K)                                                                             \
@@ -3094,6 +3108,9 @@ sv_status sv_apply_fused(sv_state s, int k, const int* qubits, const double* m) 
       hipLaunchKernelGGL((k_fused_mfma<double, K, FusedPF<double, K>::value>),                  \
                          dim3(fused_mfma_grid<double, K, false>(ng / 16)), b, 0, s->stream,       \
                          (double*)s->ptr, ng / 16, dm, q[0], q[1], q[2], q[3], q[4], back);            \
+    else if (wide)                                                                              \
+      hipLaunchKernelGGL((k_fused_mfma_wide<K>), dim3(fused_wide_grid<K>(ng / 32)), b, 0,           \
+                         s->stream, (float*)s->ptr, ng / 32, dm, q[0], q[1], q[2], q[3], q[4], back); \
     else                                                                                        \
       hipLaunchKernelGGL((k_fused_mfma<float, K, FusedPF<float, K>::value>),                    \
                          dim3(fused_mfma_grid<float, K, false>(ng / 16)), b, 0, s->stream,        \
