@@ -1774,26 +1774,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UpassWaves<
   upass_body<T, AK, AP, BK, BP, false, false, 2>(st, pd, jc, rta, rtb, dec_a, dec_b, partials, reverse, ss, dna, dnb, sa);
 }
 
-// Member-by-member outcomes of unit B from its sums S (see k_upass): each
+// Member-by-member outcomes of unit B from its sums S (LDS, see k_upass): each
 // member l is decided from the two sums that follow the outcomes already
 // drawn, p1 = S[l][h | 1 << l] / (S[l][h] + S[l][h | 1 << l]), clamped, against
-// its measurement draw.
-__device__ void decide_chain(const volatile double* S, int lb, const BlockRT* rtb, Decision* dec_b,
-                             uint8_t* rec_b, double* p1_b) {
-  int h = 0;
-  double Sm = 0.0;
-  for (int l = 0; l < lb; ++l) {
-    const int off = (2 << l) - 2;
-    const double s0 = S[off + h], s1 = S[off + (h | (1 << l))];
-    const double p1 = clamp_p1(s1 / (s0 + s1));
-    const int m = (rtb[l].u < p1) ? 1 : 0;
-    rec_b[l] = (uint8_t)m;
-    if (p1_b) p1_b[l] = p1;
-    h |= m << l;
-    Sm = m ? s1 : s0;
+// its measurement draw.  By the first wave: lane (1 << l) - 1 + h decides
+// member l after prefix h against its draw u (chain_draw, asked for before the
+// sums are there), and the outcomes are read off the vote.  Returns them.
+// (One thread after another member, each with its own trip to memory for the
+// draw, took some 4 us of a decision.)
+__device__ __forceinline__ int chain_level() { return 31 - __clz((int)threadIdx.x + 1); }
+__device__ __forceinline__ double chain_draw(int lb, const BlockRT* rtb) {
+  return threadIdx.x < 64 && chain_level() < lb ? rtb[chain_level()].u : 0.0;
+}
+__device__ __forceinline__ int decide_chain(const double* S, int lb, double u, Decision* dec_b, uint8_t* rec_b,
+                                            double* p1_b) {
+  const int t = threadIdx.x, l = chain_level(), h = t + 1 - (1 << l), off = (2 << l) - 2;
+  const bool on = l < lb;
+  const double s0 = on ? S[off + h] : 1.0, s1 = on ? S[off + (h | (1 << l))] : 1.0;
+  const double p1 = clamp_p1(s1 / (s0 + s1));
+  const uint64_t votes = __ballot(on && u < p1);
+  int out = 0;
+  for (int k = 0; k < lb; ++k) {
+    const int node = (1 << k) - 1 + out, m = (int)((votes >> node) & 1);
+    out |= m << k;
+    if (t != node) continue;
+    rec_b[k] = (uint8_t)m;
+    if (p1_b) p1_b[k] = p1;
+    if (k == lb - 1) {
+      dec_b->m = out;
+      dec_b->Sm = m ? s1 : s0;
+    }
   }
-  dec_b->m = h;
-  dec_b->Sm = Sm;
+  return out;
 }
 
 // The full tree of prefix sums (index (2 << l) - 2 + h) in LDS from a unit's
@@ -1858,11 +1870,12 @@ static __global__ __launch_bounds__(256) void k_udecide(const double* __restrict
   rec_b += (size_t)slot * rec_stride;
   if (p1_b) p1_b += (size_t)slot * rec_stride;
   __shared__ double full[kChainAcc];
+  const double u = chain_draw(lb, rtb);
   if (!split) {
     chain_tree_lds(lb, [&](int a) {
       return sum_in_order(n, [&](int i) { return partials[(size_t)a * n + i]; });
     }, full);
-    if (threadIdx.x == 0) decide_chain(full, lb, rtb, dec_b, rec_b, p1_b);
+    if (threadIdx.x < 64) decide_chain(full, lb, u, dec_b, rec_b, p1_b);
     return;
   }
   const int a = blockIdx.x;
@@ -1893,10 +1906,8 @@ static __global__ __launch_bounds__(256) void k_udecide(const double* __restrict
   __threadfence();
   const volatile double* vs = sums;
   chain_tree_lds(lb, [&](int b) { return vs[b]; }, full);
-  if (threadIdx.x == 0) {
-    decide_chain(full, lb, rtb, dec_b, rec_b, p1_b);
-    tickets[slot] = 0u;
-  }
+  if (threadIdx.x < 64) decide_chain(full, lb, u, dec_b, rec_b, p1_b);
+  if (threadIdx.x == 0) tickets[slot] = 0u;
 }
 
 // Decision of a speculative unit instance of len members after a prediction
@@ -1946,6 +1957,7 @@ static __global__ __launch_bounds__(256) void k_sdecide(const double* __restrict
     return;
   }
   const int nacc = tree ? unit_sums(len) : 2 * len;
+  const double u = tree ? chain_draw(len, rtb) : 0.0;
   __shared__ double full[kChainAcc];
   __shared__ double col[kChainAcc];
   const volatile double* vs = col;
@@ -1986,12 +1998,14 @@ static __global__ __launch_bounds__(256) void k_sdecide(const double* __restrict
   }
   if (tree) {
     chain_tree_lds(len, [&](int b) { return vs[b]; }, full);
-    if (threadIdx.x == 0) {
-      const int applied = ctl->m;
-      decide_chain(full, len, rtb, dec_b, rec_b, p1_b);
-      ctl->m = dec_b->m;
-      ctl->known = len;
-      ctl->run = dec_b->m != applied;
+    if (threadIdx.x < 64) {
+      const int m = decide_chain(full, len, u, dec_b, rec_b, p1_b);
+      if (threadIdx.x == 0) {
+        const int applied = ctl->m;
+        ctl->m = m;
+        ctl->known = len;
+        ctl->run = m != applied;
+      }
     }
     return;
   }
