@@ -1507,6 +1507,14 @@ bool template_is_monomial(const Template& tp, const std::vector<double>& eps) {
 
 int env_int(const char* name, int dflt);
 
+// Trajectories of a large complex64 register side by side, by passes with a
+// basis change: the end of a pass over one and its decision are hidden behind
+// the next one's.  Eight of five rounds 22.06 / 21.54 / 21.18 / 20.91 ms with
+// 1 / 2 / 4 / 8.  Not complex128 (41.6 ms with one and with four) and not the
+// plain passes, which find the lines their predecessor wrote in the cache if
+// they are of the same register (60.3 and 60.5 ms; complex128 113.1 and 115.3).
+constexpr int kLargeSlots = 4;
+
 // Which passes run.  Without the data ZZ layer (zeta = 0) a d = 5 register
 // takes the passes with a basis change (k_flip): five a round, none redone,
 // one register (complex64, p = 2e-3: 0.63 ms a round against 1.55 with the
@@ -1600,11 +1608,23 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   const bool small = n <= 16;
   const size_t reg_bytes = sizeof(T) * 2 * na * (spec ? 2 : 1);
   int slots = 1;
-  if (small && !(job->flags & SV_RUN_GRAPH))
-    slots = (int)std::max<size_t>(1, std::min<size_t>({(size_t)chunk, ((size_t)256 << 20) / reg_bytes, (size_t)32768}));
+  if (!(job->flags & SV_RUN_GRAPH)) {
+    if (small)
+      slots = (int)std::max<size_t>(1, std::min<size_t>({(size_t)chunk, ((size_t)256 << 20) / reg_bytes, (size_t)32768}));
+    else if (flip && sizeof(T) == 4)
+      slots = std::min(chunk, cancel ? 2 : kLargeSlots);  // (the server admits a job for two registers)
+  }
   const int n_angles = std::max(1, tp.zz_site >= 0 ? tp.zz_site + 1 : tp.n_sites);
   const size_t nrec = (size_t)job->n_traj * per_traj;
-  HIP_OK(M.alloc(&st, sizeof(T) * 2 * na * slots));
+  {
+    hipError_t e = M.alloc(&st, sizeof(T) * 2 * na * slots);
+    if (e != hipSuccess && !small && slots > 1) {  // one register at a time needs less
+      (void)hipGetLastError();
+      slots = 1;
+      e = M.alloc(&st, sizeof(T) * 2 * na);
+    }
+    HIP_OK(e);
+  }
   double* dacc = nullptr;
   unsigned* dticket = nullptr;
   const int n_dec = (spec ? per_units_s : per_units) + 1;  // a trajectory's decisions
@@ -1612,12 +1632,17 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   Packed K(s);
   K.out(&derr, sizeof(int));
   K.out(&dredos, sizeof(int));
-  K.out(&dticket, sizeof(unsigned));
+  K.out(&dticket, sizeof(unsigned) * slots);
   K.out(&drec, nrec, res->records);
   K.out(&dbits, (size_t)job->n_traj * n, res->final_bits);
   if (res->p1_trace) K.out(&dp1, sizeof(double) * nrec, res->p1_trace);
-  K.work(&partials, sizeof(double) * kChainAcc * n_tiles * slots);
-  K.work(&dacc, sizeof(double) * kChainAcc);
+  // passes with a basis change: as many workgroups as run at once (two per CU
+  // in complex128, three in complex64; see FlipShape)
+  const unsigned flip_wgs = (unsigned)device_cu_count() * (sizeof(T) == 8 ? 2u : 3u);
+  // (a pass leaves a partial of every sum per workgroup, at most one a tile)
+  const size_t parts_most = flip ? std::min<size_t>(n_tiles, flip_wgs) : n_tiles;
+  K.work(&partials, sizeof(double) * kChainAcc * parts_most * slots);
+  K.work(&dacc, sizeof(double) * kChainAcc * slots);
   K.work(&ddec, sizeof(Decision) * n_dec * slots);
   K.work(&dsums, (sizeof(double) << (n - cb)) * slots);
   HIP_OK(M.alloc(&drt, rt_per_traj * chunk));
@@ -1707,9 +1732,6 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                               ? n_tiles
                               : std::min<size_t>(n_tiles, (size_t)device_cu_count() * tune.pass_wgs_per_cu);
   const dim3 grid((unsigned)pass_wgs), block((unsigned)std::max(64, 1 << (tb - 4)));
-  // passes with a basis change: as many workgroups as run at once (two per CU
-  // in complex128, three in complex64; see FlipShape)
-  const unsigned flip_wgs = (unsigned)device_cu_count() * (sizeof(T) == 8 ? 2u : 3u);
   // the register after the last pass is wanted (else that pass only sums)
   const bool keep = xbasis || res->final_states;
   const SlotStrides ss0{(size_t)2 * na, (size_t)per_traj, (size_t)n_dec};
@@ -1735,7 +1757,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
         const FlipGrid fg = flip_grid(h, flip_wgs);
         *parts = fg.wgs;
         const int mode = ui < 0 ? kFlipSums : ui == 0 ? kFlipFirst : kFlipPass;
-        return pass_status(launch_flip<T>(h, mode, keep, dim3(fg.wgs), q, st, &dfpass[pidx], ra, rb, da, &ddec[ui + 1],
+        return pass_status(launch_flip<T>(h, mode, keep, dim3(fg.wgs, cnt), q, st, &dfpass[pidx], ra, rb, da, &ddec[ui + 1],
                                           partials, rev, (int)fg.n_cls_wg, last && !xbasis ? dsums : nullptr, ss0));
       }
       *parts = grid.x;
@@ -1747,7 +1769,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
       const int bi = inst(ui);
       const int lb = units[ui % nu].len;
       // one partial per pass workgroup
-      hipLaunchKernelGGL(k_udecide, small ? dim3(cnt) : dim3(unit_sums(lb)), dim3(small ? 64 : 256), 0, q, partials,
+      hipLaunchKernelGGL(k_udecide, small ? dim3(cnt) : dim3(unit_sums(lb), cnt), dim3(small ? 64 : 256), 0, q, partials,
                          (int)parts, lb, rt + bi, &ddec[ui], rec + bi, p1 ? p1 + bi : nullptr, ss0, (size_t)per_traj,
                          dacc, dticket, small ? 0 : 1);
     };
@@ -1837,7 +1859,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                        ss0.dec, xbasis ? 1 : 0, FlipFinal{});
   };
   double pass_ms_graph = -1.0;
-  int last_cnt = 1;  // trajectories of the last group (small registers)
+  int last_cnt = 1;  // trajectories of the last group
   std::vector<Decision> fin_host(res->final_states ? job->n_traj : 0);
   if (job->flags & SV_RUN_GRAPH) {
     // one trajectory's sequence, staged through fixed buffers and a device
@@ -1941,10 +1963,8 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                                       drec + (size_t)tg * per_traj,
                                       dp1 ? dp1 + (size_t)tg * per_traj : nullptr, timed));
         }
-        if (!async && small && is_last) {
-          HIP_OK(hipEventRecord(evs[1], s));
-          last_cnt = cnt;
-        }
+        if (!async && small && is_last) HIP_OK(hipEventRecord(evs[1], s));
+        last_cnt = cnt;
         if (res->final_states) {
           // a speculative run leaves the last unit's renormalisation pending
           if (spec)
@@ -2012,7 +2032,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   // replayed graphs and small registers: device time per pass and trajectory
   // of the last replay or group (an upper bound that includes the decisions,
   // for graphs also the draws and the final measurement)
-  res->pass_ms = pass_ms_graph >= 0.0 ? pass_ms_graph : pass_sum / timed_units;
+  res->pass_ms = pass_ms_graph >= 0.0 ? pass_ms_graph : pass_sum / ((double)timed_units * last_cnt);
   res->passes_per_round = spec ? nus : nu;
   res->redo_passes = spec ? *static_cast<const int*>(K.result(dredos)) : 0;
   return SV_OK;

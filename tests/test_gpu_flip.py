@@ -104,3 +104,16 @@ def test_first_and_last_pass(monkeypatch, rounds, xbasis, dtype):
         assert np.array_equal(g["records"], want["records"])
         assert np.array_equal(g["final_bits"], want["final_bits"])
         assert np.abs(g["p1"] - want["p1"]).max() <= tol
+
+
+@pytest.mark.parametrize("n_traj", [3, 5])
+def test_large_registers_side_by_side(n_traj):
+    """complex64 d = 5 trajectories in groups of four and a remainder: the bits
+    of each alone."""
+    kw = dict(d=5, gateset="cr", rounds=2, seed=41, p=0.01, eps=0.03, dtype="c64", want_p1=True)
+    whole = qs.run_rounds(n_traj=n_traj, traj0=6, **kw)
+    for t in (0, n_traj - 1):
+        one = qs.run_rounds(n_traj=1, traj0=6 + t, **kw)
+        assert np.array_equal(one["records"][0], whole["records"][t])
+        assert np.array_equal(one["final_bits"][0], whole["final_bits"][t])
+        assert np.array_equal(one["p1"][0], whole["p1"][t])
