@@ -85,6 +85,7 @@ def test_flip_matches_plain_passes_batch_d4(monkeypatch, dtype, mib):
 # instead of reading it (one round: they are two of the five passes; the X
 # basis starts from another state), the last one only sums unless the register
 # is wanted.
+@pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["c128", "c64"])
 @pytest.mark.parametrize("rounds", [1, 2])
 @pytest.mark.parametrize("xbasis", [False, True])
@@ -106,6 +107,7 @@ def test_first_and_last_pass(monkeypatch, rounds, xbasis, dtype):
         assert np.abs(g["p1"] - want["p1"]).max() <= tol
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("n_traj", [3, 5])
 def test_large_registers_side_by_side(n_traj):
     """complex64 d = 5 trajectories in groups of four and a remainder: the bits
