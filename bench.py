@@ -300,16 +300,16 @@ def batch_run(qs, d, n_traj, dtype, seed=7):
 
 
 def d5_without_zz_run(qs, torch, kw, n_traj=5):
-    """The d=5 workload without the data ZZ layer (zeta = 0): outcomes then
-    repeat from round to round and the speculative units run (each X pair or
-    Z chain summed and applied in one pass, redone when a predicted outcome
-    fails); timed beside the plain passes on the same trajectories."""
+    """The d=5 workload without the data ZZ layer (zeta = 0): the passes then
+    change the basis of up to 12 qubits, so that chains of checks of either
+    type are summed and applied at once; timed beside the plain passes on the
+    same trajectories."""
     import os
     kw = dict(kw, zeta=0.0)
     out = {"workload": "d5_cr without the data ZZ layer (zeta=0), otherwise as the headline",
            "trajectories": n_traj}
     saved = os.environ.get("QECSV_SPEC")
-    for name, env in (("speculative", None), ("plain", "0")):
+    for name, env in (("basis_change", None), ("plain", "0")):
         if env is None:
             os.environ.pop("QECSV_SPEC", None)
         else:
@@ -418,7 +418,7 @@ def main():
                     help="run one side measurement alone and print it (for profiling)")
     ap.add_argument("--zeta", type=float, default=None,
                     help="data ZZ angle of the timed d=5 workload (default: the workload's 0.01; "
-                         "0 runs the speculative passes; for profiles, not the benchmark line)")
+                         "0 runs the passes with a basis change; for profiles, not the benchmark line)")
     ap.add_argument("--no-extras", action="store_true",
                     help="skip the batched-launch, serving and precision measurements")
     ap.add_argument("--precision-traj", type=int, default=20,

@@ -23,9 +23,9 @@
 // 2e-3: complex128 198-210 us a pass (5.1-5.4 TB/s; the pass without flips
 // 193 us, an in-place scale of 512 MiB 192 us), complex64 102-109 us
 // (4.9-5.3 TB/s; 95 us without flips).  Above that rate lie the waits between
-// a tile's load, regroup and store.  A round: complex64 1.55 -> 0.63 ms,
-// complex128 2.4 -> 1.2 ms against the eight speculative passes and their
-// redos; 4096 d = 4 trajectories (complex64) 42.7 -> 17.6 ms.
+// a tile's load, regroup and store.  A round: complex64 1.55 -> 0.53 ms,
+// complex128 2.4 -> 1.04 ms against the eight speculative passes and their
+// redos; 4096 d = 4 trajectories (complex64) 42.7 -> 17.4 ms.
 //
 // Pauli frames: the XOR permutations are not carried out.  The stored
 // register is s Z^phix X^phiz |psi> written in the mixed basis; a Z member

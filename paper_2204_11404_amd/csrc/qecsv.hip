@@ -1517,8 +1517,8 @@ constexpr int kLargeSlots = 4;
 
 // Which passes run.  Without the data ZZ layer (zeta = 0) a d = 5 register
 // takes the passes with a basis change (k_flip): five a round, none redone,
-// one register (complex64, p = 2e-3: 0.63 ms a round against 1.55 with the
-// speculative units, complex128 1.2 against 2.4).  d = 4 keeps the
+// one register (complex64, p = 2e-3: 0.53 ms a round against 1.55 with the
+// speculative units, complex128 1.04 against 2.4).  d = 4 keeps the
 // speculative units here, whose count callers read in passes_per_round;
 // batches of d = 4 trajectories take the basis change (run_batch_lockstep).
 // With the layer the plain passes run: it is diagonal in the computational
