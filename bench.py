@@ -355,7 +355,7 @@ def d3_textbook_run(qs):
     return {"workload": "d3_textbook_c128", "trajectories": n, "launch_ms": t,
             "trajectories_per_s": n / (t * 1e-3), "per_circuit_equivalent_gbs": alg / (t * 1e-3) / 1e9,
             "per_circuit_equivalent_frac": alg / (t * 1e-3) / 1e9 / PEAK_HBM_GBS,
-            "registers_in": "LDS", "tuning": tuning}
+            "registers_in": "registers of one wave", "tuning": tuning}
 
 
 def precision_run(qs, n_state, n_stat, thetas=(0.01, 0.03, 0.05)):

@@ -367,8 +367,8 @@ sv_status sv_tuning_set(int d, int dtype, const sv_tuning* in);
  * device time) and keep the fastest for (d, dtype) on the current device:
  * d = 5, sv_run_rounds (one trajectory, one round): xpair x zchain x snake x
  *   pass_wgs_per_cu;
- * d = 4, sv_run_batch (4096 trajectories, 3 rounds): xpair x zchain x
- *   lockstep_mib;
+ * d = 4, sv_run_batch (4096 trajectories, 3 rounds, without the passes that
+ *   change the basis): xpair x zchain x lockstep_mib;
  * d <= 3, sv_run_batch (16384 trajectories, 3 rounds): batch_waves_per_cu.
  * Writes the winner to *best and its device time to *best_ms (either may be
  * NULL).  Synchronous, on the default stream; call it before serving, not

@@ -2111,6 +2111,7 @@ struct BatchInputs {
   void* final_regs = nullptr;   // host [n_traj][2^(d^2)] amplitudes, or null
   hipEvent_t done = nullptr;    // enqueue only, recorded after the results' copies
   int waves = 0;                // waves per trajectory (0: by the number of trajectories)
+  bool no_flip = false;         // d = 4: no basis change (the autotuner's trials: its choices are the other passes')
 };
 
 template <typename T>
@@ -2392,7 +2393,7 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
   const int per_traj = in.max_rounds * ns;
   const int spec_env = env_int("QECSV_SPEC", -1);
   FlipPlan fplan;
-  if (spec_env < 0 && in.zeta == 0.0 && !tp.any_dense) fplan = make_flip_plan(d, tp, false);
+  if (spec_env < 0 && in.zeta == 0.0 && !tp.any_dense && !in.no_flip) fplan = make_flip_plan(d, tp, false);
   const bool flip = !fplan.units.empty();
   const std::vector<Unit> units = flip ? fplan.units : make_units_paired(tp, tune.zchain, n, tune.xpair);
   const int nu = (int)units.size();
@@ -3809,6 +3810,7 @@ sv_status sv_autotune(int d, int dtype, int gateset, sv_tuning* best, double* be
     } else {
       BatchInputs in{d, gateset, nt, R, 0.0, seeds.data(), streams.data(), rounds.data(), pv.data(),
                      eps.data(), 0, rec.data(), bits.data(), (hipStream_t)nullptr, 0.0};
+      in.no_flip = true;
       SV_OK_OR_RETURN(dtype == SV_C128 ? run_batch_core<double>(in, tp) : run_batch_core<float>(in, tp));
       *ms = in.gpu_ms;
     }
