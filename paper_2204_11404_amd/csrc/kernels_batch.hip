@@ -28,8 +28,9 @@
 //      ZZ layer and 1/sqrt(S_m) and writes the amplitudes back.
 // After the last round wave 0 measures the data qubits one by one from the
 // highest label down (two-level descent: lane sums, then within one lane).
-// TRACE: the probabilities of the outcomes and the registers before that
-// measurement are written too (single runs that ask for them).
+// TRACE: the instantiation that sv_run_rounds takes, whatever it is asked for:
+// it can write the probabilities of the outcomes and the registers before that
+// measurement, and keeps the Kraus diagonals in double precision.
 #include "kernels_flip.hip"
 
 namespace qec {
@@ -59,12 +60,16 @@ struct SmallDesc {
   int xreg;
 };
 
-template <typename T>
+// E: precision of the Kraus diagonals.  Batches keep the register's own; runs
+// of sv_run_rounds double, rounded once with the renormalisation (complex64, d
+// = 3 with the ZZ layer, registers against 64 bits: 1.5e-7 / 2.6e-7 with float
+// diagonals, 1.3e-7 / 2.0e-7 by the register passes, which round once too).
+template <typename T, typename E>
 struct SmallSlot {
   C2<T> psi[kSmallAmps];
-  C2<T> Dc[kSmallStab][2][16];  // noise-free Kraus diagonals per template
+  C2<E> Dc[kSmallStab][2][16];  // noise-free Kraus diagonals per template
   double Wc[kSmallStab][2][16];
-  C2<T> D[2][16];               // current block when a Pauli was drawn
+  C2<E> D[2][16];               // current block when a Pauli was drawn
   double W[2][16];
   double cs[2 * kSmallSites];   // cos, sin of each site's angle
   double t1[3], t2[15];         // channel thresholds
@@ -76,10 +81,9 @@ struct SmallSlot {
 // Angle table and noise-free Kraus pairs of a launch whose over-rotation
 // angles are common to every trajectory: computed once on the host and
 // copied into each trajectory's slot instead of being rebuilt per trajectory.
-template <typename T>
 struct SmallShared {
   double cs[2 * kSmallSites];
-  C2<T> Dc[kSmallStab][2][16];
+  cd Dc[kSmallStab][2][16];
   double Wc[kSmallStab][2][16];
 };
 
@@ -184,10 +188,10 @@ struct LaneOps {
 // Tables of a new trajectory: site angles, thresholds, logical |0>.  sites:
 // the op of every gate site of the round template (index = site).
 // (tid, nl: thread index and threads of the trajectory's workgroup)
-template <typename T>
-__device__ void small_setup_tables(SmallSlot<T>& S, int tid, int nl, int n, const TOp* sites,
+template <typename T, typename E>
+__device__ void small_setup_tables(SmallSlot<T, E>& S, int tid, int nl, int n, const TOp* sites,
                                    int n_sites, const uint32_t* init_mask, T amp0, const double* eps,
-                                   double p, const SmallShared<T>* shared) {
+                                   double p, const SmallShared* shared) {
   // cos / sin of every site's angle
   if (shared) {
     for (int k = tid; k < 2 * n_sites; k += nl) S.cs[k] = shared->cs[k];
@@ -211,13 +215,14 @@ __device__ void small_setup_tables(SmallSlot<T>& S, int tid, int nl, int n, cons
 }
 
 // Noise-free Kraus pair of every template (needs the angle table).
-template <typename T>
-__device__ void small_setup_kraus(SmallSlot<T>& S, int tid, int nl, int ns, const TBlock* blocks,
-                                  int* err, const SmallShared<T>* shared) {
+template <typename T, typename E>
+__device__ void small_setup_kraus(SmallSlot<T, E>& S, int tid, int nl, int ns, const TBlock* blocks,
+                                  int* err, const SmallShared* shared) {
   if (shared) {
     for (int i = tid; i < ns * 32; i += nl) {
       const int s = i >> 5, m = (i >> 4) & 1, x = i & 15;
-      S.Dc[s][m][x] = shared->Dc[s][m][x];
+      const cd d = shared->Dc[s][m][x];
+      S.Dc[s][m][x] = C2<E>{(E)d.re, (E)d.im};
       S.Wc[s][m][x] = shared->Wc[s][m][x];
     }
     return;
@@ -231,8 +236,8 @@ __device__ void small_setup_kraus(SmallSlot<T>& S, int tid, int nl, int ns, cons
     uint32_t cur = 0;
     if (!track_column(b, CsFromTable{S.cs}, none, x, v0, v1, &cur)) atomicOr(err, 1);
     const double norm = b.type == 0 ? 1.0 / (double)(1 << b.w) : 1.0;
-    S.Dc[s][0][x] = C2<T>{(T)(v0.re * norm), (T)(v0.im * norm)};
-    S.Dc[s][1][x] = C2<T>{(T)(v1.re * norm), (T)(v1.im * norm)};
+    S.Dc[s][0][x] = C2<E>{(E)(v0.re * norm), (E)(v0.im * norm)};
+    S.Dc[s][1][x] = C2<E>{(E)(v1.re * norm), (E)(v1.im * norm)};
     S.Wc[s][0][x] = (v0.re * v0.re + v0.im * v0.im) * norm;
     S.Wc[s][1][x] = (v1.re * v1.re + v1.im * v1.im) * norm;
   }
@@ -270,14 +275,15 @@ __global__ __launch_bounds__(64 * NW) void k_batch_small(
     const int* __restrict__ order, int n_traj, const int* __restrict__ rounds,
     const double* __restrict__ pvec, const double* __restrict__ eps, int eps_stride,
     uint8_t* __restrict__ rec, int max_rounds, uint8_t* __restrict__ bits, int* __restrict__ err,
-    const TOp* __restrict__ sites, int n_sites, const SmallShared<T>* __restrict__ shared,
+    const TOp* __restrict__ sites, int n_sites, const SmallShared* __restrict__ shared,
     const uint32_t* __restrict__ init_mask, const uint8_t* __restrict__ draw_kind, double* __restrict__ p1_out,
     C2<T>* __restrict__ regs_out) {
   static_assert(NW == 1 || NW == 2 || NW == 4, "one, two or four waves per trajectory");
   constexpr int NL = 64 * NW;                       // threads of a trajectory
   constexpr int NA = NW == 1 ? 8 : NW == 2 ? 4 : 2;  // amplitudes per thread
   constexpr int DR = (kSmallDraws + NL - 1) / NL;   // draws per thread and round
-  __shared__ SmallSlot<T> S;
+  using E = std::conditional_t<TRACE, double, T>;
+  __shared__ SmallSlot<T, E> S;
   // ZZ phases are read per amplitude: keep them in LDS (the round template
   // stays in global memory: more LDS per workgroup would cost occupancy)
   __shared__ C2<T> lzz[kSmallBits * 2 + 1];
@@ -365,8 +371,8 @@ __global__ __launch_bounds__(64 * NW) void k_batch_small(
               uint32_t cur = 0;
               if (!track_ops(b.type == 0, nops, lo, lane, v0, v1, &cur)) atomicOr(err, 1);
               const double norm = b.type == 0 ? 1.0 / (double)nx : 1.0;
-              S.D[0][lane] = C2<T>{(T)(v0.re * norm), (T)(v0.im * norm)};
-              S.D[1][lane] = C2<T>{(T)(v1.re * norm), (T)(v1.im * norm)};
+              S.D[0][lane] = C2<E>{(E)(v0.re * norm), (E)(v0.im * norm)};
+              S.D[1][lane] = C2<E>{(E)(v1.re * norm), (E)(v1.im * norm)};
               S.W[0][lane] = (v0.re * v0.re + v0.im * v0.im) * norm;
               S.W[1][lane] = (v1.re * v1.re + v1.im * v1.im) * norm;
               if (lane == 0) S.F = cur;  // label 0 maps to F
@@ -374,7 +380,7 @@ __global__ __launch_bounds__(64 * NW) void k_batch_small(
           }
           __syncthreads();
         }
-        const C2<T>(*D)[16] = noisy ? S.D : S.Dc[s];
+        const C2<E>(*D)[16] = noisy ? S.D : S.Dc[s];
         const double(*W)[16] = noisy ? S.W : S.Wc[s];
         const uint32_t F = noisy ? S.F : 0u;
         // 2. measure and apply
@@ -432,8 +438,8 @@ __global__ __launch_bounds__(64 * NW) void k_batch_small(
           for (int j = 0; j < NA; ++j) {
             const uint32_t x = ((uint32_t)j & xm) | xhi;
             // (TRACE: the renormalisation with the factor, one rounding less)
-            const C2<T> e = D[m][x];
-            v[j] = TRACE ? mulc(v[j], (T)((double)e.re * scale), (T)((double)e.im * scale)) : mulc(v[j], e.re, e.im);
+            const C2<E> e = D[m][x];
+            v[j] = TRACE ? mulc(v[j], (T)(e.re * scale), (T)(e.im * scale)) : mulc(v[j], (T)e.re, (T)e.im);
           }
         }
         if (xb) small_wht<T, NA>(v, xreg, xlanes, tid);
@@ -528,7 +534,11 @@ __global__ __launch_bounds__(64 * NW) void k_batch_small(
 // drawn outcomes are read off the votes one after another.  Bound by vector
 // instructions (some 2000 a round, 2500 to set a trajectory up): 65 536 ragged
 // complex64 trajectories 4.74 -> 1.60 ms, 1000 complex128 textbook ones of
-// three rounds 78 -> 33 us.
+// three rounds 78 -> 33 us.  TRACE as for k_batch_small (an outcome's
+// p1 is in the lane of its prefix), but with the register's own precision for
+// the diagonals: one chain's rounding replaces four circuits' (complex64
+// registers against 64 bits 9.0e-8, by the passes 9.8e-8; double ones 7.1e-8,
+// and 65 536 trajectories of five rounds 1.15 -> 1.67 ms).
 //
 // Lane bits are qubits 1, 3, 4, 5, 6, 7; register bits the corners 0, 2 and 8,
 // each of which belongs to one X check and one Z check only, so that those
@@ -628,14 +638,14 @@ __device__ __forceinline__ double pair_sum(double a) {
   return a + b;
 }
 
-template <typename T>
+template <typename T, bool TRACE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 4))) void k_batch_flip(
     const TBlock* __restrict__ blocks, const FlipSmallDesc* __restrict__ fd, int draws_round,
     const uint64_t* __restrict__ tseed, const uint64_t* __restrict__ tstream, const int* __restrict__ order, int n_traj,
     const int* __restrict__ rounds, const double* __restrict__ pvec, const double* __restrict__ eps, int eps_stride,
     uint8_t* __restrict__ rec, int max_rounds, uint8_t* __restrict__ bits, int* __restrict__ err,
-    const TOp* __restrict__ sites, int n_sites, const SmallShared<T>* __restrict__ shared,
-    const uint8_t* __restrict__ draw_kind) {
+    const TOp* __restrict__ sites, int n_sites, const SmallShared* __restrict__ shared,
+    const uint8_t* __restrict__ draw_kind, double* __restrict__ p1_out, C2<T>* __restrict__ regs_out) {
   constexpr int kN = 9, kStab = 8;
   __shared__ FlipSmallSlot<T> S;
   __shared__ uint32_t ops[kStab][kMaxOpsBatch][3];  // the round template's ops
@@ -670,7 +680,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
         const double f = s < 4 ? (double)(1 << fd->w[s]) : 1.0;
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
-          const C2<T> d = shared->Dc[s][m][x];
+          const cd d = shared->Dc[s][m][x];
           S.D[0][m][i] = C2<T>{(T)(d.re * f), (T)(d.im * f)};
           S.W[0][m][i] = shared->Wc[s][m][x] * f;
         }
@@ -727,7 +737,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
       for (int i = 0; i < 4; ++i) on = on && !(__popc(g & fd->parity[i]) & 1);
       v[j] = C2<T>{on ? (T)0.17677669529663688 : (T)0, (T)0};  // 2^(-5/2)
     }
-    uint32_t phz = 0, phx = 0;  // frames (see FlipPass); no register leaves the kernel, so no sign is kept
+    uint32_t phz = 0, phx = 0;  // frames (see FlipPass)
+    int neg = 0;                // and the sign (TRACE)
     for (int r = 0; r < R; ++r) {
       // the round's draws and the noise locations that picked a Pauli
       uint64_t hits[2];
@@ -790,7 +801,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           if (ph) off |= gather_loc(ph, fd->q[C0 + i], fd->w[C0 + i]) << (4 * i);
-          if ((noisy >> (C0 + i)) & 1) ph ^= scatter_loc(S.F[C0 + i], fd->q[C0 + i], fd->w[C0 + i]);
+          if ((noisy >> (C0 + i)) & 1) {
+            const uint32_t G = scatter_loc(S.F[C0 + i], fd->q[C0 + i], fd->w[C0 + i]);
+            if (TRACE && X) neg ^= __popc(G & phz) & 1;
+            ph ^= G;
+          }
         }
         ph = (uint32_t)__builtin_amdgcn_readfirstlane((int)ph);
         const uint32_t xl = (X ? pl & 0xFFFFu : pl >> 16) ^ off;
@@ -856,6 +871,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const uint64_t vote = __ballot(S.u[fd->meas[C0 + i]] < p1[i]);
+          if (TRACE && p1_out && lane == (int)(4 * (h | (1u << i))))
+            p1_out[((size_t)t * max_rounds + r) * kStab + C0 + i] = p1[i];
           h |= (uint32_t)((vote >> (4 * (h | (1u << i)))) & 1) << i;
         }
         const double Sm = lane_value(m3, (int)(4 * h));
@@ -899,6 +916,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
       chain(I4{}, I1{}, I3{}, I2{}, I0{});
       if (r + 1 < R) small_wht_all(v, lane);
       __syncthreads();  // S.u and the noisy tables are written again
+    }
+    if (TRACE && regs_out) {
+      // amplitude x of the logical frame sits at x ^ phz, with the sign of neg
+      // and of phx there
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        uint32_t g = gl;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+          if ((j >> k) & 1) g |= 1u << kFlipRegQubit[k];
+        const bool minus = ((__popc(g & phx) ^ neg) & 1) != 0;
+        regs_out[((size_t)t << kN) + (g ^ phz)] = minus ? C2<T>{-v[j].re, -v[j].im} : v[j];
+      }
     }
     // final Z measurement, highest label first: the norms summed over the
     // lower qubits level by level (register bits 0, 1, 2: qubits 0, 2, 8),

@@ -2110,7 +2110,8 @@ struct BatchInputs {
   double* p1 = nullptr;         // host [n_traj][max_rounds][n_stab], or null
   void* final_regs = nullptr;   // host [n_traj][2^(d^2)] amplitudes, or null
   hipEvent_t done = nullptr;    // enqueue only, recorded after the results' copies
-  int waves = 0;                // waves per trajectory (0: by the number of trajectories)
+  bool run = false;             // a run of sv_run_rounds: bits that depend neither on how many trajectories
+                                // run beside one nor on what is asked for (two waves each, TRACE kernels)
   bool no_flip = false;         // d = 4: no basis change (the autotuner's trials: its choices are the other passes')
 };
 
@@ -2231,7 +2232,7 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
   const size_t nrec = (size_t)nt * in.max_rounds * ns;
   const size_t neps = in.eps_stride ? (size_t)nt * in.eps_stride : (size_t)std::max(1, tp.n_sites);
   TOp* dsites = nullptr;
-  SmallShared<T>* dshared = nullptr;
+  SmallShared* dshared = nullptr;
   uint32_t* dinit = nullptr;
   uint8_t* dkind = nullptr;
   FlipSmallDesc* dfd = nullptr;
@@ -2244,15 +2245,14 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
   // 0.138 ms, the per-circuit reduction and decision then dominate);
   // QECSV_BATCH_SPLIT forces 1, 2 or 4
   const int simds = 4 * device_cu_count();
-  int nw = in.waves ? in.waves : nt <= 2 * simds ? 2 : 1;
+  int nw = in.run || nt <= 2 * simds ? 2 : 1;
   const int forced = env_int("QECSV_BATCH_SPLIT", 0);
   if (forced == 1 || forced == 2 || forced == 4) nw = forced;
   // d = 3 without the data ZZ layer: the register in one wave's registers and
-  // the checks in chains of four (k_batch_flip), unless a split or what it
-  // does not keep - probabilities, registers - is asked for
+  // the checks in chains of four (k_batch_flip), unless a split is asked for
   FlipSmallDesc fd;
-  const bool trace = in.p1 || in.final_regs;
-  const bool flip = !trace && in.zeta == 0.0 && forced == 0 && make_flip_small(d, tp, fd);
+  const bool trace = in.run;
+  const bool flip = in.zeta == 0.0 && forced == 0 && make_flip_small(d, tp, fd);
   const std::vector<SmallDesc> sd = make_small_descs(n, tp, nw);
   const JobConst jc = make_job_const(d, in.zeta);
   // the op of every gate site (index = site)
@@ -2264,7 +2264,7 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
   // angles common to every trajectory: the angle table and noise-free Kraus
   // pairs once, here
   if (in.eps_stride == 0) {
-    SmallShared<T> sh{};
+    SmallShared sh{};
     for (int k = 0; k < tp.n_sites; ++k) {
       const double beta = op_angle(sites[k], in.eps);
       sh.cs[2 * k] = std::cos(beta);
@@ -2278,8 +2278,8 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
         if (!track_column(tp.blocks[b], CsFromTable{sh.cs}, none, x, v0, v1, &cur))
           return fail(SV_EINVAL, "circuit template is not monomial in its block basis");
         const double norm = tp.blocks[b].type == 0 ? 1.0 / (double)(1 << tp.blocks[b].w) : 1.0;
-        sh.Dc[b][0][x] = C2<T>{(T)(v0.re * norm), (T)(v0.im * norm)};
-        sh.Dc[b][1][x] = C2<T>{(T)(v1.re * norm), (T)(v1.im * norm)};
+        sh.Dc[b][0][x] = cd{v0.re * norm, v0.im * norm};
+        sh.Dc[b][1][x] = cd{v1.re * norm, v1.im * norm};
         sh.Wc[b][0][x] = (v0.re * v0.re + v0.im * v0.im) * norm;
         sh.Wc[b][1][x] = (v1.re * v1.re + v1.im * v1.im) * norm;
       }
@@ -2341,19 +2341,23 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
       hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * nwv), 0, s, dblocks, dsd, ns, n, tp.n_draws, djc,
                          dseed, dstream, dorder, nt, drounds, dp, deps, in.eps_stride, drec,
                          in.max_rounds, dbits, derr, (const TOp*)dsites, tp.n_sites,
-                         (const SmallShared<T>*)dshared, (const uint32_t*)dinit, (const uint8_t*)dkind, dp1, dregs);
+                         (const SmallShared*)dshared, (const uint32_t*)dinit, (const uint8_t*)dkind, dp1, dregs);
       return hipGetLastError();
     };
     if (flip) {
-      int per_cu = tuning_for(in.d, sizeof(T) == 8 ? SV_C128 : SV_C64).batch_waves_per_cu, resident = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, k_batch_flip<T>, 64, 0) == hipSuccess && resident > 0)
-        per_cu = std::min(per_cu, resident);
-      const int grid = std::max(1, std::min(nt, device_cu_count() * per_cu));
-      HIP_OK(hipEventRecord(ev_a, s));
-      hipLaunchKernelGGL(k_batch_flip<T>, dim3(grid), dim3(64), 0, s, dblocks, dfd, tp.n_draws, dseed, dstream, dorder,
-                         nt, drounds, dp, deps, in.eps_stride, drec, in.max_rounds, dbits, derr, (const TOp*)dsites,
-                         tp.n_sites, (const SmallShared<T>*)dshared, (const uint8_t*)dkind);
-      HIP_OK(hipGetLastError());
+      auto launch_flip_small = [&](auto kernel) -> hipError_t {
+        int per_cu = tuning_for(in.d, sizeof(T) == 8 ? SV_C128 : SV_C64).batch_waves_per_cu, resident = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, kernel, 64, 0) == hipSuccess && resident > 0)
+          per_cu = std::min(per_cu, resident);
+        const int grid = std::max(1, std::min(nt, device_cu_count() * per_cu));
+        const hipError_t e = hipEventRecord(ev_a, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, dblocks, dfd, tp.n_draws, dseed, dstream, dorder, nt,
+                           drounds, dp, deps, in.eps_stride, drec, in.max_rounds, dbits, derr, (const TOp*)dsites,
+                           tp.n_sites, (const SmallShared*)dshared, (const uint8_t*)dkind, dp1, dregs);
+        return hipGetLastError();
+      };
+      HIP_OK(trace ? launch_flip_small(k_batch_flip<T, true>) : launch_flip_small(k_batch_flip<T, false>));
     } else if (nw == 4) HIP_OK(trace ? launch(k_batch_small<T, 4, true>, 4) : launch(k_batch_small<T, 4, false>, 4));
     else if (nw == 2) HIP_OK(trace ? launch(k_batch_small<T, 2, true>, 2) : launch(k_batch_small<T, 2, false>, 2));
     else HIP_OK(trace ? launch(k_batch_small<T, 1, true>, 1) : launch(k_batch_small<T, 1, false>, 1));
@@ -2723,7 +2727,7 @@ sv_status run_rounds_small(const sv_job* job, sv_result* res, const Template& tp
     if (res->p1_trace) in.p1 = res->p1_trace + t0 * per_traj;
     if (res->final_states) in.final_regs = (char*)res->final_states + t0 * reg;
     in.done = done;
-    in.waves = 2;  // (a trajectory's bits do not depend on how many run beside it)
+    in.run = true;
     SV_OK_OR_RETURN(run_batch_core<T>(in, tp));
     ms += in.gpu_ms;
   }
