@@ -101,12 +101,16 @@ template <typename T> struct FlipShape {
 // register is wanted (keep): k_final_measure applies A to the chunk it reads.
 // d = 5: the two 155 -> 108 us in complex64 and 297 -> 171 in complex128, the
 // last one 96 -> 53 and 194 -> 142 (with k_final_measure 117 -> 88 and 217 -> 180).
+// Sums: a partial of every sum per workgroup, or per tile (per_tile: at most
+// four tiles a workgroup) where the workgroups of a register depend on how many
+// run side by side: the decisions then add the same numbers in the same order
+// whatever that is.
 template <typename T, int LB, int MODE, bool L5>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T>::kWaves))) void k_flip(
     T* __restrict__ st, const FlipPass* __restrict__ pd, const BlockRT* __restrict__ rta,
     const BlockRT* __restrict__ rtb, const Decision* __restrict__ dec_a, Decision* __restrict__ dec_b,
-    double* __restrict__ partials, int reverse, int n_cls_wg, double* __restrict__ chunk_sums, int keep,
-    SlotStrides ss) {
+    double* __restrict__ partials, int reverse, int n_cls_wg, int per_tile, double* __restrict__ chunk_sums,
+    int keep, SlotStrides ss) {
   constexpr bool INIT = MODE == kFlipSums, FIRST = MODE == kFlipFirst;
   constexpr uint32_t kAmp = 2 * sizeof(T);
   constexpr bool kAhead = FlipShape<T>::kAhead && MODE == kFlipPass;
@@ -116,8 +120,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T
   if (rtb) rtb += slot * ss.rt;
   if (dec_a) dec_a += slot * ss.dec;
   dec_b += slot * ss.dec;
-  partials += slot * kChainAcc * gridDim.x;
   const int n_outer = pd->n_outer, n_brel = pd->n_brel;
+  const uint32_t n_cols = per_tile ? 1u << n_outer : gridDim.x;
+  partials += slot * kChainAcc * n_cols;
   if (chunk_sums) chunk_sums += slot << n_outer;
   const RegBuf<T> reg(st, (uint32_t)(kAmp << (kTileMax + n_outer)));
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -231,8 +236,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T
   const uint32_t n_cls = 1u << n_brel, n_steps = 1u << (n_outer - n_brel);
   const uint32_t c0 = blockIdx.x % n_cls_wg, w0 = blockIdx.x / n_cls_wg, gs = gridDim.x / n_cls_wg;
   // (global bits of a tile, and A's packed index there)
+  auto tile_of = [&](uint32_t c, uint32_t step) { return ((reverse ? n_steps - 1 - step : step) << n_brel) | c; };
   auto locate = [&](uint32_t c, uint32_t step, uint32_t& b, uint32_t& x) {
-    const uint32_t tile = ((reverse ? n_steps - 1 - step : step) << n_brel) | c;
+    const uint32_t tile = tile_of(c, step);
     b = x = 0;
     for (int i = 0; i < n_outer; ++i)
       if ((tile >> i) & 1) {
@@ -244,7 +250,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T
 #pragma unroll
   for (int j = 0; j < (LB > 0 ? 16 : 1); ++j) acc[j] = 0.0;
   constexpr int kN = LB > 0 ? 1 << LB : 1, kGroups = kN > 16 ? kN / 16 : 1;
-  double total[kGroups];  // lane l: sum (l >> 2) & 15 of each group of 16
+  // lane l: sum (l >> 2) & 15 of each group of 16 (per_tile: of tile l & 3)
+  double total[kGroups];
+  int n_sums = 0;  // per_tile: tiles summed
 #pragma unroll
   for (int k = 0; k < kGroups; ++k) total[k] = 0.0;
 
@@ -407,7 +415,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T
           acc[j] = fma(re, re, fma(im, im, acc[j]));
         }
       }
-      if (!more || cls != cls_now) {
+      if (!more || cls != cls_now || per_tile) {
         if constexpr (INIT) {
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
@@ -474,8 +482,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T
             const int n = 16 * k + a;
             t[a] = n < kN ? p[n & ((1 << R) - 1)] * z[(n >> R) & 3] : 0.0;
           }
-          total[k] += wave_reduce16(t);
+          const double w = wave_reduce16(t);
+          if (!per_tile) total[k] += w;
+          else if ((lane & 3) == n_sums) total[k] = w;
         }
+        ++n_sums;
 #pragma unroll
         for (int j = 0; j < 16; ++j) acc[j] = 0.0;
       }
@@ -494,26 +505,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FlipShape<T
   }
 
   if constexpr (LB > 0) {
-    double(*const red)[4] = reinterpret_cast<double(*)[4]>(buf);
+    // the waves' totals added up, a column of the partial sums per workgroup
+    // or tile
+    double(*const red)[kN][4] = reinterpret_cast<double(*)[kN][4]>(buf);
+    const int n_own = per_tile ? n_sums : 1;
     __syncthreads();  // the regroup buffer is read no more
 #pragma unroll
     for (int k = 0; k < kGroups; ++k)
-      if ((lane & 3) == 0 && 16 * k + (lane >> 2) < kN) red[16 * k + (lane >> 2)][wid] = total[k];
+      if ((lane & 3) < n_own && 16 * k + (lane >> 2) < kN) red[lane & 3][16 * k + (lane >> 2)][wid] = total[k];
     __syncthreads();
-    if (tid < kN) {
+    const int own = tid >> LB, n = tid & (kN - 1);  // (at most 4 x 64 of the 256 threads)
+    const uint32_t own_steps = (n_steps - w0 + gs - 1) / gs;
+    const uint32_t col = per_tile ? tile_of(c0 + own / own_steps * n_cls_wg, w0 + own % own_steps * gs) : blockIdx.x;
+    if (own < n_own) {
       uint32_t h = 0;  // outcome bits in member order
 #pragma unroll
-      for (int l = 0; l < LB; ++l) h |= ((tid >> l) & 1) << pd->ord[l];
-      const double s = (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
+      for (int l = 0; l < LB; ++l) h |= ((n >> l) & 1) << pd->ord[l];
+      const double s = (red[own][n][0] + red[own][n][1]) + (red[own][n][2] + red[own][n][3]);
       // sums of a chain of one or two are laid out as every prefix's
-      partials[(size_t)(LB == 2 ? 2 + h : h) * gridDim.x + blockIdx.x] = s;
+      partials[(size_t)(LB == 2 ? 2 + h : h) * n_cols + col] = s;
     }
     if constexpr (LB == 2) {
-      if (tid < 2) {  // outcome tid of member 0, either outcome of member 1
+      if (own < n_own && n < 2) {  // outcome n of member 0, either outcome of member 1
         double s = 0.0;
         const int o = pd->ord[0] == 0 ? 1 : 2;
-        for (int w = 0; w < 4; ++w) s += red[tid * o][w] + red[tid * o + 3 - o][w];
-        partials[(size_t)tid * gridDim.x + blockIdx.x] = s;
+        for (int w = 0; w < 4; ++w) s += red[own][n * o][w] + red[own][n * o + 3 - o][w];
+        partials[(size_t)n * n_cols + col] = s;
       }
     }
   }

@@ -26,6 +26,6 @@ int launch_spass(const UnitPass& h, bool redo, dim3 g, dim3 b, hipStream_t s, T*
 template <typename T>
 int launch_flip(const FlipPass& h, int mode, bool keep, dim3 g, hipStream_t s, T* st, const FlipPass* pd,
                  const BlockRT* rta, const BlockRT* rtb, const Decision* da, Decision* db, double* part, int rev,
-                 int n_cls_wg, double* chunk_sums, SlotStrides ss);
+                 int n_cls_wg, bool per_tile, double* chunk_sums, SlotStrides ss);
 
 }  // namespace qec

@@ -113,11 +113,11 @@ int launch_spass(const UnitPass& h, bool redo, dim3 g, dim3 b, hipStream_t s, T*
 template <typename T>
 int launch_flip(const FlipPass& h, int mode, bool keep, dim3 g, hipStream_t s, T* st, const FlipPass* pd,
                  const BlockRT* rta, const BlockRT* rtb, const Decision* da, Decision* db, double* part, int rev,
-                 int n_cls_wg, double* chunk_sums, SlotStrides ss) {
+                 int n_cls_wg, bool per_tile, double* chunk_sums, SlotStrides ss) {
 #define QEC_FL(LBV, MODEV, L5V)                                                                                   \
   if (h.lb == LBV && mode == MODEV && (h.lane5 != 0) == L5V) {                                                    \
     hipLaunchKernelGGL((k_flip<T, LBV, MODEV, L5V>), g, dim3(256), 0, s, st, pd, rta, rtb, da, db, part, rev, \
-                       n_cls_wg, chunk_sums, keep ? 1 : 0, ss);                                                   \
+                       n_cls_wg, per_tile ? 1 : 0, chunk_sums, keep ? 1 : 0, ss);                                 \
     return 0;                                                                                                     \
   }
 #define QEC_FL_B(LBV)                                                                                        \
@@ -144,7 +144,7 @@ int launch_flip(const FlipPass& h, int mode, bool keep, dim3 g, hipStream_t s, T
 #endif
 #if !defined(QEC_PART) || QEC_PART == 2
 #define QEC_INSTANCE_2(QEC_TT) \
-  template int launch_flip<QEC_TT>(const FlipPass& h, int mode, bool keep, dim3 g, hipStream_t s, QEC_TT* st, const FlipPass* pd, const BlockRT* rta, const BlockRT* rtb, const Decision* da, Decision* db, double* part, int rev, int n_cls_wg, double* chunk_sums, SlotStrides ss);
+  template int launch_flip<QEC_TT>(const FlipPass& h, int mode, bool keep, dim3 g, hipStream_t s, QEC_TT* st, const FlipPass* pd, const BlockRT* rta, const BlockRT* rtb, const Decision* da, Decision* db, double* part, int rev, int n_cls_wg, bool per_tile, double* chunk_sums, SlotStrides ss);
 #else
 #define QEC_INSTANCE_2(QEC_TT)
 #endif

@@ -1758,7 +1758,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
         *parts = fg.wgs;
         const int mode = ui < 0 ? kFlipSums : ui == 0 ? kFlipFirst : kFlipPass;
         return pass_status(launch_flip<T>(h, mode, keep, dim3(fg.wgs, cnt), q, st, &dfpass[pidx], ra, rb, da, &ddec[ui + 1],
-                                          partials, rev, (int)fg.n_cls_wg, last && !xbasis ? dsums : nullptr, ss0));
+                                          partials, rev, (int)fg.n_cls_wg, false, last && !xbasis ? dsums : nullptr, ss0));
       }
       *parts = grid.x;
       return pass_status(launch_upass<T>(pds[pidx], dim3(grid.x, cnt), block, q, st, &dpass[pidx], djc, ra, rb, da,
@@ -2482,7 +2482,11 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
   // passes with a basis change: at least four workgroups per slot of four
   // tiles each, more when few slots would leave compute units idle (2048
   // complex64 trajectories: 10.0 / 9.4 / 9.3 / 10.4 / 13.1 ms with 1 / 2 / 4 /
-  // 8 / 16; 300: 2.45 / 2.44 / 2.30 / 2.44 / 2.75)
+  // 8 / 16; 300: 2.45 / 2.44 / 2.30 / 2.44 / 2.75).  They leave a partial per
+  // tile, so that no trajectory's bits depend on the slots beside it (a partial
+  // per workgroup: 4096 complex64 trajectories of up to nine rounds 18.8
+  // instead of 19.9 ms a call, 2048 complex128 14.6 and 15.1; four workgroups
+  // for any number of slots: one trajectory 1.55 ms instead of 1.20)
   const unsigned flip_wgs = (unsigned)device_cu_count() * (sizeof(T) == 8 ? 2u : 3u);
   // pass workgroups per slot, each taking tiles grid-stride: four tiles each
   // for passes that sum a Z chain or write logical |0> (their tables - up to
@@ -2631,9 +2635,10 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
       if (flip) {
         const FlipPass& h = fplan.passes[pidx];
         const FlipGrid fg = flip_grid(h, std::max(4u, flip_wgs / (unsigned)cnt));
-        *gx = fg.wgs;
+        *gx = 1u << h.n_outer;  // a partial per tile: the same sums whatever the other slots
+        if (4 * fg.wgs < *gx) return fail(SV_EINVAL, "more than four tiles a workgroup");
         return pass_status(launch_flip<T>(h, mode, false, dim3(fg.wgs, cnt), s, reg0, &dfpass[pidx], ra, rb, da, db,
-                                          partials, rev, (int)fg.n_cls_wg, rb ? nullptr : dsums, ss));
+                                          partials, rev, (int)fg.n_cls_wg, true, rb ? nullptr : dsums, ss));
       }
       *gx = gx_of(pds[pidx]);
       return pass_status(launch_upass<T>(pds[pidx], dim3(*gx, cnt), block, s, reg0, &dpass[pidx], djc, ra, rb, da, db, partials,
