@@ -97,8 +97,8 @@ template <typename T> struct FlipShape {
 // kFlipPass: the steps above.  The first two passes of a trajectory know the
 // register without reading it: kFlipSums sums B over the initial code state
 // (nothing is stored), kFlipFirst applies A to that state as it forms it.
-// The last pass (LB = 0) only sums the final measurement's chunks unless the
-// register is wanted (keep): k_final_measure applies A to the chunk it reads.
+// The last pass (LB = 0) only sums the final measurement's chunks (keep: it
+// stores the register): k_final_measure applies A to the chunk it reads.
 // d = 5: the two 155 -> 108 us in complex64 and 297 -> 171 in complex128, the
 // last one 96 -> 53 and 194 -> 142 (with k_final_measure 117 -> 88 and 217 -> 180).
 // Sums: a partial of every sum per workgroup, or per tile (per_tile: at most

@@ -1732,8 +1732,8 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                               ? n_tiles
                               : std::min<size_t>(n_tiles, (size_t)device_cu_count() * tune.pass_wgs_per_cu);
   const dim3 grid((unsigned)pass_wgs), block((unsigned)std::max(64, 1 << (tb - 4)));
-  // the register after the last pass is wanted (else that pass only sums)
-  const bool keep = xbasis || res->final_states;
+  // the register after the last pass is read (else that pass only sums)
+  const bool keep = xbasis;
   const SlotStrides ss0{(size_t)2 * na, (size_t)per_traj, (size_t)n_dec};
   const int draws_round = tp.n_draws;
   const int last_t = job->n_traj - 1;
@@ -1834,6 +1834,15 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     HIP_OK(hipGetLastError());
     *out = cur;
     return SV_OK;
+  };
+  // the last pass with a basis change once more, for the register: after the
+  // measurement, which so reads the same numbers whether it is wanted or not
+  auto flip_store = [&](hipStream_t q, int cnt, const BlockRT* rt) -> sv_status {
+    const FlipPass& h = fplan.passes[nu + 1];
+    const FlipGrid fg = flip_grid(h, flip_wgs);
+    return pass_status(launch_flip<T>(h, kFlipPass, true, dim3(fg.wgs, cnt), q, st, &dfpass[nu + 1],
+                                      rt + inst(per_units - 1), nullptr, &ddec[per_units - 1], &ddec[fin], partials, 0,
+                                      (int)fg.n_cls_wg, false, nullptr, ss0));
   };
   // final Z measurement of cnt data registers at buf (draw streams t on, or *tptr);
   // in the X basis a Walsh-Hadamard transform of the whole register first,
@@ -1965,6 +1974,14 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
         }
         if (!async && small && is_last) HIP_OK(hipEventRecord(evs[1], s));
         last_cnt = cnt;
+        auto measure = [&] {
+          traj_final(s, cnt, buf, drt + (size_t)ti * per_traj, dbits + (size_t)tg * n, job->traj0 + (uint64_t)tg, nullptr);
+        };
+        const bool measured = res->final_states && flip && !xbasis;
+        if (measured) {
+          measure();
+          SV_OK_OR_RETURN(flip_store(s, cnt, drt + (size_t)ti * per_traj));
+        }
         if (res->final_states) {
           // a speculative run leaves the last unit's renormalisation pending
           if (spec)
@@ -1976,7 +1993,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
                                   sizeof(Decision), cnt, hipMemcpyDeviceToHost, s));
           HIP_OK(hipStreamSynchronize(s));
         }
-        traj_final(s, cnt, buf, drt + (size_t)ti * per_traj, dbits + (size_t)tg * n, job->traj0 + (uint64_t)tg, nullptr);
+        if (!measured) measure();
         HIP_OK(hipGetLastError());
       }
     }

@@ -39,3 +39,35 @@ def test_frames_and_sign(monkeypatch, d, gateset, zeta, dtype, tol):
     assert np.abs(got["p1"] - want["p1"]).max() <= tol
     assert np.abs(got["states"] - want["states"]).max() <= tol
     assert np.array_equal(p1["p1"], got["p1"])
+
+
+def test_registers_change_no_final_bit_d5():
+    """complex64 d = 5: over-rotations around the value at which a bit of the
+    final measurement turns, in steps of the register's rounding."""
+    sites = qs.template_info(5, "cr")[1]
+    pattern = np.random.default_rng(3).uniform(0.5, 1.0, sites)
+
+    def bits(a, seed, **kw):
+        g = qs.run_rounds(d=5, gateset="cr", rounds=1, n_traj=1, seed=seed, p=0.0, eps_site=a * pattern, dtype="c64",
+                          **kw)
+        return np.concatenate([g["records"].reshape(-1), g["final_bits"].reshape(-1)])
+
+    turned = 0
+    for seed in range(16):  # (few seeds have a bit that turns while no outcome does)
+        grid = np.linspace(0.05, 0.25, 30)
+        rows = [bits(a, seed) for a in grid]
+        at = [i for i in range(29) if np.array_equal(rows[i][:24], rows[i + 1][:24]) and
+              not np.array_equal(rows[i], rows[i + 1])]
+        if not at:
+            continue
+        lo, hi = grid[at[0]], grid[at[0] + 1]
+        while hi - lo > 1e-9 * lo:
+            mid = 0.5 * (lo + hi)
+            lo, hi = (mid, hi) if np.array_equal(bits(mid, seed), rows[at[0]]) else (lo, mid)
+        near = lo * (1.0 + np.linspace(-2e-7, 2e-7, 17))
+        plain = [bits(a, seed) for a in near]
+        turned += len(np.unique(plain, axis=0)) > 1
+        print(f"case final bits seed {seed}", flush=True)
+        for a, want in zip(near, plain):
+            assert np.array_equal(bits(a, seed, want_states=True), want), (seed, a)
+    assert turned >= 2
