@@ -2140,14 +2140,10 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp);
 struct Arena {
   char* base;
   size_t cap, used;
-  bool overflow;
   template <typename P>
   hipError_t alloc(P** out, size_t bytes) {
     const size_t off = (used + 255) & ~(size_t)255;
-    if (off + bytes > cap) {
-      overflow = true;
-      return hipErrorOutOfMemory;
-    }
+    if (off + bytes > cap) return hipErrorOutOfMemory;
     *out = reinterpret_cast<P*>(base + off);
     used = off + bytes;
     return hipSuccess;
@@ -3687,7 +3683,34 @@ sv_status sv_run_batch(const sv_batch_job* job, sv_batch_result* res) {
 // copy comes from hipGetSymbolAddress, taken once per device with that device
 // current, and only that address is handed to kernels and copies.
 constexpr size_t kNoAllocScratchBytes = (size_t)64 << 20;
-static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+// (the launch's block also holds what the limit does not count: the descriptor
+// of k_batch_flip, diagonals in double precision, the gaps between its regions)
+constexpr size_t kNoAllocSlack = (size_t)8 << 10;
+static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + kNoAllocSlack];
+
+// Bytes of a job as the limit counts them: its tables, parameters and results,
+// each on a 256-byte boundary.
+static size_t noalloc_bytes(const sv_batch_job* job, const Template& tp) {
+  const size_t nt = (size_t)job->n_traj, ns = tp.blocks.size(), n = (size_t)job->d * job->d;
+  const size_t sites = (size_t)std::max(1, tp.n_sites), real = job->dtype == SV_C128 ? 8 : 4;
+  size_t used = 0;
+  auto add = [&](size_t bytes) { used = ((used + 255) & ~(size_t)255) + bytes; };
+  add(sizeof(TBlock) * ns);
+  add(sizeof(SmallDesc) * ns);
+  add(sizeof(JobConst));
+  add(sizeof(int) * nt);  // order, rounds
+  add(sizeof(int) * nt);
+  add(sizeof(int));
+  for (int i = 0; i < 3; ++i) add(8 * nt);  // p, seed, stream
+  add(sizeof(double) * (job->eps_site ? nt * tp.n_sites : sites));
+  add(nt * job->max_rounds * ns);
+  add(nt * n);
+  add(sizeof(TOp) * sites);
+  if (!job->eps_site) add(8 * 2 * kSmallSites + (2 * real + 8) * kSmallStab * 2 * 16);  // angle table, Kraus pairs
+  add(64);
+  add((size_t)std::max(1, tp.n_draws));
+  return used;
+}
 
 namespace {
 struct NoAllocDevice {
@@ -3726,14 +3749,13 @@ sv_status sv_run_batch_noalloc(const sv_batch_job* job, sv_batch_result* res) {
   if (nd.init_status != SV_OK) return fail(nd.init_status, "%s", nd.init_err.c_str());
   res->gpu_ms = 0.0;
   if (job->n_traj == 0) return SV_OK;
+  if (noalloc_bytes(job, tp) > kNoAllocScratchBytes)
+    return fail(SV_ENOMEM, "the job needs more than the %zu MiB no-allocation scratch", kNoAllocScratchBytes >> 20);
   std::lock_guard<std::mutex> lk(nd.mu);
   BatchHost h(job, res, tp);
-  Arena A{static_cast<char*>(nd.ptr), kNoAllocScratchBytes, 0, false};
+  Arena A{static_cast<char*>(nd.ptr), kNoAllocScratchBytes + kNoAllocSlack, 0};
   const sv_status st = job->dtype == SV_C128 ? run_batch_small<double>(h.in, tp, A, nd.ev_a, nd.ev_b)
                                              : run_batch_small<float>(h.in, tp, A, nd.ev_a, nd.ev_b);
-  if (A.overflow)
-    return fail(SV_ENOMEM, "the job needs more than the %zu MiB no-allocation scratch",
-                kNoAllocScratchBytes >> 20);
   res->gpu_ms = h.in.gpu_ms;
   res->passes_per_round = h.in.passes_per_round;
   res->redo_passes = h.in.redo_passes;
