@@ -114,10 +114,13 @@ class PinnedPool {
     if (!idle_.empty()) {
       p = idle_.back();
       idle_.pop_back();
-    } else if (made_ < kMost && hipHostMalloc(&p, kBlock, hipHostMallocPortable) == hipSuccess) {
-      ++made_;
     } else {
-      return nullptr;
+      if (made_ == kMost) return nullptr;
+      if (hipHostMalloc(&p, kBlock, hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();  // not the call's: it takes pageable memory
+        return nullptr;
+      }
+      ++made_;
     }
     peak_ = std::max(peak_, made_ - (int)idle_.size());
     return p;
