@@ -19,6 +19,7 @@
 #include <mutex>
 #include <thread>
 #include <type_traits>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -55,6 +56,19 @@ sv_status fail(sv_status st, const char* fmt, ...) {
   do {                                                                                \
     hipError_t e_ = (expr);                                                           \
     if (e_ != hipSuccess) return fail(SV_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
+  } while (0)
+
+// As HIP_OK for an allocation whose failure the caller may answer with a
+// smaller call: `flag` says that memory was short, and the runtime's last
+// error is taken off.
+#define MEM_OK(expr, flag)                                             \
+  do {                                                                 \
+    const hipError_t e_ = (expr);                                      \
+    if (e_ != hipSuccess) {                                            \
+      (flag) = e_ == hipErrorOutOfMemory;                              \
+      (void)hipGetLastError();                                         \
+      return fail(SV_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
+    }                                                                  \
   } while (0)
 
 #define SV_OK_OR_RETURN(expr)                \
@@ -232,18 +246,15 @@ class Packed {
   // upload: a host function on the stream releases its host memory.  (No
   // result() or collect() afterwards; fetch copies into the user's memory.)
   template <typename Alloc>
-  sv_status commit_async(Alloc& M) {
+  hipError_t commit_async(Alloc& M) {
     HostBlock* keep = nullptr;
     hipError_t e = commit(M, &keep);
     if (e == hipSuccess) e = hipLaunchHostFunc(s_, [](void* q) { delete static_cast<HostBlock*>(q); }, keep);
-    if (e != hipSuccess) {
-      if (keep) {
-        (void)hipStreamSynchronize(s_);
-        delete keep;
-      }
-      return fail(SV_EDEVICE, "set-up copies: %s", hipGetErrorString(e));
+    if (e != hipSuccess && keep) {
+      (void)hipStreamSynchronize(s_);
+      delete keep;
     }
-    return SV_OK;
+    return e;
   }
   hipError_t fetch() {
     if (block_ && block_->pinned) {
@@ -1540,9 +1551,10 @@ constexpr int kLargeSlots = 4;
 // (complex128); with zeta = 0.01 the layer turns 15 % of the X checks'
 // outcomes from one round to the next and the redos make them slower (3.1
 // against 3.0 ms).
+// most_slots: registers side by side at most.  no_memory: an allocation failed.
 template <typename T>
-sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
-                       const std::atomic<int>* cancel = nullptr, hipEvent_t done = nullptr) {
+sv_status run_rounds_sized(const sv_job* job, sv_result* res, const Template& tp, const std::atomic<int>* cancel,
+                           hipEvent_t done, int most_slots, bool& no_memory) {
   const bool async = done != nullptr;
   const int d = job->d, n = d * d, ns = (int)tp.blocks.size(), R = job->rounds;
   const int tb = std::min(kTileMax, n);
@@ -1617,17 +1629,10 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     else if (flip && sizeof(T) == 4)
       slots = std::min(chunk, cancel ? 2 : kLargeSlots);  // (the server admits a job for two registers)
   }
+  slots = std::min(slots, most_slots);
   const int n_angles = std::max(1, tp.zz_site >= 0 ? tp.zz_site + 1 : tp.n_sites);
   const size_t nrec = (size_t)job->n_traj * per_traj;
-  {
-    hipError_t e = M.alloc(&st, sizeof(T) * 2 * na * slots);
-    if (e != hipSuccess && !small && slots > 1) {  // one register at a time needs less
-      (void)hipGetLastError();
-      slots = 1;
-      e = M.alloc(&st, sizeof(T) * 2 * na);
-    }
-    HIP_OK(e);
-  }
+  MEM_OK(M.alloc(&st, sizeof(T) * 2 * na * slots), no_memory);
   double* dacc = nullptr;
   unsigned* dticket = nullptr;
   const int n_dec = (spec ? per_units_s : per_units) + 1;  // a trajectory's decisions
@@ -1648,9 +1653,9 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   K.work(&dacc, sizeof(double) * kChainAcc * slots);
   K.work(&ddec, sizeof(Decision) * n_dec * slots);
   K.work(&dsums, (sizeof(double) << (n - cb)) * slots);
-  HIP_OK(M.alloc(&drt, rt_per_traj * chunk));
+  MEM_OK(M.alloc(&drt, rt_per_traj * chunk), no_memory);
   BlockDense* ddn = nullptr;  // dense Kraus pairs (blocks with crosstalk inside)
-  if (tp.any_dense) HIP_OK(M.alloc(&ddn, dn_per_traj * chunk));
+  if (tp.any_dense) MEM_OK(M.alloc(&ddn, dn_per_traj * chunk), no_memory);
 
   const std::vector<UnitPass> pds = flip ? std::vector<UnitPass>(nu + 2) : make_unit_passes(n, tb, tp, units);
   FlipPass* dfpass = nullptr;
@@ -1664,7 +1669,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   if (spec) {
     for (const TBlock& b : tp.blocks)
       pred0.push_back(job->gateset == SV_GATESET_CR ? (uint8_t)((b.w / 2) % 2) : (uint8_t)0);
-    HIP_OK(M.alloc(&st2, sizeof(T) * 2 * na * slots));
+    MEM_OK(M.alloc(&st2, sizeof(T) * 2 * na * slots), no_memory);
     K.work(&dctl, sizeof(SpecCtl) * per_units_s * slots);
   }
   std::vector<double> eps(n_angles, job->eps);
@@ -1703,8 +1708,7 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
     K.put(&dspass, spds.data(), sizeof(UnitPass) * spds.size());
     K.put(&dpred0, pred0.data(), pred0.size());
   }
-  if (async) SV_OK_OR_RETURN(K.commit_async(M));
-  else HIP_OK(K.commit(M));
+  MEM_OK(async ? K.commit_async(M) : K.commit(M), no_memory);
   HIP_OK(hipMemsetAsync(ddec, 0, sizeof(Decision) * n_dec * slots, s));
   // four instances of a check a wave
   auto prepare_grid = [&](int n_traj) { return (unsigned)(((((int64_t)n_traj * R + 3) / 4) * ns + 1) / 2); };
@@ -2058,6 +2062,16 @@ sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp,
   return SV_OK;
 }
 
+// A run by register passes.  Where memory is short for the registers side by
+// side, one at a time takes the least (nothing has been enqueued by then).
+template <typename T>
+sv_status run_rounds_t(const sv_job* job, sv_result* res, const Template& tp, const std::atomic<int>* cancel = nullptr,
+                       hipEvent_t done = nullptr) {
+  bool no_memory = false;
+  const sv_status st = run_rounds_sized<T>(job, res, tp, cancel, done, INT_MAX, no_memory);
+  return no_memory ? run_rounds_sized<T>(job, res, tp, cancel, done, 1, no_memory) : st;
+}
+
 // Lane / register maps of the small-register batch kernel for each block
 // template: a lane's 8 registers span three of a weight-4 check's qubits (its
 // fourth is lane bit 0), or a weight-2 check's two qubits and the lowest other
@@ -2130,6 +2144,7 @@ struct BatchInputs {
   double* p1 = nullptr;         // host [n_traj][max_rounds][n_stab], or null
   void* final_regs = nullptr;   // host [n_traj][2^(d^2)] amplitudes, or null
   hipEvent_t done = nullptr;    // enqueue only, recorded after the results' copies
+  bool no_memory = false;       // out: an allocation failed
   bool run = false;             // a run of sv_run_rounds: bits that depend neither on how many trajectories
                                 // run beside one nor on what is asked for (two waves each, TRACE kernels)
   bool no_flip = false;         // d = 4: no basis change (the autotuner's trials: its choices are the other passes')
@@ -2338,8 +2353,7 @@ sv_status run_batch_small(BatchInputs& in, const Template& tp, Alloc& M, hipEven
   K.out(&dbits, (size_t)nt * n, in.final_bits);
   if (in.p1) K.out(&dp1, sizeof(double) * nrec, in.p1);
   if (in.final_regs) K.out(&dregs, (sizeof(C2<T>) << n) * nt, in.final_regs);
-  if (async) SV_OK_OR_RETURN(K.commit_async(M));
-  else HIP_OK(K.commit(M));
+  MEM_OK(async ? K.commit_async(M) : K.commit(M), in.no_memory);
   if (eps_apart) HIP_OK(hipMemcpyAsync(deps, in.eps, sizeof(double) * neps, hipMemcpyHostToDevice, s));
   {
     // a persistent launch: no more workgroups than stay resident at once
@@ -2730,7 +2744,7 @@ sv_status run_rounds_small(const sv_job* job, sv_result* res, const Template& tp
   const size_t per_traj = (size_t)R * tp.blocks.size(), reg = sizeof(C2<T>) << n;
   // (at most 256 MiB of results on the device at a time)
   const size_t bytes = per_traj * (res->p1_trace ? 9 : 1) + n + (res->final_states ? reg : 0);
-  const int most = done ? job->n_traj : (int)std::max<size_t>(1, std::min<size_t>(job->n_traj, ((size_t)256 << 20) / bytes));
+  int most = done ? job->n_traj : (int)std::max<size_t>(1, std::min<size_t>(job->n_traj, ((size_t)256 << 20) / bytes));
   std::vector<double> eps(std::max(1, tp.n_sites), job->eps);
   if (job->eps_site) std::copy(job->eps_site, job->eps_site + tp.n_sites, eps.begin());
   const std::vector<uint64_t> seeds(most, job->seed);
@@ -2738,9 +2752,9 @@ sv_status run_rounds_small(const sv_job* job, sv_result* res, const Template& tp
   const std::vector<double> p(most, job->p);
   std::vector<uint64_t> streams(most);
   double ms = 0.0;
-  for (int t0 = 0; t0 < job->n_traj; t0 += most) {
+  for (int t0 = 0, cnt; t0 < job->n_traj; t0 += cnt) {
     if (cancel && cancel->load(std::memory_order_relaxed)) return fail(SV_EBUSY, "cancelled");
-    const int cnt = std::min(most, job->n_traj - t0);
+    cnt = std::min(most, job->n_traj - t0);
     for (int i = 0; i < cnt; ++i) streams[i] = job->traj0 + (uint64_t)(t0 + i);
     BatchInputs in{job->d, job->gateset, cnt, R, job->zeta, seeds.data(), streams.data(), rounds.data(), p.data(),
                    eps.data(), 0, res->records + t0 * per_traj, res->final_bits + (size_t)t0 * n,
@@ -2749,7 +2763,13 @@ sv_status run_rounds_small(const sv_job* job, sv_result* res, const Template& tp
     if (res->final_states) in.final_regs = (char*)res->final_states + t0 * reg;
     in.done = done;
     in.run = true;
-    SV_OK_OR_RETURN(run_batch_core<T>(in, tp));
+    const sv_status st = run_batch_core<T>(in, tp);
+    if (in.no_memory && cnt > 1 && !done) {  // fewer at a time (nothing has been enqueued)
+      most = cnt / 2;
+      cnt = 0;
+      continue;
+    }
+    SV_OK_OR_RETURN(st);
     ms += in.gpu_ms;
   }
   const int nu = (int)make_units_paired(tp, tuning_for(job->d, job->dtype).zchain, n,

@@ -1,5 +1,6 @@
 """Calls that find less memory than they would like: without pinned blocks they
-take pageable memory, and the results are the same.
+take pageable memory, without device memory for the trajectories side by side
+they run fewer at a time, and the results are the same.
 
 A small library in front of the HIP runtime refuses the allocation; the call
 runs in a process of its own, which loads it before the simulator."""
@@ -19,14 +20,19 @@ FRONT = r"""
 #include <stddef.h>
 typedef int (*host_fn)(void**, size_t, unsigned);
 typedef int (*dev_fn)(void**, size_t, void*);
+typedef int (*free_fn)(void*, void*);
 static host_fn real_host;
 static dev_fn real_dev;
+static free_fn real_free;
 int refuse_host = 0, refused = 0;
-size_t most = ~(size_t)0;
+size_t most = ~(size_t)0; /* bytes allocated in stream order at a time */
+static size_t live, size_of[1024];
+static void* ptr_of[1024];
 void setup(const char* path) {
   void* h = dlopen(path, RTLD_NOW);
   real_host = (host_fn)dlsym(h, "hipHostMalloc");
   real_dev = (dev_fn)dlsym(h, "hipMallocAsync");
+  real_free = (free_fn)dlsym(h, "hipFreeAsync");
 }
 int hipHostMalloc(void** p, size_t n, unsigned flags) {
   if (!refuse_host) return real_host(p, n, flags);
@@ -34,10 +40,29 @@ int hipHostMalloc(void** p, size_t n, unsigned flags) {
   return real_host(NULL, n, flags); /* an error of the runtime's own, which it remembers */
 }
 int hipMallocAsync(void** p, size_t n, void* s) {
-  if (n <= most) return real_dev(p, n, s);
-  ++refused;
-  real_host(NULL, n, 0); /* as above */
-  return 2; /* out of memory */
+  if (n > most || live > most - n) {
+    ++refused;
+    real_host(NULL, n, 0); /* as above */
+    return 2;              /* out of memory */
+  }
+  const int r = real_dev(p, n, s);
+  for (int i = 0; r == 0 && i < 1024; ++i)
+    if (!ptr_of[i]) {
+      ptr_of[i] = *p;
+      size_of[i] = n;
+      live += n;
+      break;
+    }
+  return r;
+}
+int hipFreeAsync(void* p, void* s) {
+  for (int i = 0; p && i < 1024; ++i)
+    if (ptr_of[i] == p) {
+      ptr_of[i] = NULL;
+      live -= size_of[i];
+      break;
+    }
+  return real_free(p, s);
 }
 """
 
@@ -77,4 +102,26 @@ def test_no_pinned_block(tmp_path):
         assert refused.value > 0
         refuse_host.value = 0
         assert same(a, qs.run_rounds(**kw))
+    """)
+
+
+# d = 5: four registers fit and the tables beside them do not; d = 4 (also with
+# two registers each: the predicted passes): room for some of the registers;
+# d <= 3: for some of the results
+@pytest.mark.parametrize("mib,kw", [
+    (1024, dict(d=5, rounds=2, n_traj=4, dtype="c64")),
+    (40, dict(d=4, rounds=2, n_traj=150, dtype="c64", zeta=0.01)),
+    (40, dict(d=4, rounds=2, n_traj=60, dtype="c64", zeta=0.0)),
+    (6, dict(d=3, rounds=2, n_traj=2000, dtype="c128", zeta=0.01, want_states=True)),
+])
+def test_short_device_memory(tmp_path, mib, kw):
+    print(f"case short device memory {mib} {kw}", flush=True)
+    _run(tmp_path, f"""
+        kw = dict(gateset="cr", seed=3, p=0.02, eps=0.02, **{kw!r})
+        most.value = {mib} << 20
+        a = qs.run_rounds(**kw)
+        assert refused.value > 0
+        n = refused.value
+        most.value = 1 << 40
+        assert same(a, qs.run_rounds(**kw)) and refused.value == n
     """)
