@@ -46,13 +46,15 @@ __global__ void k_logical0(T* __restrict__ st, uint64_t n_amp, const JobConst* _
   st2(st, i, C2<T>{in ? (T)jc->amp0 : (T)0, (T)0});
 }
 
-// The operations on a whole register take a direction (`back`: highest
-// addresses first) that the library alternates: a pass starts on the lines its
-// predecessor left in the 256 MB last-level cache (26 qubits, complex128: 398
-// -> 362 us a gate; an in-place scale without that reuse takes 383).
-__device__ __forceinline__ uint64_t walk_thread(int back) {
-  const uint64_t b = back ? (uint64_t)gridDim.x - 1 - blockIdx.x : (uint64_t)blockIdx.x;
-  return b * blockDim.x + threadIdx.x;
+// The operations on a whole register take a direction, which the library
+// alternates for registers larger than the 256 MB last-level cache: a pass
+// starts on the lines its predecessor left there (26 qubits, complex128: 398 ->
+// 362 us a gate; an in-place scale without that reuse takes 383).  turn: 0, or
+// the number of workgroups - 1, a power of two, for highest addresses first (one
+// scalar instruction: the number from the dispatch packet instead cost a
+// complex64 phase on 25 qubits 18 us of 98).
+__device__ __forceinline__ uint64_t walk_thread(uint32_t turn) {
+  return (uint64_t)(blockIdx.x ^ turn) * blockDim.x + threadIdx.x;
 }
 
 __device__ __forceinline__ uint64_t insert_zero(uint64_t x, int q) {
@@ -61,8 +63,8 @@ __device__ __forceinline__ uint64_t insert_zero(uint64_t x, int q) {
 }
 
 template <typename T>
-__global__ void k_gate1(T* __restrict__ st, uint64_t n_pairs, int q, Mat2 M, int back) {
-  const uint64_t p = walk_thread(back);
+__global__ void k_gate1(T* __restrict__ st, uint64_t n_pairs, int q, Mat2 M, uint32_t turn) {
+  const uint64_t p = walk_thread(turn);
   if (p >= n_pairs) return;
   const uint64_t i0 = insert_zero(p, q), i1 = i0 | (1ull << q);
   const C2<T> a = ld2(st, i0), b = ld2(st, i1);
@@ -77,8 +79,8 @@ __global__ void k_gate1(T* __restrict__ st, uint64_t n_pairs, int q, Mat2 M, int
 
 // qlo < qhi; local index bit 0 = q0 (first listed), bit 1 = q1.
 template <typename T>
-__global__ void k_gate2(T* __restrict__ st, uint64_t n_quads, int q0, int q1, Mat4 M, int back) {
-  const uint64_t p = walk_thread(back);
+__global__ void k_gate2(T* __restrict__ st, uint64_t n_quads, int q0, int q1, Mat4 M, uint32_t turn) {
+  const uint64_t p = walk_thread(turn);
   if (p >= n_quads) return;
   const int qlo = q0 < q1 ? q0 : q1, qhi = q0 < q1 ? q1 : q0;
   const uint64_t i00 = insert_zero(insert_zero(p, qlo), qhi);
@@ -110,11 +112,11 @@ __device__ __forceinline__ T quad_xor(T v, int d) {  // lane ^ d within the quad
   return d == 1 ? dpp_mv<0xB1>(v) : d == 2 ? dpp_mv<0x4E>(v) : dpp_mv<0x1B>(v);
 }
 template <typename T>
-__global__ __launch_bounds__(256) void k_gate2_quad(T* __restrict__ st, int swap, Mat4 M, int back) {
+__global__ __launch_bounds__(256) void k_gate2_quad(T* __restrict__ st, int swap, Mat4 M, uint32_t turn) {
   __shared__ T sm[32];
   if (threadIdx.x < 32) sm[threadIdx.x] = (T)M.m[threadIdx.x];
   __syncthreads();
-  const uint64_t i = walk_thread(back);
+  const uint64_t i = walk_thread(turn);
   const C2<T> a = ld2(st, i);
   const int x = (int)(i & 3);                               // address bits 0, 1
   auto local = [&](int y) { return swap ? ((y >> 1) & 1) | ((y & 1) << 1) : y; };
@@ -134,11 +136,11 @@ __global__ __launch_bounds__(256) void k_gate2_quad(T* __restrict__ st, int swap
 // The same gate for complex64 registers: thread i holds amplitudes 2 i and
 // 2 i + 1 (one 16-byte access), its pair lane i ^ 1 the other half of the
 // quadruple (DPP quad_perm xor 1); each thread computes its two rows.
-__global__ __launch_bounds__(256) void k_gate2_pair_f32(float* __restrict__ st, int swap, Mat4 M, int back) {
+__global__ __launch_bounds__(256) void k_gate2_pair_f32(float* __restrict__ st, int swap, Mat4 M, uint32_t turn) {
   __shared__ float sm[32];
   if (threadIdx.x < 32) sm[threadIdx.x] = (float)M.m[threadIdx.x];
   __syncthreads();
-  const uint64_t i = walk_thread(back);
+  const uint64_t i = walk_thread(turn);
   const float4 a = reinterpret_cast<const float4*>(st)[i];
   const float4 b{dpp_mv<0xB1>(a.x), dpp_mv<0xB1>(a.y), dpp_mv<0xB1>(a.z), dpp_mv<0xB1>(a.w)};
   const int hi = (int)(i & 1);  // address bit 1 of this thread's pair
@@ -167,8 +169,8 @@ __global__ __launch_bounds__(256) void k_gate2_pair_f32(float* __restrict__ st, 
 }
 
 template <typename T>
-__global__ void k_diag(T* __restrict__ st, uint64_t n_amp, int k, int q0, int q1, int q2, int q3, int q4, Diag32 D, int back) {
-  const uint64_t i = walk_thread(back);
+__global__ void k_diag(T* __restrict__ st, uint64_t n_amp, int k, int q0, int q1, int q2, int q3, int q4, Diag32 D, uint32_t turn) {
+  const uint64_t i = walk_thread(turn);
   if (i >= n_amp) return;
   const int qs[5] = {q0, q1, q2, q3, q4};
   int loc = 0;
@@ -181,12 +183,12 @@ __global__ void k_diag(T* __restrict__ st, uint64_t n_amp, int k, int q0, int q1
 template <typename T, int K>
 __global__ __launch_bounds__(256) void k_fused(T* __restrict__ st, uint64_t n_groups,
                                                const double* __restrict__ mat, int q0, int q1,
-                                               int q2, int q3, int q4, int back) {
+                                               int q2, int q3, int q4, uint32_t turn) {
   constexpr int N = 1 << K;
   __shared__ T sm[2 * N * N];
   for (int i = threadIdx.x; i < 2 * N * N; i += blockDim.x) sm[i] = (T)mat[i];
   __syncthreads();
-  const uint64_t g = walk_thread(back);
+  const uint64_t g = walk_thread(turn);
   if (g >= n_groups) return;
   const int qs[5] = {q0, q1, q2, q3, q4};
   // insert zeros at the sorted qubit positions
@@ -633,8 +635,8 @@ __global__ __launch_bounds__(256) void k_measure_decide(const double2* __restric
 }
 
 template <typename T>
-__global__ void k_project(T* __restrict__ st, uint64_t n_pairs, int q, const MeasOut* __restrict__ mo, int back) {
-  const uint64_t p = walk_thread(back);
+__global__ void k_project(T* __restrict__ st, uint64_t n_pairs, int q, const MeasOut* __restrict__ mo, uint32_t turn) {
+  const uint64_t p = walk_thread(turn);
   if (p >= n_pairs) return;
   const int m = mo->m;
   const double Sm = m ? mo->S1 : mo->S0;

@@ -2832,10 +2832,20 @@ struct sv_state_s {
   hipEvent_t mat_ev[8] = {};
   bool mat_used[8] = {};
   int mat_next = 0;
-  int back = 0;  // direction of the last pass over the register (walk_thread)
+  int back = 0;  // direction of the last pass over the register (next_walk)
 };
-// Direction of the next pass over s's register.
-static int next_walk(sv_state s) { return s->back ^= 1; }
+// Direction of the next pass over s's register (1: highest addresses first).  A
+// register that fits the 256 MB last-level cache is walked forwards always: it
+// has nothing to gain there, and backwards a workgroup's amplitudes are in
+// another die's L2 (gates, alternating and forwards: 22 qubits complex64 15 and
+// 9 us, 20 qubits complex128 12 and 7, 256 MiB within 3 %).  Larger ones
+// alternate: 25 qubits complex128 158 us, forwards 193; 26 qubits 360 and 396.
+static int next_walk(sv_state s) {
+  constexpr size_t kLastLevelCache = (size_t)256 << 20;
+  return s->bytes > kLastLevelCache ? s->back ^= 1 : 0;
+}
+// The same for a launch of `grid` workgroups, a power of two (walk_thread).
+static uint32_t next_turn(sv_state s, unsigned grid) { return next_walk(s) ? grid - 1 : 0u; }
 
 static constexpr int kMeasGrid = 1024;
 static constexpr int kMatSlots = 8;
@@ -3013,10 +3023,10 @@ sv_status sv_apply_gate(sv_state s, int k, const int* qubits, const double* m) {
     const uint64_t np = na >> 1;
     if (s->dt == SV_C128)
       hipLaunchKernelGGL(k_gate1<double>, dim3(grid_for(np, 256)), dim3(256), 0, s->stream,
-                         (double*)s->ptr, np, qubits[0], M, next_walk(s));
+                         (double*)s->ptr, np, qubits[0], M, next_turn(s, grid_for(np, 256)));
     else
       hipLaunchKernelGGL(k_gate1<float>, dim3(grid_for(np, 256)), dim3(256), 0, s->stream,
-                         (float*)s->ptr, np, qubits[0], M, next_walk(s));
+                         (float*)s->ptr, np, qubits[0], M, next_turn(s, grid_for(np, 256)));
   } else if (qubits[0] + qubits[1] == 1 && s->n >= 9) {
     // qubits 0 and 1: one amplitude per thread, quadruples exchanged within
     // DPP quads (whole 256-thread blocks)
@@ -3025,20 +3035,21 @@ sv_status sv_apply_gate(sv_state s, int k, const int* qubits, const double* m) {
     const dim3 g((unsigned)(na / 256)), b(256);
     const int swap = qubits[0] == 1;
     if (s->dt == SV_C128)
-      hipLaunchKernelGGL(k_gate2_quad<double>, g, b, 0, s->stream, (double*)s->ptr, swap, M, next_walk(s));
+      hipLaunchKernelGGL(k_gate2_quad<double>, g, b, 0, s->stream, (double*)s->ptr, swap, M,
+                         next_turn(s, g.x));
     else  // two amplitudes per thread: half the threads
       hipLaunchKernelGGL(k_gate2_pair_f32, dim3((unsigned)(na / 512)), b, 0, s->stream, (float*)s->ptr,
-                         swap, M, next_walk(s));
+                         swap, M, next_turn(s, (unsigned)(na / 512)));
   } else {
     Mat4 M;
     std::memcpy(M.m, m, sizeof M.m);
     const uint64_t nq = na >> 2;
     if (s->dt == SV_C128)
       hipLaunchKernelGGL(k_gate2<double>, dim3(grid_for(nq, 256)), dim3(256), 0, s->stream,
-                         (double*)s->ptr, nq, qubits[0], qubits[1], M, next_walk(s));
+                         (double*)s->ptr, nq, qubits[0], qubits[1], M, next_turn(s, grid_for(nq, 256)));
     else
       hipLaunchKernelGGL(k_gate2<float>, dim3(grid_for(nq, 256)), dim3(256), 0, s->stream,
-                         (float*)s->ptr, nq, qubits[0], qubits[1], M, next_walk(s));
+                         (float*)s->ptr, nq, qubits[0], qubits[1], M, next_turn(s, grid_for(nq, 256)));
   }
   HIP_OK(hipGetLastError());
   return SV_OK;
@@ -3055,10 +3066,10 @@ sv_status sv_apply_diag(sv_state s, int k, const int* qubits, const double* phas
   const uint64_t na = 1ull << s->n;
   if (s->dt == SV_C128)
     hipLaunchKernelGGL(k_diag<double>, dim3(grid_for(na, 256)), dim3(256), 0, s->stream,
-                       (double*)s->ptr, na, k, q[0], q[1], q[2], q[3], q[4], D, next_walk(s));
+                       (double*)s->ptr, na, k, q[0], q[1], q[2], q[3], q[4], D, next_turn(s, grid_for(na, 256)));
   else
     hipLaunchKernelGGL(k_diag<float>, dim3(grid_for(na, 256)), dim3(256), 0, s->stream,
-                       (float*)s->ptr, na, k, q[0], q[1], q[2], q[3], q[4], D, next_walk(s));
+                       (float*)s->ptr, na, k, q[0], q[1], q[2], q[3], q[4], D, next_turn(s, grid_for(na, 256)));
   HIP_OK(hipGetLastError());
   return SV_OK;
 }
@@ -3160,14 +3171,15 @@ sv_status sv_apply_fused(sv_state s, int k, const int* qubits, const double* m) 
   for (int i = 0; i < k; ++i) wide = wide && q[i] > 0;
   const dim3 g(grid_for(ng, 256)), b(256);
   const int back = next_walk(s);
+  const uint32_t turn = back ? g.x - 1 : 0u;
 #define QEC_FUSED(K)                                                                             \
   case K:                                                                                       \
     if (s->dt == SV_C128)                                                                       \
       hipLaunchKernelGGL((k_fused<double, K>), g, b, 0, s->stream, (double*)s->ptr, ng, dm, q[0], \
-                         q[1], q[2], q[3], q[4], back);                                               \
+                         q[1], q[2], q[3], q[4], turn);                                               \
     else                                                                                        \
       hipLaunchKernelGGL((k_fused<float, K>), g, b, 0, s->stream, (float*)s->ptr, ng, dm, q[0],   \
-                         q[1], q[2], q[3], q[4], back);                                               \
+                         q[1], q[2], q[3], q[4], turn);                                               \
     break;
 #define QEC_FUSED_MFMA(K)                                                                        \
   case K:                                                                                       \
@@ -3235,10 +3247,10 @@ static sv_status measure_common(sv_state s, int anc, double u, int forced, int* 
   const uint64_t np = na >> 1;
   if (s->dt == SV_C128)
     hipLaunchKernelGGL(k_project<double>, dim3(grid_for(np, 256)), dim3(256), 0, s->stream,
-                       (double*)s->ptr, np, anc, s->mo, next_walk(s));
+                       (double*)s->ptr, np, anc, s->mo, next_turn(s, grid_for(np, 256)));
   else
     hipLaunchKernelGGL(k_project<float>, dim3(grid_for(np, 256)), dim3(256), 0, s->stream,
-                       (float*)s->ptr, np, anc, s->mo, next_walk(s));
+                       (float*)s->ptr, np, anc, s->mo, next_turn(s, grid_for(np, 256)));
   HIP_OK(hipGetLastError());
   MeasOut mo;
   HIP_OK(hipMemcpyAsync(&mo, s->mo, sizeof mo, hipMemcpyDeviceToHost, s->stream));
