@@ -3165,9 +3165,10 @@ sv_status sv_apply_fused(sv_state s, int k, const int* qubits, const double* m) 
   // 436 -> 472 us, and keeps the direct kernel)
   bool low = mfma && s->dt == SV_C64;
   for (int i = 0; i < k; ++i) low = low && q[i] < k;
-  // complex64, bit 0 no target, 32 groups or more: two groups a lane (26
-  // qubits, k = 5: 257 -> 236 us)
-  bool wide = mfma && s->dt == SV_C64 && s->n - k >= 5;
+  // complex64, bit 0 no target: two groups a lane (26 qubits, k = 5: 257 -> 236
+  // us; 20 qubits 14.8 -> 14.0), from a tile of 32 groups a SIMD on: with fewer
+  // the halved number of waves costs more (18 qubits, k = 5: 11.9 -> 12.8 us)
+  bool wide = mfma && s->dt == SV_C64 && ng / 32 >= 4 * (uint64_t)device_cu_count();
   for (int i = 0; i < k; ++i) wide = wide && q[i] > 0;
   const dim3 g(grid_for(ng, 256)), b(256);
   const int back = next_walk(s);
