@@ -363,15 +363,18 @@ sv_status sv_tuning_get(int d, int dtype, sv_tuning* out);
 /* Replace the parameters for (d, dtype) on the current device; SV_EINVAL if
  * a field is out of range. */
 sv_status sv_tuning_set(int d, int dtype, const sv_tuning* in);
-/* Time candidate parameters on synthetic work of this shape (tens of ms of
- * device time) and keep the fastest for (d, dtype) on the current device:
+/* Time candidate parameters on synthetic work of this shape (up to a few
+ * seconds of device time) and keep the fastest for (d, dtype) on the current device:
  * d = 5, sv_run_rounds (one trajectory, one round): xpair x zchain x snake x
  *   pass_wgs_per_cu;
- * d = 4, sv_run_batch (4096 trajectories, 3 rounds, without the passes that
- *   change the basis): xpair x zchain x lockstep_mib;
+ * d = 4, sv_run_batch (4096 trajectories, 3 rounds): xpair x zchain x
+ *   lockstep_mib;
  * d <= 3, sv_run_batch (16384 trajectories, 3 rounds): batch_waves_per_cu.
- * Writes the winner to *best and its device time to *best_ms (either may be
- * NULL).  Synchronous, on the default stream; call it before serving, not
+ * Batches are timed without the data ZZ layer and with it (zeta = 0.01), which
+ * take different kernels, d = 5 runs with it (without it their passes have
+ * nothing to choose).  Writes the winner to *best and its device time (of both
+ * batches together) to *best_ms (either may be NULL).  After an error the
+ * parameters are those of before.  Synchronous, on the default stream; call it before serving, not
  * while other threads run jobs of the same shape. */
 sv_status sv_autotune(int d, int dtype, int gateset, sv_tuning* best, double* best_ms);
 /* Write / read the parameters of the current device's architecture as text

@@ -2147,7 +2147,6 @@ struct BatchInputs {
   bool no_memory = false;       // out: an allocation failed
   bool run = false;             // a run of sv_run_rounds: bits that depend neither on how many trajectories
                                 // run beside one nor on what is asked for (two waves each, TRACE kernels)
-  bool no_flip = false;         // d = 4: no basis change (the autotuner's trials: its choices are the other passes')
 };
 
 template <typename T>
@@ -2427,7 +2426,7 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
   const int per_traj = in.max_rounds * ns;
   const int spec_env = env_int("QECSV_SPEC", -1);
   FlipPlan fplan;
-  if (spec_env < 0 && in.zeta == 0.0 && !tp.any_dense && !in.no_flip) fplan = make_flip_plan(d, tp, false);
+  if (spec_env < 0 && in.zeta == 0.0 && !tp.any_dense) fplan = make_flip_plan(d, tp, false);
   const bool flip = !fplan.units.empty();
   const std::vector<Unit> units = flip ? fplan.units : make_units_paired(tp, tune.zchain, n, tune.xpair);
   const int nu = (int)units.size();
@@ -3823,10 +3822,14 @@ sv_status sv_autotune(int d, int dtype, int gateset, sv_tuning* best, double* be
   const Template tp = build_template(d, gateset);
   const TuneKey key{current_device(), d, dtype};
   sv_tuning base = default_tuning();
+  bool had = false;  // parameters of this key before
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     const auto it = g_tune.find(key);
-    if (it != g_tune.end()) base = it->second;
+    if (it != g_tune.end()) {
+      base = it->second;
+      had = true;
+    }
   }
   std::vector<sv_tuning> cands;
   if (d == 5) {
@@ -3892,11 +3895,15 @@ sv_status sv_autotune(int d, int dtype, int gateset, sv_tuning* best, double* be
                                        : run_rounds_t<float>(&job, &res, tp));
       *ms = res.gpu_ms;
     } else {
-      BatchInputs in{d, gateset, nt, R, 0.0, seeds.data(), streams.data(), rounds.data(), pv.data(),
-                     eps.data(), 0, rec.data(), bits.data(), (hipStream_t)nullptr, 0.0};
-      in.no_flip = true;
-      SV_OK_OR_RETURN(dtype == SV_C128 ? run_batch_core<double>(in, tp) : run_batch_core<float>(in, tp));
-      *ms = in.gpu_ms;
+      // without the data ZZ layer and with it: other kernels, with parameters
+      // of their own (d = 4: xpair and zchain are the plain passes') and in common
+      *ms = 0.0;
+      for (double zeta : {0.0, 0.01}) {
+        BatchInputs in{d, gateset, nt, R, zeta, seeds.data(), streams.data(), rounds.data(), pv.data(),
+                       eps.data(), 0, rec.data(), bits.data(), (hipStream_t)nullptr, 0.0};
+        SV_OK_OR_RETURN(dtype == SV_C128 ? run_batch_core<double>(in, tp) : run_batch_core<float>(in, tp));
+        *ms += in.gpu_ms;
+      }
     }
     return SV_OK;
   };
@@ -3917,7 +3924,8 @@ sv_status sv_autotune(int d, int dtype, int gateset, sv_tuning* best, double* be
   const sv_tuning chosen = (st == SV_OK && win >= 0) ? cands[win] : base;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tune[key] = chosen;
+    if (st == SV_OK || had) g_tune[key] = chosen;
+    else g_tune.erase(key);  // as untuned as before
   }
   if (st != SV_OK) return st;
   if (best) *best = chosen;
