@@ -1210,7 +1210,7 @@ uint32_t check_mask(const TBlock& b) {
   return m;
 }
 
-bool plan_flips(int n, const Template& tp, FlipPlan& P) {
+bool plan_flips(const Template& tp, FlipPlan& P) {
   const uint32_t low = (1u << kFlipLow) - 1;
   const int ns = (int)tp.blocks.size();
   uint32_t xb = 0;  // qubits in the Hadamard basis
@@ -1242,7 +1242,6 @@ bool plan_flips(int n, const Template& tp, FlipPlan& P) {
     P.flips.push_back(F);
     c += len;
   }
-  (void)n;
   return xb == 0;
 }
 
@@ -1472,7 +1471,7 @@ void flip_init_state(const Template& tp, int d, bool plus, uint32_t T, FlipPass&
 FlipPlan make_flip_plan(int d, const Template& tp, bool plus) {
   FlipPlan P;
   const int n = d * d;
-  if (n < kTileMax || !plan_flips(n, tp, P)) return FlipPlan{};
+  if (n < kTileMax || !plan_flips(tp, P)) return FlipPlan{};
   const int nu = (int)P.units.size();
   P.passes.resize(nu + 2);
   P.passes[0] = make_flip_pass(n, tp, nullptr, &P.units[0], 0u);
@@ -2737,8 +2736,7 @@ sv_status run_batch_lockstep(BatchInputs& in, const Template& tp) {
 // by passes, 156 here; 500 of five rounds, records only: 1020, 480).  Taken
 // with graph replay too: one launch has nothing to replay.
 template <typename T>
-sv_status run_rounds_small(const sv_job* job, sv_result* res, const Template& tp, const std::atomic<int>* cancel,
-                           hipEvent_t done) {
+sv_status run_rounds_small(const sv_job* job, sv_result* res, const Template& tp, hipEvent_t done) {
   const int n = job->d * job->d, R = job->rounds;
   const size_t per_traj = (size_t)R * tp.blocks.size(), reg = sizeof(C2<T>) << n;
   // (at most 256 MiB of results on the device at a time)
@@ -2752,7 +2750,6 @@ sv_status run_rounds_small(const sv_job* job, sv_result* res, const Template& tp
   std::vector<uint64_t> streams(most);
   double ms = 0.0;
   for (int t0 = 0, cnt; t0 < job->n_traj; t0 += cnt) {
-    if (cancel && cancel->load(std::memory_order_relaxed)) return fail(SV_EBUSY, "cancelled");
     cnt = std::min(most, job->n_traj - t0);
     for (int i = 0; i < cnt; ++i) streams[i] = job->traj0 + (uint64_t)(t0 + i);
     BatchInputs in{job->d, job->gateset, cnt, R, job->zeta, seeds.data(), streams.data(), rounds.data(), p.data(),
@@ -2781,7 +2778,8 @@ sv_status run_rounds_small(const sv_job* job, sv_result* res, const Template& tp
   return SV_OK;
 }
 
-// Every run of sv_run_rounds and the server.  What the on-chip launch does
+// Every run of sv_run_rounds, and the server's d = 5 jobs (the only ones with
+// a cancel flag).  What the on-chip launch does
 // not have - twirled angles, the X basis, idle noise (more draws), dense
 // blocks - keeps the passes, and so do d >= 4 and the forced pass kinds.
 template <typename T>
@@ -2789,7 +2787,7 @@ sv_status run_job(const sv_job* job, sv_result* res, const Template& tp, const s
                   hipEvent_t done = nullptr) {
   const bool plain = (job->flags & ~(uint32_t)(SV_RUN_GRAPH | SV_RUN_VIRTUAL_Z)) == 0;
   if (plain && !tp.any_dense && env_int("QECSV_SPEC", -1) < 0 && batch_is_small(tp, job->d) && batch_template_fits(tp))
-    return run_rounds_small<T>(job, res, tp, cancel, done);
+    return run_rounds_small<T>(job, res, tp, done);
   return run_rounds_t<T>(job, res, tp, cancel, done);
 }
 
