@@ -76,3 +76,19 @@ def test_fused_several_tiles_a_wave(n, qubits):
         ref = _apply(ref, n, qubits, m)
     # two sums of 32 complex terms on a vector of norm 1
     assert float(torch.abs(t - ref).max()) < 270 * 2.0**-24
+
+
+@pytest.mark.parametrize("n,qubits", [(18, [17, 1, 9, 4]), (19, [1, 18, 9, 4]), (19, [5, 1, 17, 13, 2]),
+                                      (20, [1, 2, 3, 4, 19])])
+def test_fused_at_the_edge_of_two_groups_a_lane(n, qubits):
+    """The largest registers that take one group a lane and the smallest that
+    take two: a tile of 32 groups a SIMD on 256 compute units."""
+    import torch
+    print(f"case fused edge {n} {qubits}", flush=True)
+    t = _random(n, "c64")
+    ref = t.to(torch.complex128, copy=True)
+    s = qs.State(n, "c64", stream=torch.cuda.current_stream(), tensor=t)
+    m = _unitary(len(qubits), np.random.default_rng(n))
+    s.apply_fused(qubits, m)
+    # one sum of at most 32 complex terms on a vector of norm 1
+    assert float(torch.abs(t - _apply(ref, n, qubits, m)).max()) < 135 * 2.0**-24
