@@ -2739,8 +2739,9 @@ template <typename T>
 sv_status run_rounds_small(const sv_job* job, sv_result* res, const Template& tp, hipEvent_t done) {
   const int n = job->d * job->d, R = job->rounds;
   const size_t per_traj = (size_t)R * tp.blocks.size(), reg = sizeof(C2<T>) << n;
-  // (at most 256 MiB of results on the device at a time)
-  const size_t bytes = per_traj * (res->p1_trace ? 9 : 1) + n + (res->final_states ? reg : 0);
+  // (at most 256 MiB on the device at a time: results, and 32 bytes of draw
+  // stream, seed, p, rounds and place in the order)
+  const size_t bytes = per_traj * (res->p1_trace ? 9 : 1) + n + 32 + (res->final_states ? reg : 0);
   int most = done ? job->n_traj : (int)std::max<size_t>(1, std::min<size_t>(job->n_traj, ((size_t)256 << 20) / bytes));
   std::vector<double> eps(std::max(1, tp.n_sites), job->eps);
   if (job->eps_site) std::copy(job->eps_site, job->eps_site + tp.n_sites, eps.begin());

@@ -125,3 +125,18 @@ def test_short_device_memory(tmp_path, mib, kw):
         most.value = 1 << 40
         assert same(a, qs.run_rounds(**kw)) and refused.value == n
     """)
+
+
+def test_small_runs_stay_within_their_limit(tmp_path):
+    """Ten million d = 2 trajectories of one round: seven bytes of results each
+    and 32 of parameters, 256 MiB at a time and 1 MiB for the tables."""
+    print("case limit of small runs", flush=True)
+    _run(tmp_path, """
+        most.value = 257 << 20
+        a = qs.run_rounds(d=2, gateset="cr", rounds=1, n_traj=10_000_000, seed=3, p=0.02, eps=0.02, dtype="c64")
+        assert refused.value == 0
+        n = 8_000_000
+        b = qs.run_rounds(d=2, gateset="cr", rounds=1, n_traj=1000, seed=3, p=0.02, eps=0.02, dtype="c64", traj0=n)
+        assert np.array_equal(a["records"][n:n + 1000], b["records"])
+        assert np.array_equal(a["final_bits"][n:n + 1000], b["final_bits"])
+    """)
