@@ -259,13 +259,16 @@ typedef struct sv_result {
                            final measurement, or NULL */
   double gpu_ms;        /* out: device time of the whole run (hipEvents) */
   double pass_ms;       /* out: mean device time per register pass of the last
-                           trajectory's second round, or its only one (one pass applies an X check, a pair of
-                           them or a chain of checks; with speculative units,
-                           their prediction passes); d <= 4, whose
-                           trajectories run side by side: per pass and
-                           trajectory of the last group, its decisions
-                           included (d <= 3 in one launch: that launch's
-                           share) */
+                           trajectory's second round, or its only one (one pass
+                           applies an X check, a pair of them or a chain of
+                           checks; with speculative units, their prediction
+                           passes); where large registers run side by side
+                           (complex64, d = 5, zeta = 0: up to four), a
+                           register's share of a launch over the last of them;
+                           d <= 4, whose trajectories run side by side: per
+                           pass and trajectory of the last group, its
+                           decisions included (d <= 3 in one launch: that
+                           launch's share) */
   int passes_per_round; /* out: register passes per round (speculative units:
                            prediction passes per round) */
   int redo_passes;      /* out: speculative units' redo passes that ran, over
@@ -291,9 +294,10 @@ typedef struct sv_result {
  * that) and the pass runs again when a drawn outcome differs.  Records, p1 and
  * states are those of the plain passes.  With d <= 3 and no flag but
  * SV_RUN_VIRTUAL_Z the whole run is one launch that keeps each register on
- * chip (passes_per_round then counts the passes it stands for).  The environment variable QECSV_SPEC =
- * 0 / 1 asks for the plain / the speculative passes whatever zeta is (not with
- * the dense crosstalk, which always uses the plain passes). */
+ * chip (passes_per_round then counts the passes it stands for).  The
+ * environment variable QECSV_SPEC = 0 / 1 asks for the plain / the speculative
+ * passes whatever zeta is (not with the dense crosstalk, which always uses the
+ * plain passes). */
 sv_status sv_run_rounds(const sv_job* job, sv_result* res);
 
 /* The same run enqueued without waiting, so that jobs on several streams
@@ -358,7 +362,9 @@ typedef struct sv_tuning {
                              amplitudes; 0: one X check per pass */
 } sv_tuning;
 
-/* Effective parameters (set, tuned or built-in, then the environment). */
+/* Effective parameters (set, tuned or built-in, then the environment; for a
+ * d = 5 shape that was never set or tuned the built-in ones, whose zchain and
+ * pass_wgs_per_cu its runs replace as said there). */
 sv_status sv_tuning_get(int d, int dtype, sv_tuning* out);
 /* Replace the parameters for (d, dtype) on the current device; SV_EINVAL if
  * a field is out of range. */
@@ -374,8 +380,8 @@ sv_status sv_tuning_set(int d, int dtype, const sv_tuning* in);
  * take different kernels, d = 5 runs with it (without it their passes have
  * nothing to choose).  Writes the winner to *best and its device time (of both
  * batches together) to *best_ms (either may be NULL).  After an error the
- * parameters are those of before.  Synchronous, on the default stream; call it before serving, not
- * while other threads run jobs of the same shape. */
+ * parameters are those of before.  Synchronous, on the default stream; call it
+ * before serving, not while other threads run jobs of the same shape. */
 sv_status sv_autotune(int d, int dtype, int gateset, sv_tuning* best, double* best_ms);
 /* Write / read the parameters of the current device's architecture as text
  * lines "arch d dtype zchain snake batch_waves_per_cu lockstep_mib

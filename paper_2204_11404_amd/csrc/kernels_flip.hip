@@ -25,7 +25,7 @@
 // (4.9-5.3 TB/s; 95 us without flips).  Above that rate lie the waits between
 // a tile's load, regroup and store.  A round: complex64 1.55 -> 0.53 ms,
 // complex128 2.4 -> 1.04 ms against the eight speculative passes and their
-// redos; 4096 d = 4 trajectories (complex64) 42.7 -> 17.4 ms.
+// redos; 4096 d = 4 trajectories (complex64) 42.7 -> 18.5 ms.
 //
 // Pauli frames: the XOR permutations are not carried out.  The stored
 // register is s Z^phix X^phiz |psi> written in the mixed basis; a Z member

@@ -337,7 +337,8 @@ __global__ __launch_bounds__(256) void k_fused_mfma(T* __restrict__ st, uint64_t
 // moves two neighbouring amplitudes at a time, the same element of two groups
 // (16-byte accesses, runs of 256 bytes instead of 128), and a wave owns 32
 // groups, two B tiles against one copy of the matrix.  Bound by HBM in pieces
-// of 256 bytes (26 qubits, k = 5: 257 -> 232-240 us, 4.6 TB/s; the products
+// of 256 bytes (26 qubits, k = 5: 257 -> 232-240 us, 4.6 TB/s one way, 198 in
+// turn; the products
 // alone take some 110 us; two, three or four waves a SIMD, with the next
 // tile's loads ahead or without, are within 3 %).
 template <int K>

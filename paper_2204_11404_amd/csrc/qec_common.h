@@ -722,8 +722,9 @@ QEC_HD uint32_t flip_place(uint32_t g) {
 // per slot, which the LDS instructions carry as their offset.  The strides of
 // thread bits 3 and 4 are 8 and 16 modulo the 32 eight-byte banks in both
 // layouts, so 32 lanes reach 32 banks.  complex64 moves whole amplitudes (two
-// barriers a tile); complex128 real parts, then imaginary parts, through a
-// buffer of the same size (four barriers, but three workgroups per CU).
+// barriers a tile); complex128 real parts, then imaginary parts (four barriers
+// a tile) through a buffer of the same size, half of what whole amplitudes
+// would take.
 struct FlipLds {
   // strides of s0[0..3], s2[0..3], e (bits 0..2: 1, 2, 4); each exceeds the
   // sum of the smaller ones, so no two places coincide

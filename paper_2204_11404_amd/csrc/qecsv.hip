@@ -1053,7 +1053,7 @@ void launch_wht_all(hipStream_t s, T* st, int n, int slots) {
   }
 }
 
-// Pass launches (compiled apart from this file, see passes.inc): a status of
+// Pass launches (compiled apart from this file, see passes.hip): a status of
 // the launch tables as an sv_status.
 sv_status pass_status(int r) {
   if (r == kLaunchNoTable) return fail(SV_EINVAL, "dense unit without its Kraus table");
@@ -1531,9 +1531,13 @@ constexpr int kLargeSlots = 4;
 // Which passes run.  Without the data ZZ layer (zeta = 0) a d = 5 register
 // takes the passes with a basis change (k_flip): five a round, none redone,
 // one register (complex64, p = 2e-3: 0.53 ms a round against 1.55 with the
-// speculative units, complex128 1.04 against 2.4).  d = 4 keeps the
-// speculative units here, whose count callers read in passes_per_round;
-// batches of d = 4 trajectories take the basis change (run_batch_lockstep).
+// speculative units, complex128 1.04-1.08 against 2.4).  d = 4 runs keep the
+// speculative units, whose count callers read in passes_per_round: the basis
+// change halves their device time, but laying out its plan takes some 0.4 ms of
+// each call, so that few trajectories gain nothing (complex64, whole calls: one
+// of five rounds 865 us, by the basis change 892; six of three 705 and 819; 60
+// of five 1845 and 1257; 300 5.05 ms and 2.74).  Batches of d = 4 trajectories
+// take the basis change (run_batch_lockstep).
 // With the layer the plain passes run: it is diagonal in the computational
 // basis only, and the X checks cannot be summed together across it.
 // QECSV_SPEC = 0 / 1 asks for the plain / speculative passes whatever zeta is.
@@ -3164,7 +3168,7 @@ sv_status sv_apply_fused(sv_state s, int k, const int* qubits, const double* m) 
   bool low = mfma && s->dt == SV_C64;
   for (int i = 0; i < k; ++i) low = low && q[i] < k;
   // complex64, bit 0 no target: two groups a lane (26 qubits, k = 5: 257 -> 236
-  // us; 20 qubits 14.8 -> 14.0), from a tile of 32 groups a SIMD on: with fewer
+  // us one way, 224 -> 198 in turn; 20 qubits 14.8 -> 14.0), from a tile of 32 groups a SIMD on: with fewer
   // the halved number of waves costs more (18 qubits, k = 5: 11.9 -> 12.8 us)
   bool wide = mfma && s->dt == SV_C64 && ng / 32 >= 4 * (uint64_t)device_cu_count();
   for (int i = 0; i < k; ++i) wide = wide && q[i] > 0;
